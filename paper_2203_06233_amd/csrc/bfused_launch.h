@@ -33,7 +33,7 @@ template <int NB, int NS, int NW, int MODE>
 hipError_t gob(const ProbDesc* desc, int n, long long total, int refine, hipStream_t st, unsigned long long* queue) {
   constexpr int L = nsl(NB, NW), M = nsm(NB, NS, NW);
   // enough workgroups to fill every CU a few times over, never more than systems
-  const long long want = 256LL * (NW == 4 ? 4 : 2);
+  const long long want = 256LL * (16 / NW);
   const dim3 grid((unsigned)(total < want ? total : want)), block(64 * NW);
   if (refine == 0)
     hipLaunchKernelGGL((bfused_batched_kernel<NB, NS, L, M, NW, MODE, false>), grid, block, 0, st, desc, n, total,
@@ -43,6 +43,12 @@ hipError_t gob(const ProbDesc* desc, int n, long long total, int refine, hipStre
                        queue);
   return hipGetLastError();
 }
+
+// Waves per system: one or two where the system has one or two block columns
+// (their few blocks leave more waves idle at every barrier), four up to 64
+// DOF, and at 96 DOF four or eight as the variant asks.  Every count gives
+// the same bits.
+constexpr int nw_of(int NB) { return NB == 1 ? 1 : NB == 2 ? 2 : 4; }
 
 // one switch for the single-cube and batched launches
 template <int MODE, class F>
@@ -58,8 +64,8 @@ hipError_t pick(int D, int S, int waves, F&& f) {
   using W4 = std::integral_constant<int, 4>;
   using W8 = std::integral_constant<int, 8>;
   switch (nb) {
-    case 1: return by_s(std::integral_constant<int, 1>{}, W4{});
-    case 2: return by_s(std::integral_constant<int, 2>{}, W4{});
+    case 1: return by_s(std::integral_constant<int, 1>{}, std::integral_constant<int, nw_of(1)>{});
+    case 2: return by_s(std::integral_constant<int, 2>{}, std::integral_constant<int, nw_of(2)>{});
     case 3: return by_s(std::integral_constant<int, 3>{}, W4{});
     case 4: return by_s(std::integral_constant<int, 4>{}, W4{});
     case 5: case 6:
@@ -69,20 +75,19 @@ hipError_t pick(int D, int S, int waves, F&& f) {
   return hipErrorInvalidValue;
 }
 
-// The wave count pick() takes for D and the requested waves.
-inline int pick_waves(int D, int waves) {
+// Whether pick() takes eight waves for D and the requested waves.
+inline bool pick_eight(int D, int waves) {
   const int nb = (D + 15) / 16;
-  return nb <= 4 ? 4 : nb <= 6 ? (waves == 8 ? 8 : 4) : 8;
+  return nb > 6 || (nb > 4 && waves == 8);
 }
 
-// One-cube launches of the shapes that run on NWSEL waves (the 4- and 8-wave
-// kernels live in separate translation units, built with different
-// lane_tid() forms).
-template <int MODE, int NWSEL>
+// One-cube launches of the shapes that run on eight waves, or of the others
+// (in separate translation units, which build in parallel).
+template <int MODE, bool EIGHT>
 hipError_t single(const Dims& d, const float2* snap, const float2* steer, float2* w, int* info, hipStream_t st,
                   int waves) {
   return pick<MODE>(d.D, d.S, waves, [&](auto nb, auto ns, auto nw) -> hipError_t {
-    if constexpr (decltype(nw)::value == NWSEL)
+    if constexpr ((decltype(nw)::value == 8) == EIGHT)
       return go1<decltype(nb)::value, decltype(ns)::value, decltype(nw)::value, MODE>(d, snap, steer, w, info, st);
     else
       return hipErrorInvalidValue;

@@ -8,10 +8,54 @@ namespace stap {
 
 namespace {
 
+// R_L in global memory, of which the lower triangle is read.
 struct GlobalRB {
   const float2* A;
   int D;
-  __device__ float2 lower(int i, int k) const { return A[(long long)i * D + k]; }
+  bool vec;  // rows16(A, D)
+  // Lane (m, q): R[16I + m][16J + 4q + i], i = 0..3 (J <= I), identity beyond D.
+  __device__ __forceinline__ Acc block(int I, int J) const {
+    const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
+    const int r = 16 * I + m, c0 = 16 * J + 4 * q;
+    Acc a;
+    float2 v[4];
+    if (J < I) {
+      load4(A, r, c0, r < D, D, vec, v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = c0 + i;
+        v[i] = make_float2(r == c ? 1.f : 0.f, 0.f);
+        if (r < D && c < D) {
+          v[i] = c <= r ? A[r * D + c] : A[c * D + r];
+          if (c > r) v[i].y = -v[i].y;
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a.re[i] = v[i].x;
+      a.im[i] = v[i].y;
+    }
+    return a;
+  }
+  __device__ __forceinline__ Acc get(int J, int I, int) const {
+    if (J <= I) {  // conj(R[16I + m][16J + 4q + s])
+      Acc a = block(I, J);
+      a.im = -a.im;
+      return a;
+    }
+    const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
+    Acc a;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 16 * J + 4 * q + i, c = 16 * I + m;
+      const float2 v = (r < D && c < D) ? A[r * D + c] : make_float2(0.f, 0.f);
+      a.re[i] = v.x;
+      a.im[i] = v.y;
+    }
+    return a;
+  }
 };
 
 // With refinement and 8 waves the register allocation is capped at 128 so
@@ -25,13 +69,34 @@ void bsolve_kernel(const float2* __restrict__ cov,
   using C = BCfg<NSL, NSM, NW>;
   extern __shared__ __align__(16) unsigned char lds[];
   const int sys = blockIdx.x;
-  bsolve_system<C, REFINE>(GlobalRB{cov + (long long)sys * d.D * d.D, d.D}, steer + steer_offset(d, sys),
-                           wout + (long long)sys * d.S * d.D, info_out ? info_out + sys : nullptr, d, lds);
+  const float2* const A = cov + (long long)sys * d.D * d.D;
+  const float2* const V = steer + steer_offset(d, sys);
+  const GlobalRB R{A, d.D, rows16(A, d.D)};
+  const Slots<C> sl(d.D, d.S, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
+  const SolveLds<C, REFINE> L(lds, sl.NB, sl.NS);
+  const int m = lane_tid() & 15, q = (lane_tid() & 63) >> 4;
+  Acc al[NSL], am[NSM];
+#pragma unroll
+  for (int t = 0; t < NSL; ++t) {
+    al[t] = acc_zero();
+    if (sl.lv[t]) {
+      al[t] = R.block(sl.lr[t], sl.lc[t]);
+      if (sl.lr[t] == sl.lc[t]) {
+        const float rd = blk_diag(al[t]);
+        if (m >> 2 == q) L.rdiag[16 * sl.lr[t] + m] = rd;
+      }
+      al[t] = acc_neg(al[t]);
+    }
+  }
+  load_steer(sl, V, d.D, d.S, am);
+  for (int r = threadIdx.x; r < 16 * sl.NB; r += C::NT) L.d64[r] = 0.0;
+  bsolve_blocks<C, REFINE>(sl, al, am, L, R, V, wout + (long long)sys * d.S * d.D,
+                           info_out ? info_out + sys : nullptr, d, nullptr);
 }
 
 template <int NSL, int NSM, int NW, bool REFINE>
 hipError_t go_r(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info, hipStream_t st) {
-  const size_t lds = BCfg<NSL, NSM, NW>::lds_bytes((d.D + 15) / 16, (d.S + 15) / 16);
+  const size_t lds = BCfg<NSL, NSM, NW>::lds_bytes((d.D + 15) / 16, (d.S + 15) / 16, REFINE);
   if (lds > 48 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsolve_kernel<NSL, NSM, NW, REFINE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

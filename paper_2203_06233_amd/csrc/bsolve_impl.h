@@ -24,80 +24,70 @@
 // X[m][4q + i], i = 0..3.  This is the MFMA result layout of X^T, and the A
 // and B operand layouts of a product whose k index runs over the block
 // columns, so every product is formed transposed (X^T -= conj(Q) P^T) and no
-// block is ever shuffled.  In LDS a block keeps the same order (registers
-// 0-1 of all lanes, then registers 2-3), so a fragment load is two 16-byte
-// reads per lane with consecutive lanes on consecutive addresses.
+// block is ever shuffled.
+//
+// In LDS a block is two planes of 256 floats (real, imaginary), so a fragment
+// moves as two 16-byte accesses per lane straight from and to the registers
+// of the products.  Within a plane the 16-byte unit of row r, columns
+// 4c .. 4c+3 sits at 16 c + 4 (r / 4) + (r + c) % 4: the 16 lanes of a
+// fragment access and the 64 lanes of a transposed one (bofs) both fall on
+// distinct banks.  The interleaved complex layout before it needed register
+// moves around every access, and its transposed accesses fell eight lanes to
+// a bank.
 #pragma once
+
+#include <type_traits>
 
 #include "common.h"
 
 namespace stap {
 
-// The FP64 refinement residual either loads the operands of a block column's
-// four k-steps before their products (more registers, less exposed LDS
-// latency) or interleaves loads and products step by step.  Measured: the
-// first is faster in the 8-wave one-cube fused kernel (7.16 -> 7.03 ms on
-// the 32 x 256 x 16384 cube), the second in the persistent batched one
-// (48.0 against 50.0 ms on the uneven batch); translation units choose with
-// STAP_RESIDUAL_LOADS_AHEAD.
-#ifdef STAP_RESIDUAL_LOADS_AHEAD
-constexpr bool kResidualLoadsAhead = true;
-#else
-constexpr bool kResidualLoadsAhead = false;
-#endif
-
-
-struct Frag {
-  float2 v[4];
-};
 struct Acc {
   floatx4 re, im;
 };
 
-// Complex offset of element (r, c) of a block stored in fragment order: the
-// lane holding it is l = r + 16 (c / 4), its register i = c % 4; registers
-// 0-1 of every lane come first (16 bytes per lane), then registers 2-3, so
-// each of the two 16-byte accesses of a fragment covers one contiguous
-// kilobyte across the wave.
+constexpr int kBlk = 512;  // floats of one block in LDS
+
+// Offset of element (r, c) in a plane of a block.
 __device__ __forceinline__ int bofs(int r, int c) {
-  const int l = r + 16 * (c >> 2), i = c & 3;
-  return (i < 2 ? 0 : 128) + 2 * l + (i & 1);
+  const int cq = c >> 2;
+  return 4 * (16 * cq + 4 * (r >> 2) + ((r + cq) & 3)) + (c & 3);
+}
+// Offset of the lane's own X[m][4q .. 4q+3].
+__device__ __forceinline__ int nat_ofs() {
+  const int l = lane_tid() & 63;
+  return bofs(l & 15, 4 * (l >> 4));
 }
 
-__device__ __forceinline__ Frag frag_load(const float2* blk) {
-  const int l = lane_tid() & 63;
-  const float4 a = *reinterpret_cast<const float4*>(blk + 2 * l);
-  const float4 b = *reinterpret_cast<const float4*>(blk + 128 + 2 * l);
-  Frag f;
-  f.v[0] = make_float2(a.x, a.y);
-  f.v[1] = make_float2(a.z, a.w);
-  f.v[2] = make_float2(b.x, b.y);
-  f.v[3] = make_float2(b.z, b.w);
-  return f;
+__device__ __forceinline__ Acc blk_load(const float* blk, int nat) {
+  Acc a;
+  a.re = *reinterpret_cast<const floatx4*>(blk + nat);
+  a.im = *reinterpret_cast<const floatx4*>(blk + 256 + nat);
+  return a;
 }
-__device__ __forceinline__ void frag_store(float2* blk, const Frag& f) {
-  const int l = lane_tid() & 63;
-  *reinterpret_cast<float4*>(blk + 2 * l) = make_float4(f.v[0].x, f.v[0].y, f.v[1].x, f.v[1].y);
-  *reinterpret_cast<float4*>(blk + 128 + 2 * l) = make_float4(f.v[2].x, f.v[2].y, f.v[3].x, f.v[3].y);
+__device__ __forceinline__ void blk_store(float* blk, const Acc& a, int nat) {
+  *reinterpret_cast<floatx4*>(blk + nat) = a.re;
+  *reinterpret_cast<floatx4*>(blk + 256 + nat) = a.im;
 }
 // Store X^T: the lane's X[m][4q + i] goes to element (4q + i, m).
-__device__ __forceinline__ void frag_store_t(float2* blk, const Frag& f) {
+__device__ __forceinline__ void blk_store_t(float* blk, const Acc& a) {
   const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) blk[bofs(4 * q + i, m)] = f.v[i];
+  for (int i = 0; i < 4; ++i) {
+    const int o = bofs(4 * q + i, m);
+    blk[o] = a.re[i];
+    blk[256 + o] = a.im[i];
+  }
 }
-__device__ __forceinline__ Frag to_frag(const Acc& a) {
-  Frag f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f.v[i] = make_float2(a.re[i], a.im[i]);
-  return f;
-}
-__device__ __forceinline__ Acc to_acc(const Frag& f) {
+// The lane's X[4q + i][m], i = 0..3.
+__device__ __forceinline__ Acc blk_load_t(const float* blk) {
+  const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
   Acc a;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    a.re[i] = f.v[i].x;
-    a.im[i] = f.v[i].y;
+    const int o = bofs(4 * q + i, m);
+    a.re[i] = blk[o];
+    a.im[i] = blk[256 + o];
   }
   return a;
 }
@@ -115,47 +105,130 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
 // x -= P Q^H (SUB) or x += P Q^H.  As x^T -/+= conj(Q) P^T: MFMA A operand
 // conj(Q)[m][k], B operand P[m][k], k-quarter s covering k = 4 q' + s.
 template <bool SUB>
-__device__ __forceinline__ void mma_pqh(Acc& x, const Frag& P, const Frag& Q) {
+__device__ __forceinline__ void mma_pqh(Acc& x, const Acc& P, const Acc& Q) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const float qr = SUB ? -Q.v[s].x : Q.v[s].x, qi = SUB ? -Q.v[s].y : Q.v[s].y;
-    const float pr = P.v[s].x, pi = P.v[s].y;
-    x.re = mfma4(qr, pr, x.re);  // Re(conj(q) p) = qr pr + qi pi
-    x.re = mfma4(qi, pi, x.re);
-    x.im = mfma4(qr, pi, x.im);  // Im(conj(q) p) = qr pi - qi pr
-    x.im = mfma4(-qi, pr, x.im);
+    const float qr = SUB ? -Q.re[s] : Q.re[s], qi = SUB ? -Q.im[s] : Q.im[s];
+    x.re = mfma4(qr, P.re[s], x.re);  // Re(conj(q) p) = qr pr + qi pi
+    x.re = mfma4(qi, P.im[s], x.re);
+    x.im = mfma4(qr, P.im[s], x.im);  // Im(conj(q) p) = qr pi - qi pr
+    x.im = mfma4(-qi, P.re[s], x.im);
   }
 }
 
 // x -= P Q (SUB) or x += P Q, with Qt the fragment of Q^T.  As x^T -/+= Q^T P^T.
 template <bool SUB>
-__device__ __forceinline__ void mma_pq(Acc& x, const Frag& P, const Frag& Qt) {
+__device__ __forceinline__ void mma_pq(Acc& x, const Acc& P, const Acc& Qt) {
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const float qr = SUB ? -Qt.v[s].x : Qt.v[s].x, qi = SUB ? -Qt.v[s].y : Qt.v[s].y;
-    const float pr = P.v[s].x, pi = P.v[s].y;
-    x.re = mfma4(qr, pr, x.re);  // Re(q p) = qr pr - qi pi
-    x.re = mfma4(-qi, pi, x.re);
-    x.im = mfma4(qr, pi, x.im);  // Im(q p) = qr pi + qi pr
-    x.im = mfma4(qi, pr, x.im);
+    const float qr = SUB ? -Qt.re[s] : Qt.re[s], qi = SUB ? -Qt.im[s] : Qt.im[s];
+    x.re = mfma4(qr, P.re[s], x.re);  // Re(q p) = qr pr - qi pi
+    x.re = mfma4(-qi, P.im[s], x.re);
+    x.im = mfma4(qr, P.im[s], x.im);  // Im(q p) = qr pi + qi pr
+    x.im = mfma4(qi, P.re[s], x.im);
   }
 }
 
-__device__ __forceinline__ float2 shfl2(float2 v, int src) {
-  return make_float2(__shfl(v.x, src), __shfl(v.y, src));
-}
-__device__ __forceinline__ float bcast(float v, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
+// How the blocked solve forms its block products x += P Q^H and x += P Q.
+//
+// Without refinement: FP32 MFMA on the blocks themselves.
+//
+// With refinement: every published block is split exactly into three BF16
+// terms per component (x = h + m + l to 24 bits, as in the covariance) and
+// the six products hh, hm, mh, hl, lh, mm run on v_mfma_f32_16x16x32_bf16
+// with FP32 accumulation; a lane's eight values (four real, four imaginary)
+// are its k slice of one 32-deep product, so a complex block product is 12
+// instructions of 16 cycles instead of 16 of 32.  What decides is the unit,
+// not the cycles: FP32 (and FP64) MFMA occupies the vector ALU of its SIMD,
+// and while one wave streams it no other wave of the SIMD issues a VALU
+// instruction at any priority (measured: a wave's FMA goes from 5 cycles to
+// waiting until the stream ends; beside BF16 MFMA it takes 8), so the waves'
+// products froze the diagonal factorisation that everything else waits for.
+// The product errors are those of FP32 and the FP64 refinement removes them;
+// without refinement the FP32 arithmetic stays as it is.
+struct OpF32 {
+  typedef Acc Frag;
+  static constexpr int kB = kBlk;  // floats of a published block
+  static __device__ __forceinline__ Frag frag(const Acc& a) { return a; }
+  static __device__ __forceinline__ Frag load(const float* blk, int nat) { return blk_load(blk, nat); }
+  static __device__ __forceinline__ void store(float* blk, const Frag& f, int nat) { blk_store(blk, f, nat); }
+  static __device__ __forceinline__ void store_t(float* blk, const Acc& a, int) { blk_store_t(blk, a); }
+  static __device__ __forceinline__ void pqh(Acc& x, const Frag& P, const Frag& Q) { mma_pqh<false>(x, P, Q); }
+  static __device__ __forceinline__ void pq(Acc& x, const Frag& P, const Frag& Qt) { mma_pq<false>(x, P, Qt); }
+};
+struct OpSplit {
+  struct Frag {
+    uint4 t[3];  // terms h, m, l: {re 0-1, re 2-3, im 0-1, im 2-3}
+  };
+  static constexpr int kB = 768;  // three planes of 64 16-byte units
+  static __device__ __forceinline__ Frag frag(const Acc& a) {
+    Frag f;
+    split3x2(a.re[0], a.re[1], f.t[0].x, f.t[1].x, f.t[2].x);
+    split3x2(a.re[2], a.re[3], f.t[0].y, f.t[1].y, f.t[2].y);
+    split3x2(a.im[0], a.im[1], f.t[0].z, f.t[1].z, f.t[2].z);
+    split3x2(a.im[2], a.im[3], f.t[0].w, f.t[1].w, f.t[2].w);
+    return f;
+  }
+  static __device__ __forceinline__ Frag load(const float* blk, int nat) {
+    Frag f;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) f.t[p] = *reinterpret_cast<const uint4*>(blk + 256 * p + nat);
+    return f;
+  }
+  static __device__ __forceinline__ void store(float* blk, const Frag& f, int nat) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(blk + 256 * p + nat) = f.t[p];
+  }
+  // transposed in FP32 through the block's own place, then split
+  static __device__ __forceinline__ void store_t(float* blk, const Acc& a, int nat) {
+    blk_store_t(blk, a);
+    store(blk, frag(blk_load(blk, nat)), nat);
+  }
+  static __device__ __forceinline__ unsigned int neg2(unsigned int u) { return u ^ 0x80008000u; }
+  static __device__ __forceinline__ floatx4 mm(const uint4& a, const uint4& b, floatx4 c) {
+    typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+  }
+  // x.re += A B, x.im += A C over the six term products, small ones first
+  static __device__ __forceinline__ void six(Acc& x, const Frag& A, const uint4 (&B)[3], const uint4 (&C)[3]) {
+    constexpr int PA[6] = {1, 0, 2, 0, 1, 0}, PB[6] = {1, 2, 0, 1, 0, 0};
+    Acc t = acc_zero();
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+      t.re = mm(A.t[PA[p]], B[PB[p]], t.re);
+      t.im = mm(A.t[PA[p]], C[PB[p]], t.im);
+    }
+    x.re += t.re;
+    x.im += t.im;
+  }
+  // Re(conj(q) p) = qr pr + qi pi, Im(conj(q) p) = qr pi - qi pr
+  static __device__ __forceinline__ void pqh(Acc& x, const Frag& P, const Frag& Q) {
+    uint4 C[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) C[p] = make_uint4(P.t[p].z, P.t[p].w, neg2(P.t[p].x), neg2(P.t[p].y));
+    six(x, Q, P.t, C);
+  }
+  // Re(q p) = qr pr - qi pi, Im(q p) = qr pi + qi pr
+  static __device__ __forceinline__ void pq(Acc& x, const Frag& P, const Frag& Qt) {
+    uint4 B[3], C[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      B[p] = make_uint4(P.t[p].x, P.t[p].y, neg2(P.t[p].z), neg2(P.t[p].w));
+      C[p] = make_uint4(P.t[p].z, P.t[p].w, P.t[p].x, P.t[p].y);
+    }
+    six(x, Qt, B, C);
+  }
+};
 
-// Broadcast lane J of every 16-lane row to the whole row (DPP row_newbcast).
-template <int J>
-__device__ __forceinline__ float rowb(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + J, 0xF, 0xF, true));
-}
-template <int J>
-__device__ __forceinline__ float2 rowb2(float2 v) {
-  return make_float2(rowb<J>(v.x), rowb<J>(v.y));
+// Keeps the compiler from computing what depends on a block's registers (its
+// split terms) ahead of the loop that uses it, for all slots at once.
+__device__ __forceinline__ void pin(Acc& a) { asm volatile("" : "+v"(a.re), "+v"(a.im)); }
+
+__device__ __forceinline__ Acc acc_neg(const Acc& a) {
+  Acc b;
+  b.re = -a.re;
+  b.im = -a.im;
+  return b;
 }
 
 __device__ __forceinline__ double bcast64(double v, int lane) {
@@ -165,13 +238,53 @@ __device__ __forceinline__ double bcast64(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Column j of the in-wave factorisation of diag_factor_inv().  Rows and
-// columns at or before j are never read again once column j is done, so the
-// update of A needs no mask: with l = A[m][j] / d_j^2 (unmasked) the lanes
-// take A[m][c] -= l A[j][c], which is right wherever m, c > j and harmless
-// elsewhere.  The inverse is kept with unscaled rows Y (X[m] = Y[m] / d_m):
-// rows below j take Y[m] -= (l_mj / d_j) Y[j]; the lane of row j records
-// 1 / d_j for the final scaling.
+// State of the in-wave factorisation and inversion of a 16 x 16 diagonal
+// block.
+struct Diag {
+  Acc A;           // row m: columns > j of A, columns <= j of Y
+  floatx4 cr, ci;  // columns 4 (j / 4) .. + 3 of A at row m, on every lane
+  float rs;        // 1 / d_j of the column to come
+  float rsm;       // 1 / d_m
+  int fail;
+  double p64;      // FP64 Schur diagonal of row m (on the lane holding (m, m))
+  int m, q;
+};
+
+// v -= l * (row J of v) on every lane for the register pairs (re, im) listed,
+// l = lx + i ly: the row broadcast is a DPP operand of the FMA (the compiler
+// folds DPP moves into multiplications but not into FMAs, and separate moves
+// are a third of the column's instructions).  Per value the order is
+// fma(-lx, b, fma(+-ly, b', v)).  l is zero on row J itself, so the broadcast
+// reads the row's old value whatever has been written, and every register's
+// uses are at least 4 instructions apart (DPP reads need two wait states
+// after a write); the s_nops keep that distance to the compiler's
+// instructions on both sides.
+#define STAP_F(D, S, L) "v_fmac_f32_dpp " D ", " S ", " L " row_newbcast:%[j] row_mask:0xf bank_mask:0xf\n"
+#define STAP_ROWUPD(P) P("%[r0]", "%[i0]") P("%[r1]", "%[i1]") P("%[r2]", "%[i2]") P("%[r3]", "%[i3]")
+#define STAP_P1(R, I) STAP_F(R, I, "%[ly]")
+#define STAP_P2(R, I) STAP_F(I, "-" R, "%[ly]")
+#define STAP_P3(R, I) STAP_F(R, "-" R, "%[lx]")
+#define STAP_P4(R, I) STAP_F(I, "-" I, "%[lx]")
+#define STAP_COLS(C1, C2, C3, C4)                                                                          \
+  asm("s_nop 1\n" C1 STAP_ROWUPD(STAP_P1) C2 STAP_ROWUPD(STAP_P2) C3 STAP_ROWUPD(STAP_P3) C4               \
+          STAP_ROWUPD(STAP_P4) "s_nop 1"                                                                   \
+      : [r0] "+v"(ar0), [r1] "+v"(ar1), [r2] "+v"(ar2), [r3] "+v"(ar3), [i0] "+v"(ai0), [i1] "+v"(ai1),     \
+        [i2] "+v"(ai2), [i3] "+v"(ai3), [c1] "+v"(cr1), [c2] "+v"(cr2), [c3] "+v"(cr3), [e1] "+v"(ci1),     \
+        [e2] "+v"(ci2), [e3] "+v"(ci3)                                                                     \
+      : [lx] "v"(lx), [ly] "v"(ly), [j] "n"(j))
+
+// Column j of diag_factor_inv().  The inverse is formed in place: once the
+// multipliers l_mj of column j are taken, A's column j is dead and Y's column
+// j (X[m] = Y[m] / d_m, Y starts as the identity) comes to life in its
+// registers, so one row update Y[m][c <= j], A[m][c > j] -= (l_mj / d_j) row j
+// serves both; rows at or before j take none (l is zero there) and the lane
+// of row j records 1 / d_j for the final scaling.  What is left above the
+// diagonal at the end is dropped by diag_end().
+//
+// The multipliers of a column are read from a copy of the current four
+// columns that every lane of a row keeps (cr, ci), updated like A itself and
+// refreshed every fourth column: a cross-lane read through the LDS pipe, with
+// its latency, once per four columns instead of once per column.
 //
 // The pivot is taken in FP64: every lane keeps, for its row m, p64 =
 // (loaded diagonal R_mm) - (sum over earlier block columns of |L_mk|^2, FP64
@@ -183,38 +296,95 @@ __device__ __forceinline__ double bcast64(double v, int lane) {
 // on meaningless values and only the first failing index is kept, so the 16
 // columns form one straight-line block the compiler can overlap.
 template <int j>
-__device__ __forceinline__ void diag_col(Frag& A, Frag& X, int m, float& rsm, int& fail, double& p64) {
-  constexpr int jq = j >> 2, ji = j & 3;
-  const double piv64 = bcast64(p64, j + 16 * jq);  // row j's FP64 Schur diagonal, wave-uniform
-  fail = (fail == 0 && !(piv64 > 0.0)) ? j + 1 : fail;
-  const float piv = (float)piv64;
-  const float rs = __builtin_amdgcn_rsqf(piv), r2 = rs * rs;
-  const float2 amj = shfl2(A.v[ji], m + 16 * jq);  // A[m][j]
-  const float2 la = make_float2(amj.x * r2, amj.y * r2);  // l_mj / d_j
-  const float2 lx = (m > j) ? la : make_float2(0.f, 0.f);
-  rsm = (m == j) ? rs : rsm;
-  // l_mj = A[m][j] / d_j in FP32, squared and summed in FP64 for row m
-  const float lr = amj.x * rs, li = amj.y * rs;
-  p64 -= (m > j) ? (double)lr * (double)lr + (double)li * (double)li : 0.0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const float2 rj = rowb2<j>(A.v[t]);  // A[j][c] = conj(A[c][j])
-    const float2 yj = rowb2<j>(X.v[t]);  // Y[j][c]
-    // A[m][c] -= l_mj conj(l_cj) = (A[m][j] / d_j^2) A[j][c]
-    A.v[t].x = fmaf(-la.x, rj.x, fmaf(la.y, rj.y, A.v[t].x));
-    A.v[t].y = fmaf(-la.x, rj.y, fmaf(-la.y, rj.x, A.v[t].y));
-    X.v[t].x = fmaf(-lx.x, yj.x, fmaf(lx.y, yj.y, X.v[t].x));
-    X.v[t].y = fmaf(-lx.x, yj.y, fmaf(-lx.y, yj.x, X.v[t].y));
-  }
+__device__ __forceinline__ void diag_pivot(Diag& s) {
+  const double piv64 = bcast64(s.p64, j + 16 * (j >> 2));  // row j's FP64 Schur diagonal, wave-uniform
+  s.fail = (s.fail == 0 && !(piv64 > 0.0)) ? j + 1 : s.fail;
+  s.rs = __builtin_amdgcn_rsqf((float)piv64);
 }
 template <int j>
-__device__ __forceinline__ void diag_cols(Frag& A, Frag& X, int m, float& rsm, int& fail, double& p64) {
-  diag_col<j>(A, X, m, rsm, fail, p64);
-  if constexpr (j < 15) diag_cols<j + 1>(A, X, m, rsm, fail, p64);
+__device__ __forceinline__ void diag_col(Diag& s) {
+  constexpr int jq = j >> 2, ji = j & 3;
+  if constexpr (ji == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s.cr[i] = __shfl(s.A.re[i], s.m + 16 * jq);
+      s.ci[i] = __shfl(s.A.im[i], s.m + 16 * jq);
+    }
+  }
+  const float rs = s.rs, r2 = rs * rs;
+  const float ax = s.m > j ? s.cr[ji] : 0.f, ay = s.m > j ? s.ci[ji] : 0.f;  // A[m][j]
+  const float lx = ax * r2, ly = ay * r2;                                    // l_mj / d_j
+  s.rsm = (s.m == j) ? rs : s.rsm;
+  // l_mj = A[m][j] / d_j in FP32, squared and summed in FP64 for row m
+  const float lr = ax * rs, li = ay * rs;
+  s.p64 -= (double)lr * (double)lr + (double)li * (double)li;
+  if constexpr (j < 15) diag_pivot<j + 1>(s);  // its latency passes behind the update
+  s.A.re[ji] = s.q == jq ? (s.m == j ? 1.f : 0.f) : s.A.re[ji];
+  s.A.im[ji] = s.q == jq ? 0.f : s.A.im[ji];
+  float ar0 = s.A.re[0], ar1 = s.A.re[1], ar2 = s.A.re[2], ar3 = s.A.re[3];
+  float ai0 = s.A.im[0], ai1 = s.A.im[1], ai2 = s.A.im[2], ai3 = s.A.im[3];
+  float cr1 = s.cr[1], cr2 = s.cr[2], cr3 = s.cr[3], ci1 = s.ci[1], ci2 = s.ci[2], ci3 = s.ci[3];
+  // A[m][c] -= l_mj conj(l_cj) = (A[m][j] / d_j^2) A[j][c], and Y likewise
+  if constexpr (ji == 0)
+    STAP_COLS(STAP_P1("%[c1]", "%[e1]") STAP_P1("%[c2]", "%[e2]") STAP_P1("%[c3]", "%[e3]"),
+              STAP_P2("%[c1]", "%[e1]") STAP_P2("%[c2]", "%[e2]") STAP_P2("%[c3]", "%[e3]"),
+              STAP_P3("%[c1]", "%[e1]") STAP_P3("%[c2]", "%[e2]") STAP_P3("%[c3]", "%[e3]"),
+              STAP_P4("%[c1]", "%[e1]") STAP_P4("%[c2]", "%[e2]") STAP_P4("%[c3]", "%[e3]"));
+  else if constexpr (ji == 1)
+    STAP_COLS(STAP_P1("%[c2]", "%[e2]") STAP_P1("%[c3]", "%[e3]"),
+              STAP_P2("%[c2]", "%[e2]") STAP_P2("%[c3]", "%[e3]"),
+              STAP_P3("%[c2]", "%[e2]") STAP_P3("%[c3]", "%[e3]"),
+              STAP_P4("%[c2]", "%[e2]") STAP_P4("%[c3]", "%[e3]"));
+  else if constexpr (ji == 2)
+    STAP_COLS(STAP_P1("%[c3]", "%[e3]"), STAP_P2("%[c3]", "%[e3]"), STAP_P3("%[c3]", "%[e3]"),
+              STAP_P4("%[c3]", "%[e3]"));
+  else
+    STAP_COLS("", "", "", "");
+  s.A.re = floatx4{ar0, ar1, ar2, ar3};
+  s.A.im = floatx4{ai0, ai1, ai2, ai3};
+  s.cr = floatx4{s.cr[0], cr1, cr2, cr3};
+  s.ci = floatx4{s.ci[0], ci1, ci2, ci3};
+}
+template <int j>
+__device__ __forceinline__ void diag_cols(Diag& s) {
+  diag_col<j>(s);
+  if constexpr (j < 15) diag_cols<j + 1>(s);
+}
+#undef STAP_F
+#undef STAP_ROWUPD
+#undef STAP_P1
+#undef STAP_P2
+#undef STAP_P3
+#undef STAP_P4
+#undef STAP_COLS
+
+__device__ __forceinline__ void diag_begin(Diag& s, const Acc& A, double p64) {
+  const int l = lane_tid() & 63;
+  s.A = A;
+  s.cr = s.ci = floatx4{0.f, 0.f, 0.f, 0.f};
+  s.rsm = 1.f;
+  s.fail = 0;
+  s.p64 = p64;
+  s.m = l & 15;
+  s.q = l >> 4;
+  diag_pivot<0>(s);
+}
+// SIGN / d_m times row m of Y, zero above the diagonal.
+template <int SIGN>
+__device__ __forceinline__ Acc diag_end(const Diag& s) {
+  const float sc = SIGN < 0 ? -s.rsm : s.rsm;
+  Acc X;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool lower = 4 * s.q + i <= s.m;
+    X.re[i] = lower ? s.A.re[i] * sc : 0.f;
+    X.im[i] = lower ? s.A.im[i] * sc : 0.f;
+  }
+  return X;
 }
 
 // Factor the Hermitian 16 x 16 block A (full, both triangles) as L L^H inside
-// one wave and return X = L^-1 (lower triangular).  Column j: pivot
+// one wave and return X = SIGN L^-1 (lower triangular).  Column j: pivot
 // d_j = sqrt(A[j][j]) (taken in FP64 as above, p64 the lane's starting
 // value for its row: loaded diagonal minus the earlier block columns),
 // l_mj = A[m][j] / d_j for m > j, then A[m][c] -= l_mj conj(l_cj) for
@@ -222,34 +392,34 @@ __device__ __forceinline__ void diag_cols(Frag& A, Frag& X, int m, float& rsm, i
 // identity carrying column j of L (row j of X divided by d_j, then row m -=
 // l_mj row j), the row divisions deferred.  A[c][j] is read as conj(A[j][c])
 // from row j, which lives in the same 16-lane row of the wave (a DPP
-// broadcast); only l_mj crosses rows.  Returns 0 or the 1-based index of the
-// first non-positive pivot.
-__device__ __forceinline__ int diag_factor_inv(Frag& A, Frag& X, double p64) {
-  const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) X.v[i] = make_float2(m == 4 * q + i ? 1.f : 0.f, 0.f);
-  int fail = 0;
-  float rsm = 1.f;
-  diag_cols<0>(A, X, m, rsm, fail, p64);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) X.v[i] = make_float2(X.v[i].x * rsm, X.v[i].y * rsm);
-  return fail;
+// broadcast).  Returns 0 or the 1-based index of the first non-positive
+// pivot.  The wave runs at raised priority: the other waves of its system
+// wait for it.
+template <int SIGN>
+__device__ __forceinline__ int diag_factor_inv(const Acc& A, Acc& X, double p64) {
+  Diag s;
+  diag_begin(s, A, p64);
+  __builtin_amdgcn_s_setprio(3);
+  diag_cols<0>(s);
+  __builtin_amdgcn_s_setprio(0);
+  X = diag_end<SIGN>(s);
+  return s.fail;
 }
 
 // The lane's own diagonal element of a block in fragment order (lane (m, q)
 // holds X[m][4q + i]; the element (m, m) sits in lane q = m / 4, register
 // m % 4), or 0 on the other lanes.
-__device__ __forceinline__ float frag_diag(const Frag& A) {
+__device__ __forceinline__ float blk_diag(const Acc& A) {
   const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
   float v = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v = (m == 4 * q + i) ? A.v[i].x : v;
+  for (int i = 0; i < 4; ++i) v = (m == 4 * q + i) ? A.re[i] : v;
   return v;
 }
 
 // Row sums of |X|^2 of a block in fragment order, in FP64, on every lane of
 // the row (lane (m, q) holds row m, columns 4q .. 4q + 3).
-__device__ __forceinline__ double frag_row_norm2(const Acc& x) {
+__device__ __forceinline__ double blk_row_norm2(const Acc& x) {
   double p = 0.0;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -268,7 +438,7 @@ __device__ __forceinline__ double frag_row_norm2(const Acc& x) {
 // order, so every step is balanced to within one block per wave and set.
 // Loops over a wave's blocks run over its slots (unrolled, so register
 // indices are constants) and test the slot's block coordinates, which are
-// run-time values.
+// run-time values (wave-uniform).
 template <int NSL_, int NSM_, int NW_>
 struct BCfg {
   static constexpr int NSL = NSL_, NSM = NSM_, NW = NW_;
@@ -276,164 +446,170 @@ struct BCfg {
   // L and M slots per wave a (NB, NS) system needs
   __host__ __device__ static constexpr int lslots(int NB) { return (NB * (NB + 1) / 2 + NW - 1) / NW; }
   __host__ __device__ static constexpr int mslots(int NB, int NS) { return (NS * NB + NW - 1) / NW; }
-  // LDS: exchange blocks (NB + NS + 1 for the factorisation and solves, all
-  // NS NB blocks of Z for the refinement residual), the gamma partials
-  // [NB][16 NS] (FP64), a flag, and the FP64 row sums of |L|^2 over the
-  // finished block columns [16 NB] (for the FP64 pivots)
-  __host__ __device__ static constexpr size_t xblocks(int NB, int NS) {
-    return (size_t)(NB + NS + 1 > NS * NB ? NB + NS + 1 : NS * NB);
+  // LDS: exchange blocks (NB + NS + 1 for the factorisation and solves; with
+  // refinement, all NS NB blocks of Z in FP32 for the residual), the gamma
+  // partials [NB][16 NS] (FP64), a flag, the FP64 row sums of |L|^2 over the
+  // finished block columns [16 NB] and the loaded diagonal [16 NB] (for the
+  // FP64 pivots)
+  __host__ __device__ static constexpr size_t xbytes(int NB, int NS, bool refine) {
+    const size_t x = (size_t)(NB + NS + 1) * (refine ? OpSplit::kB : OpF32::kB) * 4;
+    const size_t z = refine ? (size_t)NS * NB * kBlk * 4 : 0;
+    return x > z ? x : z;
   }
-  __host__ __device__ static constexpr size_t lds_bytes(int NB, int NS) {
-    return xblocks(NB, NS) * 256 * 8 + (size_t)NB * 16 * NS * 8 + 16 + (size_t)NB * 16 * 8;
+  __host__ __device__ static constexpr size_t lds_bytes(int NB, int NS, bool refine) {
+    return xbytes(NB, NS, refine) + (size_t)NB * 16 * NS * 8 + 16 + (size_t)NB * 16 * (8 + 4);
   }
 };
 
-// Factor diagonal block Jd held in L slot td (after its last update from the
-// panel L_{Jd,Jd-1} in xb when `update`), keep Linv in the slot, publish it
-// at dinv and the pivot status at sflag.  The block passes through dinv on
-// its way in and out of the register slot, so the diagonal code exists once
-// and every register slot is addressed by a constant index.
-// The FP64 pivots start from the loaded diagonal of the block (rdg, kept
-// per slot since the load) minus the FP64 row sums of |L|^2 over the earlier
-// block columns (d64, LDS).
-template <int NSL>
-__device__ __forceinline__ void bs_factor_diag(Acc (&acc)[NSL], const float (&rdg)[NSL], int td, int Jd, bool update,
-                                               const float2* xb, const double* d64, float2* dinv, int* sflag) {
-  float rd = 0.f;
+// Block coordinates of a wave's register slots.
+template <class C>
+struct Slots {
+  int NB, NS;
+  bool lv[C::NSL], mv[C::NSM];
+  int lr[C::NSL], lc[C::NSL], mr[C::NSM], mc[C::NSM];
+  __device__ __forceinline__ Slots(int D, int S, int wave) {
+    NB = (D + 15) >> 4;
+    NS = (S + 15) >> 4;
 #pragma unroll
-  for (int t = 0; t < NSL; ++t)
-    if (td == t) {
-      frag_store(dinv, to_frag(acc[t]));
-      rd = rdg[t];
+    for (int t = 0; t < C::NSL; ++t) {
+      const int g = wave + C::NW * t;
+      lv[t] = false;
+      lr[t] = lc[t] = 0;
+      int start = 0;
+      for (int J = 0; J < NB; ++J) {
+        const int len = NB - J;
+        if (g >= start && g < start + len) {
+          lv[t] = true;
+          lc[t] = J;
+          lr[t] = J + (g - start);
+        }
+        start += len;
+      }
     }
-  Frag A = frag_load(dinv), X;
-  if (update) {
-    Acc a = to_acc(A);
-    const Frag P = frag_load(xb + Jd * 256);
-    mma_pqh<true>(a, P, P);
-    A = to_frag(a);
-  }
-  const int m = lane_tid() & 15;
-  const double p64 = (double)rd - (Jd > 0 ? d64[16 * Jd + m] : 0.0);
-  const int f = diag_factor_inv(A, X, p64);
-  frag_store(dinv, X);
 #pragma unroll
-  for (int t = 0; t < NSL; ++t)
-    if (td == t) acc[t] = to_acc(X);
-  if ((lane_tid() & 63) == 0) *sflag = f ? 16 * Jd + f : 0;
-}
+    for (int t = 0; t < C::NSM; ++t) {
+      const int g = wave + C::NW * t;
+      mv[t] = g < NS * NB;
+      mc[t] = g / NS;
+      mr[t] = g - (g / NS) * NS;
+    }
+  }
+};
+// Number of L block (I, J) in that order.
+__device__ __forceinline__ int lblock(int NB, int I, int J) { return J * NB - J * (J - 1) / 2 + (I - J); }
+
+// The LDS regions of a system (lds_bytes(NB, NS, REFINE) at xlds).
+template <class C, bool REFINE>
+struct SolveLds {
+  typedef std::conditional_t<REFINE, OpSplit, OpF32> Op;
+  float* xb;      // exchange blocks
+  float* dinv;    // minus the inverse of the current diagonal block
+  double* gpart;  // gamma partials
+  int* sflag;     // pivot status
+  double* d64;    // FP64 row sums of |L|^2
+  float* rdiag;   // loaded diagonal
+  __device__ __forceinline__ SolveLds(unsigned char* xlds, int NB, int NS) {
+    xb = reinterpret_cast<float*>(xlds);
+    dinv = xb + (size_t)(NB + NS) * Op::kB;
+    gpart = reinterpret_cast<double*>(xlds + C::xbytes(NB, NS, REFINE));
+    sflag = reinterpret_cast<int*>(gpart + NB * 16 * NS);
+    d64 = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(sflag) + 16);
+    rdiag = reinterpret_cast<float*>(d64 + NB * 16);
+  }
+};
 
 __device__ __forceinline__ doublex4 mfma64(double a, double b, doublex4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// A global read the compiler must not merge with an earlier read of the
-// same address: keeping such values live across the whole solve costs more
-// registers than reading them again (they are cache hits).
-__device__ __forceinline__ float2 reload(const float2* p) {
-  const volatile float* v = reinterpret_cast<const volatile float*>(p);
-  return make_float2(v[0], v[1]);
+// Whether rows of D complex elements starting at p keep 16-byte alignment
+// at every even column.
+__device__ __forceinline__ bool rows16(const void* p, int D) {
+  return (D & 1) == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+}
+// Elements k .. k+3 of row s of a [rows][D] array (k a multiple of 4), zero
+// from column D on and for rows not in the array; two 16-byte loads where
+// the rows allow it (vec = rows16()), which fetches a lane's 32 bytes in one
+// go.  The element index passes through an empty asm statement, so that the
+// compiler neither merges the loads with an earlier read of the same
+// elements (keeping those live across the solve costs more registers than
+// reading them again from the cache) nor, as volatile loads would be, issues
+// them one round trip at a time.
+__device__ __forceinline__ void load4(const float2* base, int s, int k, bool row_ok, int D, bool vec, float2 (&v)[4]) {
+  int o = s * D + k;
+  asm volatile("" : "+v"(o));
+  if (vec && row_ok && k + 4 <= D) {
+    const float4 a = *reinterpret_cast<const float4*>(base + o);
+    const float4 b = *reinterpret_cast<const float4*>(base + o + 2);
+    v[0] = make_float2(a.x, a.y);
+    v[1] = make_float2(a.z, a.w);
+    v[2] = make_float2(b.x, b.y);
+    v[3] = make_float2(b.z, b.w);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (row_ok && k + i < D) ? base[o + i] : make_float2(0.f, 0.f);
+  }
+}
+__device__ __forceinline__ void store4(float2* base, int s, int k, bool row_ok, int D, bool vec, const float2 (&v)[4]) {
+  const int o = s * D + k;
+  if (vec && row_ok && k + 4 <= D) {
+    *reinterpret_cast<float4*>(base + o) = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+    *reinterpret_cast<float4*>(base + o + 2) = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
+  } else if (row_ok) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (k + i < D) base[o + i] = v[i];
+  }
 }
 
-// Solve one system (D <= 16 NB, S <= 16 NS, lslots(NB) <= NSL,
-// mslots(NB, NS) <= NSM).  src.lower(i, k) (k <= i < D) yields the loaded
-// covariance; it must stay readable for the whole call when REFINE (the FP64
-// residual reads it again).  xlds points at lds_bytes(NB, NS) of 16-byte
-// aligned LDS, which may overlap the source only without REFINE (the source
-// is read completely before the first write).  W is this system's [S][D]
-// output, info its status word (may be null).  park (may be null) is LDS of
-// at least 16 NS x 16 NB complex that is free once the last residual has
-// been formed (the source, when it lives in LDS): the last refinement step
-// keeps u there instead of in W.
-template <class C, bool REFINE, class RSrc>
-__device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __restrict__ steer,
-                                              float2* __restrict__ W, int* __restrict__ info, const Dims& d,
-                                              unsigned char* xlds, float2* park = nullptr) {
-  constexpr int NSL = C::NSL, NSM = C::NSM, NW = C::NW;
-  const int D = d.D, S = d.S;
-  const int NB = (D + 15) >> 4, NS = (S + 15) >> 4;
-  float2* xb = reinterpret_cast<float2*>(xlds);  // exchange blocks, 256 complex each
-  double* gpart = reinterpret_cast<double*>(xlds + C::xblocks(NB, NS) * 256 * 8);
-  int* sflag = reinterpret_cast<int*>(gpart + NB * 16 * NS);
-  double* d64 = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(sflag) + 16);
-  const int tid = lane_tid(), lane = tid & 63, m = lane & 15, q = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float2* dinv = xb + (size_t)(NB + NS) * 256;
-
-  // block coordinates of each slot
-  bool lv[NSL], mv[NSM];
-  int lr[NSL], lc[NSL], mr[NSM], mc[NSM];
+// -M = -V^H blocks of the wave's slots (zero beyond S and D).
+template <class C>
+__device__ __forceinline__ void load_steer(const Slots<C>& sl, const float2* __restrict__ steer, int D, int S,
+                                           Acc (&am)[C::NSM]) {
+  const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
+  const bool vec = rows16(steer, D);
 #pragma unroll
-  for (int t = 0; t < NSL; ++t) {
-    const int g = wave + NW * t;
-    lv[t] = false;
-    lr[t] = 0;
-    lc[t] = 0;
-    int start = 0;
-    for (int J = 0; J < NB; ++J) {
-      const int len = NB - J;
-      if (g >= start && g < start + len) {
-        lv[t] = true;
-        lc[t] = J;
-        lr[t] = J + (g - start);
-      }
-      start += len;
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < NSM; ++t) {
-    const int g = wave + NW * t;
-    mv[t] = g < NS * NB;
-    mc[t] = g / NS;
-    mr[t] = g - (g / NS) * NS;
-  }
-
-  Acc al[NSL], am[NSM];
-  float rdg[NSL];  // loaded diagonal of the slot's block (diagonal blocks), for the FP64 pivots
-  // ---- load R_L blocks (identity beyond D) and M = V^H blocks
-#pragma unroll
-  for (int t = 0; t < NSL; ++t) {
+  for (int t = 0; t < C::NSM; ++t) {
     Acc a = acc_zero();
-    if (lv[t]) {
-      const int r = 16 * lr[t] + m;
+    if (sl.mv[t]) {
+      const int s = 16 * sl.mr[t] + m;
+      float2 v[4];
+      load4(steer, s, 16 * sl.mc[t] + 4 * q, s < S, D, vec, v);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int c = 16 * lc[t] + 4 * q + i;
-        float2 v;
-        if (r < D && c < D) {
-          if (c <= r) {
-            v = src.lower(r, c);
-          } else {
-            v = src.lower(c, r);
-            v.y = -v.y;
-          }
-        } else {
-          v = make_float2(r == c ? 1.f : 0.f, 0.f);
-        }
-        a.re[i] = v.x;
-        a.im[i] = v.y;
-      }
-    }
-    al[t] = a;
-    rdg[t] = frag_diag(to_frag(a));
-  }
-#pragma unroll
-  for (int t = 0; t < NSM; ++t) {
-    Acc a = acc_zero();
-    if (mv[t]) {
-      const int s = 16 * mr[t] + m;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = 16 * mc[t] + 4 * q + i;
-        const float2 v = (s < S && k < D) ? steer[s * D + k] : make_float2(0.f, 0.f);
-        a.re[i] = v.x;
-        a.im[i] = -v.y;
+        a.re[i] = -v[i].x;
+        a.im[i] = v[i].y;
       }
     }
     am[t] = a;
   }
-  __syncthreads();  // without REFINE the source may be LDS that the exchange blocks reuse
-  for (int r = tid; r < 16 * NB; r += C::NT) d64[r] = 0.0;  // read from step J = 0 on, after a barrier
+}
+
+// Solve one system (D <= 16 NB, S <= 16 NS, lslots(NB) <= NSL,
+// mslots(NB, NS) <= NSM).  al holds the wave's blocks of minus the loaded
+// covariance (identity beyond D, diagonal blocks with both triangles), am
+// those of -M: blocks still to be finished are kept negated, so that every
+// update adds (x -= P Q^H is -x += P Q^H) and the panel product with
+// -Linv_JJ restores the sign, all exactly.  L.rdiag holds the loaded diagonal of the diagonal blocks
+// (written by the wave that owns them) and L.d64 zeros, visible after the
+// next barrier.  With REFINE src.get(J, I) yields, on lane (m, q), R_L[16J +
+// 4q + s][16I + m], s = 0..3; it must stay readable for the whole call.  W is
+// this system's [S][D] output, info its status word (may be null).  park
+// (may be null) is LDS of at least NS NB blocks that is free once the last
+// residual has been formed (the source, when it lives in LDS): the last
+// refinement step keeps u there instead of in W.
+template <class C, bool REFINE, class RSrc>
+__device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::NSL], Acc (&am)[C::NSM],
+                                              const SolveLds<C, REFINE>& L, const RSrc& src,
+                                              const float2* __restrict__ steer, float2* __restrict__ W,
+                                              int* __restrict__ info, const Dims& d, float* park) {
+  typedef typename SolveLds<C, REFINE>::Op Op;
+  typedef typename Op::Frag Frag;
+  constexpr int NSL = C::NSL, NSM = C::NSM, kB = Op::kB;
+  const int D = d.D, S = d.S, NB = sl.NB, NS = sl.NS;
+  float* const xb = L.xb;
+  const int tid = lane_tid(), lane = tid & 63, m = lane & 15, q = lane >> 4;
+  const int nat = nat_ofs();
 
   // ---- factorisation with the forward solve of the steering rows.  The
   // wave owning diagonal block J+1 applies its last update (from column J)
@@ -443,31 +619,29 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
   for (int J = -1; J < NB; ++J) {
     if (J >= 0) {
       __syncthreads();
-      fail = *sflag;
+      fail = *L.sflag;
       if (fail) break;
-      const Frag Q = frag_load(dinv);
+      const Frag Q = Op::load(L.dinv, nat);
 #pragma unroll
       for (int t = 0; t < NSL; ++t) {
-        if (lv[t] && lc[t] == J && lr[t] != J) {
-          const Frag P = to_frag(al[t]);
+        if (sl.lv[t] && sl.lc[t] == J && sl.lr[t] != J) {
           Acc x = acc_zero();
-          mma_pqh<false>(x, P, Q);
+          Op::pqh(x, Op::frag(al[t]), Q);
           al[t] = x;
-          frag_store(xb + lr[t] * 256, to_frag(x));
+          Op::store(xb + sl.lr[t] * kB, Op::frag(x), nat);
           // FP64 row sums of |L|^2 for the pivots of block row lr (one
           // panel block per block row and step: no other writer)
-          const double pn = frag_row_norm2(x);
-          if (q == 0) d64[16 * lr[t] + m] += pn;
+          const double pn = blk_row_norm2(x);
+          if (q == 0) L.d64[16 * sl.lr[t] + m] += pn;
         }
       }
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t] && mc[t] == J) {
-          const Frag P = to_frag(am[t]);
+        if (sl.mv[t] && sl.mc[t] == J) {
           Acc x = acc_zero();
-          mma_pqh<false>(x, P, Q);
+          Op::pqh(x, Op::frag(am[t]), Q);
           am[t] = x;
-          frag_store(xb + (NB + mr[t]) * 256, to_frag(x));
+          Op::store(xb + (NB + sl.mr[t]) * kB, Op::frag(x), nat);
         }
       }
       __syncthreads();
@@ -475,17 +649,42 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
     int tn = -1;
 #pragma unroll
     for (int t = 0; t < NSL; ++t)
-      if (J + 1 < NB && lv[t] && lr[t] == J + 1 && lc[t] == J + 1) tn = t;
-    if (tn >= 0) bs_factor_diag<NSL>(al, rdg, tn, J + 1, J >= 0, xb, d64, dinv, sflag);
+      if (J + 1 < NB && sl.lv[t] && sl.lr[t] == J + 1 && sl.lc[t] == J + 1) tn = t;
+    if (tn >= 0) {
+      // the diagonal code exists once: the slot's block is copied in and out
+      Acc A = acc_zero();
+#pragma unroll
+      for (int t = 0; t < NSL; ++t)
+        if (tn == t) {
+          A.re = al[t].re;
+          A.im = al[t].im;
+        }
+      if (J >= 0) {
+        const Frag P = Op::load(xb + (J + 1) * kB, nat);
+        Op::pqh(A, P, P);
+      }
+      const int r = 16 * (J + 1) + m;
+      const double p64 = (double)L.rdiag[r] - (J >= 0 ? L.d64[r] : 0.0);
+      Acc X;
+      const int f = diag_factor_inv<-1>(acc_neg(A), X, p64);
+      Op::store(L.dinv, Op::frag(X), nat);
+#pragma unroll
+      for (int t = 0; t < NSL; ++t)
+        if (tn == t) {
+          al[t].re = X.re;
+          al[t].im = X.im;
+        }
+      if (lane == 0) *L.sflag = f ? 16 * (J + 1) + f : 0;
+    }
     if (J >= 0) {
 #pragma unroll
       for (int t = 0; t < NSL; ++t)
-        if (lv[t] && lc[t] > J && t != tn)
-          mma_pqh<true>(al[t], frag_load(xb + lr[t] * 256), frag_load(xb + lc[t] * 256));
+        if (sl.lv[t] && sl.lc[t] > J && t != tn)
+          Op::pqh(al[t], Op::load(xb + sl.lr[t] * kB, nat), Op::load(xb + sl.lc[t] * kB, nat));
 #pragma unroll
       for (int t = 0; t < NSM; ++t)
-        if (mv[t] && mc[t] > J)
-          mma_pqh<true>(am[t], frag_load(xb + (NB + mr[t]) * 256), frag_load(xb + mc[t] * 256));
+        if (sl.mv[t] && sl.mc[t] > J)
+          Op::pqh(am[t], Op::load(xb + (NB + sl.mr[t]) * kB, nat), Op::load(xb + sl.mc[t] * kB, nat));
     }
   }
 
@@ -499,46 +698,52 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
   if (!REFINE || d.refine == 0) {
 #pragma unroll
     for (int t = 0; t < NSM; ++t) {
-      if (mv[t]) {
+      if (sl.mv[t]) {
         float p = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) p = fmaf(am[t].re[i], am[t].re[i], fmaf(am[t].im[i], am[t].im[i], p));
         p += __shfl_xor(p, 16);
         p += __shfl_xor(p, 32);
-        if (q == 0) gpart[mc[t] * 16 * NS + 16 * mr[t] + m] = p;
+        if (q == 0) L.gpart[sl.mc[t] * 16 * NS + 16 * sl.mr[t] + m] = p;
       }
     }
   }
 
   // ---- back solve, row form Z L = Y^H (M holds Y^H on entry, Z on exit)
   auto back_solve = [&]() {
-    float2* zb = xb + (size_t)NB * 256;
+    float* zb = xb + (size_t)NB * kB;
+#pragma unroll
+    for (int t = 0; t < NSM; ++t) am[t] = acc_neg(am[t]);
     for (int J = NB - 1; J >= 0; --J) {
       __syncthreads();  // previous readers of the exchange blocks are done
 #pragma unroll
-      for (int t = 0; t < NSL; ++t)  // L_JI^T (Linv_JJ^T at I = J)
-        if (lv[t] && lr[t] == J) frag_store_t(xb + lc[t] * 256, to_frag(al[t]));
+      for (int t = 0; t < NSL; ++t)  // L_JI^T (-Linv_JJ^T at I = J)
+        if (sl.lv[t] && sl.lr[t] == J) {
+          pin(al[t]);
+          Op::store_t(xb + sl.lc[t] * kB, al[t], nat);
+        }
       __syncthreads();
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t] && mc[t] == J) {
-          const Frag P = to_frag(am[t]);
+        if (sl.mv[t] && sl.mc[t] == J) {
           Acc x = acc_zero();
-          mma_pq<false>(x, P, frag_load(xb + J * 256));
+          Op::pq(x, Op::frag(am[t]), Op::load(xb + J * kB, nat));
           am[t] = x;
-          frag_store(zb + mr[t] * 256, to_frag(x));
+          if (J > 0) Op::store(zb + sl.mr[t] * kB, Op::frag(x), nat);
         }
       }
       if (J > 0) {
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NSM; ++t)
-          if (mv[t] && mc[t] < J) mma_pq<true>(am[t], frag_load(zb + mr[t] * 256), frag_load(xb + mc[t] * 256));
+          if (sl.mv[t] && sl.mc[t] < J)
+            Op::pq(am[t], Op::load(zb + sl.mr[t] * kB, nat), Op::load(xb + sl.mc[t] * kB, nat));
       }
     }
   };
   back_solve();
 
+  const bool vecW = rows16(W, D), vecV = rows16(steer, D);
   if (REFINE) {
     for (int it = 0; it < d.refine; ++it) {
       const bool lds_park = park != nullptr && it == d.refine - 1;
@@ -546,13 +751,12 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
       // back by the same lane after the correction), or in park
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t] && !lds_park) {
-          const int s = 16 * mr[t] + m;
+        if (sl.mv[t] && !lds_park) {
+          const int s = 16 * sl.mr[t] + m;
+          float2 u[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int k = 16 * mc[t] + 4 * q + i;
-            if (s < S && k < D) W[s * D + k] = make_float2(am[t].re[i], -am[t].im[i]);
-          }
+          for (int i = 0; i < 4; ++i) u[i] = make_float2(am[t].re[i], -am[t].im[i]);
+          store4(W, s, 16 * sl.mc[t] + 4 * q, s < S, D, vecW, u);
         }
       }
       // residual in row form: conj(r) = conj(v) - Z R_L, FP64 MFMA (FP32
@@ -565,58 +769,37 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
       __syncthreads();
 #pragma unroll
       for (int t = 0; t < NSM; ++t)
-        if (mv[t]) frag_store(xb + (mr[t] * NB + mc[t]) * 256, to_frag(am[t]));
+        if (sl.mv[t]) blk_store(xb + (sl.mr[t] * NB + sl.mc[t]) * kBlk, am[t], nat);
       __syncthreads();
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t]) {
+        if (sl.mv[t]) {
           doublex4 a1 = {0.0, 0.0, 0.0, 0.0}, a2 = a1, a3 = a1;
-          const float2* zrow = xb + (size_t)mr[t] * NB * 256 + 2 * lane;
-          const int c = 16 * mc[t] + m;
-          // R_L[r][c] for r = 16 J + 4 q + s4, c = 16 I + m (identity beyond D)
-          auto r_elem = [&](int J, int s4) {
-            const int r = 16 * J + 4 * q + s4;
-            float2 rv;
-            if (r < D && c < D) {
-              rv = c <= r ? src.lower(r, c) : src.lower(c, r);
-              rv.y = c <= r ? rv.y : -rv.y;
-            } else {
-              rv = make_float2(r == c ? 1.f : 0.f, 0.f);
-            }
-            return rv;
-          };
-          auto acc3 = [&](float2 rv, float2 z) {
-            const double qr = rv.x, qi = rv.y, pr = z.x, pi = z.y;
-            a1 = mfma64(qr, pr, a1);
-            a2 = mfma64(qi, pi, a2);
-            a3 = mfma64(qr + qi, pr + pi, a3);
-          };
-          for (int J = 0; J < NB; ++J) {
-            if constexpr (kResidualLoadsAhead) {
-              // the four k-steps' operands loaded before their products
-              float2 zz[4], rr[4];
-#pragma unroll
-              for (int s4 = 0; s4 < 4; ++s4) {
-                zz[s4] = zrow[J * 256 + (s4 & 2) * 64 + (s4 & 1)];  // Z_{N,J}[m][4q + s4]
-                rr[s4] = r_elem(J, s4);
-              }
-#pragma unroll
-              for (int s4 = 0; s4 < 4; ++s4) acc3(rr[s4], zz[s4]);
-            } else {
+          const float* zrow = xb + sl.mr[t] * NB * kBlk;
 #pragma unroll 1
-              for (int s4 = 0; s4 < 4; ++s4) acc3(r_elem(J, s4), zrow[J * 256 + (s4 & 2) * 64 + (s4 & 1)]);
+          for (int J = 0; J < NB; ++J) {
+            const Acc z = blk_load(zrow + J * kBlk, nat);  // Z_{N,J}[m][4q + s]
+            const Acc r = src.get(J, sl.mc[t], nat);
+#pragma unroll
+            for (int s4 = 0; s4 < 4; ++s4) {
+              const double qr = r.re[s4], qi = r.im[s4], pr = z.re[s4], pi = z.im[s4];
+              a1 = mfma64(qr, pr, a1);
+              a2 = mfma64(qi, pi, a2);
+              a3 = mfma64(qr + qi, pr + pi, a3);
             }
           }
           const doublex4 cr = a1 - a2, ci = a3 - a1 - a2;
-          const int s = 16 * mr[t] + m;
+          const int s = 16 * sl.mr[t] + m;
+          // the slot's Z is in LDS now: its registers hold minus the
+          // residual, column q + 4i in register i
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int k = 16 * mc[t] + q + 4 * i;
-            const float2 v = (s < S && k < D) ? reload(steer + s * D + k) : make_float2(0.f, 0.f);
-            // the slot's Z is in LDS now: its registers hold the residual,
-            // column q + 4i in register i
-            am[t].re[i] = (float)((double)v.x - cr[i]);
-            am[t].im[i] = (float)(-(double)v.y - ci[i]);
+            const int k = 16 * sl.mc[t] + q + 4 * i;
+            int o = s * D + k;
+            asm volatile("" : "+v"(o));
+            const float2 v = (s < S && k < D) ? steer[o] : make_float2(0.f, 0.f);
+            am[t].re[i] = (float)(cr[i] - (double)v.x);
+            am[t].im[i] = (float)((double)v.y + ci[i]);
           }
         }
       }
@@ -626,56 +809,62 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
       // then takes the Z block itself (u for the correction)
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t]) {
-          float2* zb = xb + (mr[t] * NB + mc[t]) * 256;
-          float2* tb = lds_park ? park + (mr[t] * NB + mc[t]) * 256 : zb;
+        if (sl.mv[t]) {
+          float* zb = xb + (sl.mr[t] * NB + sl.mc[t]) * kBlk;
+          float* tb = lds_park ? park + (sl.mr[t] * NB + sl.mc[t]) * kBlk : zb;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) tb[bofs(m, q + 4 * i)] = make_float2(am[t].re[i], am[t].im[i]);
-          am[t] = to_acc(frag_load(tb));
-          if (lds_park) frag_store(tb, frag_load(zb));
+          for (int i = 0; i < 4; ++i) {
+            const int o = bofs(m, q + 4 * i);
+            tb[o] = am[t].re[i];
+            tb[256 + o] = am[t].im[i];
+          }
+          am[t] = blk_load(tb, nat);
+          if (lds_park) blk_store(tb, blk_load(zb, nat), nat);
         }
       }
       // forward solve Y^H L^H = r^H with the stored factor
       for (int J = 0; J < NB; ++J) {
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < NSL; ++t)  // column J of L (Linv_JJ at the diagonal)
-          if (lv[t] && lc[t] == J) frag_store(xb + lr[t] * 256, to_frag(al[t]));
+        for (int t = 0; t < NSL; ++t)  // column J of L (-Linv_JJ at the diagonal)
+          if (sl.lv[t] && sl.lc[t] == J) {
+            pin(al[t]);
+            Op::store(xb + sl.lr[t] * kB, Op::frag(al[t]), nat);
+          }
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NSM; ++t) {
-          if (mv[t] && mc[t] == J) {
-            const Frag P = to_frag(am[t]);
+          if (sl.mv[t] && sl.mc[t] == J) {
             Acc x = acc_zero();
-            mma_pqh<false>(x, P, frag_load(xb + J * 256));
+            Op::pqh(x, Op::frag(am[t]), Op::load(xb + J * kB, nat));
             am[t] = x;
-            frag_store(xb + (NB + mr[t]) * 256, to_frag(x));
+            if (J + 1 < NB) Op::store(xb + (NB + sl.mr[t]) * kB, Op::frag(x), nat);
           }
         }
-        __syncthreads();
+        if (J + 1 < NB) {
+          __syncthreads();
 #pragma unroll
-        for (int t = 0; t < NSM; ++t)
-          if (mv[t] && mc[t] > J)
-            mma_pqh<true>(am[t], frag_load(xb + (NB + mr[t]) * 256), frag_load(xb + mc[t] * 256));
+          for (int t = 0; t < NSM; ++t)
+            if (sl.mv[t] && sl.mc[t] > J)
+              Op::pqh(am[t], Op::load(xb + (NB + sl.mr[t]) * kB, nat), Op::load(xb + sl.mc[t] * kB, nat));
+        }
       }
       back_solve();
       // Z += the correction (u kept in W or park)
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t] && lds_park) {
-          const Acc z = to_acc(frag_load(park + (mr[t] * NB + mc[t]) * 256));
+        if (sl.mv[t] && lds_park) {
+          const Acc z = blk_load(park + (sl.mr[t] * NB + sl.mc[t]) * kBlk, nat);
           am[t].re += z.re;
           am[t].im += z.im;
-        } else if (mv[t]) {
-          const int s = 16 * mr[t] + m;
+        } else if (sl.mv[t]) {
+          const int s = 16 * sl.mr[t] + m;
+          float2 u[4];
+          load4(W, s, 16 * sl.mc[t] + 4 * q, s < S, D, vecW, u);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int k = 16 * mc[t] + 4 * q + i;
-            if (s < S && k < D) {
-              const float2 u = reload(W + s * D + k);
-              am[t].re[i] += u.x;
-              am[t].im[i] -= u.y;
-            }
+            am[t].re[i] += u[i].x;
+            am[t].im[i] -= u[i].y;
           }
         }
       }
@@ -684,20 +873,17 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
       // gamma_s = Re(v_s^H u_s) in FP64 for the refined u, u = conj(Z)
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
-        if (mv[t]) {
-          const int s = 16 * mr[t] + m;
+        if (sl.mv[t]) {
+          const int s = 16 * sl.mr[t] + m;
+          float2 v[4];
+          load4(steer, s, 16 * sl.mc[t] + 4 * q, s < S, D, vecV, v);
           double p = 0.0;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int k = 16 * mc[t] + 4 * q + i;
-            if (s < S && k < D) {
-              const float2 v = reload(steer + s * D + k);
-              p += (double)v.x * am[t].re[i] - (double)v.y * am[t].im[i];  // Re(conj(v) conj(z))
-            }
-          }
+          for (int i = 0; i < 4; ++i)  // Re(conj(v) conj(z))
+            p += (double)v[i].x * am[t].re[i] - (double)v[i].y * am[t].im[i];
           p += __shfl_xor(p, 16);
           p += __shfl_xor(p, 32);
-          if (q == 0) gpart[mc[t] * 16 * NS + 16 * mr[t] + m] = p;
+          if (q == 0) L.gpart[sl.mc[t] * 16 * NS + 16 * sl.mr[t] + m] = p;
         }
       }
     }
@@ -707,18 +893,15 @@ __device__ __forceinline__ void bsolve_system(const RSrc& src, const float2* __r
   // ---- w_s = u_s / sqrt(gamma_s), u_s = conj(z_s)
 #pragma unroll
   for (int t = 0; t < NSM; ++t) {
-    if (mv[t]) {
-      const int s = 16 * mr[t] + m;
+    if (sl.mv[t]) {
+      const int s = 16 * sl.mr[t] + m;
       double gam = 0.0;
-      for (int J = 0; J < NB; ++J) gam += gpart[J * 16 * NS + s];
+      for (int J = 0; J < NB; ++J) gam += L.gpart[J * 16 * NS + s];
       const float sc = 1.f / sqrtf((float)gam);
-      if (s < S) {
+      float2 w[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = 16 * mc[t] + 4 * q + i;
-          if (k < D) W[s * D + k] = make_float2(am[t].re[i] * sc, -am[t].im[i] * sc);
-        }
-      }
+      for (int i = 0; i < 4; ++i) w[i] = make_float2(am[t].re[i] * sc, -am[t].im[i] * sc);
+      store4(W, s, 16 * sl.mc[t] + 4 * q, s < S, D, vecW, w);
     }
   }
   if (tid == 0 && info) *info = 0;

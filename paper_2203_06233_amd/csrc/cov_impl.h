@@ -46,6 +46,19 @@ __device__ __forceinline__ void cov_tile_of(int t, int& I, int& J) {
   J = t - i * (i + 1) / 2;
 }
 
+// Tiles of this wave in row order: tile t = wave + NW * i, -1 where there is
+// none.  The coordinates are wave-uniform and computed once.
+template <class Cfg>
+__device__ __forceinline__ void cov_tiles(int (&tI)[Cfg::TPW], int (&tJ)[Cfg::TPW]) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+#pragma unroll
+  for (int i = 0; i < Cfg::TPW; ++i) {
+    const int t = wave + Cfg::NW * i;
+    cov_tile_of(t, tI[i], tJ[i]);
+    if (t >= Cfg::NTILE) tI[i] = -1;
+  }
+}
+
 __device__ __forceinline__ floatx4 mfma_bf16(uint4 a, uint4 b, floatx4 c) {
   typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b),
@@ -69,18 +82,21 @@ __device__ __forceinline__ unsigned int f2e4m3(float x) {
   return s | ((unsigned int)e << 3) | m;
 }
 
-// Accumulate R_hat for one system into accR/accI (tile t = wave + NW*i of the
-// lower block triangle, MFMA 16x16 layout: lane l holds rows 4(l/16)+r,
-// column l%16).  X points at row 0, range cell 0 of the system's Doppler bin
+// Accumulate R_hat for one system into accR/accI: tile i of the wave is the
+// block (tI[i], tJ[i]) of the lower block triangle (tI < 0: none; wave-
+// uniform), MFMA 16x16 layout: lane l holds rows 4(l/16)+r, column l%16; with
+// SWAP the operands change places, which transposes every tile bit for bit:
+// lane l holds row l%16, columns 4(l/16)+r, the fragment order of the blocked
+// solve.  X points at row 0, range cell 0 of the system's Doppler bin
 // (row stride rstride); the N training cells are cm.cell(0 .. N-1).  lds
 // holds Cfg::LDS_BYTES; red holds NW floats.  Returns with the accumulators
 // scaled to R_hat (1/N, FP8 scale undone).
-template <class Cfg>
+template <class Cfg, bool SWAP = false>
 __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, long long rstride, int D, int N,
                                                CellMap cm, unsigned char* lds, float* red,
+                                               const int (&tI)[Cfg::TPW], const int (&tJ)[Cfg::TPW],
                                                floatx4 (&accR)[Cfg::TPW], floatx4 (&accI)[Cfg::TPW]) {
   constexpr int DP = Cfg::DP, NW = Cfg::NW, MODE = Cfg::MODE, NT = Cfg::NT, TPW = Cfg::TPW;
-  constexpr int NTILE = Cfg::NTILE;
   constexpr int F32_PITCH = Cfg::F32_PITCH, BF_PITCH = Cfg::BF_PITCH, F8_PITCH = Cfg::F8_PITCH;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   floatx4 corR[TPW], corI[TPW];
@@ -188,6 +204,15 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
     }
   };
 
+  auto mm4 = [](float a, float b, floatx4 c) {
+    return SWAP ? __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0)
+                : __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  };
+  auto mmb = [](uint4 a, uint4 b, floatx4 c) { return SWAP ? mfma_bf16(b, a, c) : mfma_bf16(a, b, c); };
+  auto mm8 = [](long a, long b, floatx4 c) {
+    return SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(b, a, c, 0, 0, 0)
+                : __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a, b, c, 0, 0, 0);
+  };
   load_chunk(0);
   for (int c0 = 0; c0 < N; c0 += kCovChunk) {
     const int nc = min(kCovChunk, N - c0);
@@ -198,11 +223,8 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
 
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
-      const int t = wave + NW * i;
-      if (t < NTILE) {
-        int I, J;
-        cov_tile_of(t, I, J);
-        const int ra = I * 16 + (lane & 15), rb = J * 16 + (lane & 15);
+      if (tI[i] >= 0) {
+        const int ra = tI[i] * 16 + (lane & 15), rb = tJ[i] * 16 + (lane & 15);
         if (MODE == 0) {
           const float2* xs = reinterpret_cast<const float2*>(lds);
           const int kq = (nc + 3) & ~3;
@@ -214,9 +236,9 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
             for (int kk = 0; kk < kq; kk += 4) {
               const float2 a = xs[ra * F32_PITCH + kk + (lane >> 4)];
               const float2 bb = xs[rb * F32_PITCH + kk + (lane >> 4)];
-              rr = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, bb.x, rr, 0, 0, 0);
-              ii = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, bb.y, ii, 0, 0, 0);
-              tt = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x + a.y, bb.x - bb.y, tt, 0, 0, 0);
+              rr = mm4(a.x, bb.x, rr);
+              ii = mm4(a.y, bb.y, ii);
+              tt = mm4(a.x + a.y, bb.x - bb.y, tt);
             }
             accR[i] += rr + ii;
             accI[i] += (tt - rr) + ii;
@@ -226,10 +248,10 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
             for (int kk = 0; kk < kq; kk += 4) {
               const float2 a = xs[ra * F32_PITCH + kk + (lane >> 4)];
               const float2 bb = xs[rb * F32_PITCH + kk + (lane >> 4)];
-              rr = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, bb.x, rr, 0, 0, 0);
-              ii = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, bb.y, ii, 0, 0, 0);
-              tt = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, bb.x, tt, 0, 0, 0);
-              ri = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, bb.y, ri, 0, 0, 0);
+              rr = mm4(a.x, bb.x, rr);
+              ii = mm4(a.y, bb.y, ii);
+              tt = mm4(a.y, bb.x, tt);
+              ri = mm4(a.x, bb.y, ri);
             }
             accR[i] += rr + ii;
             accI[i] += tt - ri;
@@ -245,18 +267,18 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
             A[p] = pl[p * PS4 + oa];
             Bv[p] = pl[p * PS4 + ob];
           }
-          accR[i] = mfma_bf16(A[0], Bv[0], accR[i]);
-          accR[i] = mfma_bf16(A[3], Bv[3], accR[i]);
-          accI[i] = mfma_bf16(A[3], Bv[0], accI[i]);
-          accI[i] = mfma_bf16(negbf8(A[0]), Bv[3], accI[i]);
+          accR[i] = mmb(A[0], Bv[0], accR[i]);
+          accR[i] = mmb(A[3], Bv[3], accR[i]);
+          accI[i] = mmb(A[3], Bv[0], accI[i]);
+          accI[i] = mmb(negbf8(A[0]), Bv[3], accI[i]);
           constexpr int PA[5] = {0, 1, 0, 2, 1};
           constexpr int PB[5] = {1, 0, 2, 0, 1};
 #pragma unroll
           for (int q = 0; q < 5; ++q) {
-            corR[i] = mfma_bf16(A[PA[q]], Bv[PB[q]], corR[i]);
-            corR[i] = mfma_bf16(A[3 + PA[q]], Bv[3 + PB[q]], corR[i]);
-            corI[i] = mfma_bf16(A[3 + PA[q]], Bv[PB[q]], corI[i]);
-            corI[i] = mfma_bf16(negbf8(A[PA[q]]), Bv[3 + PB[q]], corI[i]);
+            corR[i] = mmb(A[PA[q]], Bv[PB[q]], corR[i]);
+            corR[i] = mmb(A[3 + PA[q]], Bv[3 + PB[q]], corR[i]);
+            corI[i] = mmb(A[3 + PA[q]], Bv[PB[q]], corI[i]);
+            corI[i] = mmb(negbf8(A[PA[q]]), Bv[3 + PB[q]], corI[i]);
           }
         } else {
           const unsigned char* pl = lds;
@@ -265,10 +287,10 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
           const long br = *reinterpret_cast<const long*>(pl + rb * F8_PITCH + 8 * (lane >> 4));
           const long bi = *reinterpret_cast<const long*>(pl + DP * F8_PITCH + rb * F8_PITCH + 8 * (lane >> 4));
           const long nar = ar ^ 0x8080808080808080L;
-          accR[i] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ar, br, accR[i], 0, 0, 0);
-          accR[i] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ai, bi, accR[i], 0, 0, 0);
-          accI[i] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ai, br, accI[i], 0, 0, 0);
-          accI[i] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(nar, bi, accI[i], 0, 0, 0);
+          accR[i] = mm8(ar, br, accR[i]);
+          accR[i] = mm8(ai, bi, accR[i]);
+          accI[i] = mm8(ai, br, accI[i]);
+          accI[i] = mm8(nar, bi, accI[i]);
         }
       }
     }
@@ -286,54 +308,46 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
 }
 
 // delta = eps * Re tr(R_hat) / D with the trace summed in FP64.  dsum holds
-// Cfg::DP doubles; every thread returns the same value.
+// Cfg::DP doubles, to be written again only after another barrier; every
+// thread returns the same value.  Its barrier also ends the products' use of
+// the staging buffer.
 template <class Cfg>
-__device__ __forceinline__ float cov_delta(const floatx4 (&accR)[Cfg::TPW], int D, float eps, double* dsum,
-                                           float* s_delta) {
-  constexpr int NW = Cfg::NW, TPW = Cfg::TPW, NTILE = Cfg::NTILE;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+__device__ __forceinline__ float cov_delta(const floatx4 (&accR)[Cfg::TPW], const int (&tI)[Cfg::TPW],
+                                           const int (&tJ)[Cfg::TPW], int D, float eps, double* dsum) {
+  constexpr int TPW = Cfg::TPW;
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
-    const int t = wave + NW * i;
-    if (t < NTILE) {
-      int I, J;
-      cov_tile_of(t, I, J);
-      if (I == J) {
+    if (tI[i] >= 0 && tI[i] == tJ[i]) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = I * 16 + 4 * (lane >> 4) + r, col = J * 16 + (lane & 15);
-          if (row == col && row < D) dsum[row] = (double)accR[i][r];
-        }
+      for (int r = 0; r < 4; ++r) {
+        const int row = tI[i] * 16 + 4 * (lane >> 4) + r, col = tJ[i] * 16 + (lane & 15);
+        if (row == col && row < D) dsum[row] = (double)accR[i][r];
       }
     }
   }
   __syncthreads();
-  if (wave == 0) {
-    double s = 0.0;
-    for (int q = lane; q < D; q += 64) s += dsum[q];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) *s_delta = (float)((double)eps * s / (double)D);
-  }
-  __syncthreads();
-  return *s_delta;
+  // every wave forms the same sum, which saves handing it over (a barrier)
+  double s = 0.0;
+  for (int q = lane; q < D; q += 64) s += dsum[q];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  return (float)((double)eps * s / (double)D);
 }
 
 // Hand every lower element (row >= col, both < D) of the loaded covariance to
 // emit(row, col, value): diagonal real with delta added.
 template <class Cfg, class Emit>
-__device__ __forceinline__ void cov_emit(const floatx4 (&accR)[Cfg::TPW], const floatx4 (&accI)[Cfg::TPW], int D,
-                                         float delta, Emit emit) {
-  constexpr int NW = Cfg::NW, TPW = Cfg::TPW, NTILE = Cfg::NTILE;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+__device__ __forceinline__ void cov_emit(const floatx4 (&accR)[Cfg::TPW], const floatx4 (&accI)[Cfg::TPW],
+                                         const int (&tI)[Cfg::TPW], const int (&tJ)[Cfg::TPW], int D, float delta,
+                                         Emit emit) {
+  constexpr int TPW = Cfg::TPW;
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
-    const int t = wave + NW * i;
-    if (t < NTILE) {
-      int I, J;
-      cov_tile_of(t, I, J);
+    if (tI[i] >= 0) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = I * 16 + 4 * (lane >> 4) + r, col = J * 16 + (lane & 15);
+        const int row = tI[i] * 16 + 4 * (lane >> 4) + r, col = tJ[i] * 16 + (lane & 15);
         if (row < D && col < D && row >= col) {
           if (row == col) emit(row, col, make_float2(accR[i][r] + delta, 0.f));
           else emit(row, col, make_float2(accR[i][r], accI[i][r]));

@@ -30,32 +30,31 @@ void cov_kernel(const float2* __restrict__ snap,
   __shared__ __align__(16) unsigned char lds[Cfg::LDS_BYTES];
   __shared__ double dsum[DP];
   __shared__ float red[NW];
-  __shared__ float s_delta;
   const int sys = blockIdx.x;
   const int k = sys / d.B, b = sys - (sys / d.B) * d.B;
   const int D = d.D;
   const float2* X = snap + (long long)k * D * d.R;
   floatx4 accR[Cfg::TPW], accI[Cfg::TPW];
-  cov_accumulate<Cfg>(X, d.R, D, d.N, train_cells(d, b), lds, red, accR, accI);
-  const float dl = cov_delta<Cfg>(accR, D, d.eps, dsum, &s_delta);
+  int tI[Cfg::TPW], tJ[Cfg::TPW];
+  cov_tiles<Cfg>(tI, tJ);
+  cov_accumulate<Cfg>(X, d.R, D, d.N, train_cells(d, b), lds, red, tI, tJ, accR, accI);
+  const float dl = cov_delta<Cfg>(accR, tI, tJ, D, d.eps, dsum);
   if (delta_out && threadIdx.x == 0) delta_out[sys] = dl;
   float2* out = cov + (long long)sys * D * D;
   // lower triangle: for each register the 16 lanes of a row write 16
   // consecutive elements of one matrix row
-  cov_emit<Cfg>(accR, accI, D, dl, [&](int row, int col, float2 v) {
+  cov_emit<Cfg>(accR, accI, tI, tJ, D, dl, [&](int row, int col, float2 v) {
     out[(long long)row * D + col] = v;
   });
   // upper triangle as the conjugate transpose: the lane's four registers
   // are four consecutive elements of one matrix row of the upper part, so
   // off-diagonal tiles inside D go out as two 16-byte stores per lane
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63;
   const bool vec_ok = (reinterpret_cast<uintptr_t>(out) & 15) == 0;  // the ABI asks for 8-byte alignment only
 #pragma unroll
   for (int i = 0; i < Cfg::TPW; ++i) {
-    const int t = wave + NW * i;
-    if (t < Cfg::NTILE) {
-      int I, J;
-      cov_tile_of(t, I, J);
+    const int I = tI[i], J = tJ[i];
+    if (I >= 0) {
       const int col = J * 16 + (lane & 15), row0 = I * 16 + 4 * (lane >> 4);
       if (I > J && 16 * I + 16 <= D && (D & 1) == 0 && vec_ok) {
         float4* dst = reinterpret_cast<float4*>(out + (long long)col * D + row0);

@@ -37,17 +37,18 @@ __device__ __forceinline__ void fused_system(const float2* __restrict__ snap, co
   __shared__ SolveShared<K> sh;
   __shared__ double dsum[K::DPC];
   __shared__ float red[K::NT / 64];
-  __shared__ float s_delta;
 
   const int k = sys / d.B, b = sys - (sys / d.B) * d.B;
   const int D = d.D;
   const float2* X = snap + (long long)k * D * d.R;
   floatx4 accR[C::TPW], accI[C::TPW];
-  cov_accumulate<C>(X, d.R, D, d.N, train_cells(d, b), lds, red, accR, accI);
-  const float dl = cov_delta<C>(accR, D, d.eps, dsum, &s_delta);
+  int tI[C::TPW], tJ[C::TPW];
+  cov_tiles<C>(tI, tJ);
+  cov_accumulate<C>(X, d.R, D, d.N, train_cells(d, b), lds, red, tI, tJ, accR, accI);
+  const float dl = cov_delta<C>(accR, tI, tJ, D, d.eps, dsum);
   __syncthreads();  // the staging buffer is dead: reuse it for R_L
   float2* Rp = reinterpret_cast<float2*>(lds);
-  cov_emit<C>(accR, accI, D, dl, [&](int row, int col, float2 v) { Rp[row * (row + 1) / 2 + col] = v; });
+  cov_emit<C>(accR, accI, tI, tJ, D, dl, [&](int row, int col, float2 v) { Rp[row * (row + 1) / 2 + col] = v; });
   __syncthreads();
   solve_system<K, REFINE, true>(PackedR{Rp}, Rp, Rp + K::kPacked, steer + steer_offset(d, sys),
                                 wout + (long long)sys * d.S * D,
@@ -95,61 +96,118 @@ __global__ __launch_bounds__(16 * TY) void fused_batched_kernel(const ProbDesc* 
   }
 }
 
+// R_L in LDS for the residual of the blocked solve: the blocks of the lower
+// block triangle in their register order, both triangles of a diagonal block.
+struct LdsR {
+  const float* base;
+  int NB;
+  __device__ __forceinline__ Acc get(int J, int I, int nat) const {
+    if (J <= I) {  // R[16J + 4q + s][16I + m] = conj(R[16I + m][16J + 4q + s])
+      Acc a = blk_load(base + lblock(NB, I, J) * kBlk, nat);
+      a.im = -a.im;
+      return a;
+    }
+    return blk_load_t(base + lblock(NB, J, I) * kBlk);
+  }
+};
+
 // The same with the blocked matrix-core solve (bsolve_impl.h): NB block
 // columns of the covariance (compile time, for the covariance tiles), NS
-// steering blocks at most, NW waves, NSL / NSM register blocks per wave.  With REFINE the packed R_L stays in LDS for the FP64 residual and the
-// solver's exchange blocks follow it; without, they reuse the same bytes.
+// steering blocks at most, NW waves, NSL / NSM register blocks per wave.  A
+// wave computes the covariance tiles of the very blocks it owns in the solve,
+// in the solve's register order (operands swapped), so the factorisation
+// starts on the accumulators: going through a packed copy in LDS instead took
+// 14 % of the kernel (39 of 274 thousand cycles per system at 96 DOF).  With
+// REFINE the blocks are also stored in LDS for the FP64 residual and the
+// solver's exchange blocks follow them; without, those reuse the staging
+// bytes.
 template <int NB, int NS, int NSL, int NSM, int NW, int MODE, bool REFINE>
 __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, const float2* __restrict__ steer,
                                               float2* __restrict__ wout, int* __restrict__ info_out,
                                               const Dims& d, int sys) {
   using C = CovCfg<16 * NB, NW, MODE>;
   using B = BCfg<NSL, NSM, NW>;
-  constexpr int PACK = (16 * NB * (16 * NB + 1) / 2 * 8 + 255) / 256 * 256;
-  constexpr int EXCH = (int)B::lds_bytes(NB, NS);
-  constexpr int B1 = C::LDS_BYTES > PACK ? C::LDS_BYTES : PACK;
-  constexpr int B2 = REFINE ? PACK + EXCH : EXCH;
-  constexpr int BYTES = B1 > B2 ? B1 : B2;
+  static_assert(C::TPW == NSL, "one covariance tile per L slot");
+  constexpr int RBYTES = NB * (NB + 1) / 2 * kBlk * 4;
+  constexpr int EXCH = (int)B::lds_bytes(NB, NS, REFINE);
+  constexpr int B2 = REFINE ? RBYTES + EXCH : EXCH;
+  constexpr int BYTES = C::LDS_BYTES > B2 ? C::LDS_BYTES : B2;
   __shared__ __align__(16) unsigned char lds[BYTES];
   __shared__ double dsum[16 * NB];
   __shared__ float red[NW];
-  __shared__ float s_delta;
 
   const int k = sys / d.B, b = sys - (sys / d.B) * d.B;
   const int D = d.D;
   const float2* X = snap + (long long)k * D * d.R;
-  floatx4 accR[C::TPW], accI[C::TPW];
-  cov_accumulate<C>(X, d.R, D, d.N, train_cells(d, b), lds, red, accR, accI);
-  const float dl = cov_delta<C>(accR, D, d.eps, dsum, &s_delta);
-  __syncthreads();
-  float2* Rp = reinterpret_cast<float2*>(lds);
-  cov_emit<C>(accR, accI, D, dl, [&](int row, int col, float2 v) { Rp[row * (row + 1) / 2 + col] = v; });
-  __syncthreads();
-  // the packed R_L is dead after the last residual: u of that step is kept
-  // there when it fits
-  constexpr bool PARK = REFINE && PACK >= NS * NB * 256 * 8;
-  bsolve_system<B, REFINE>(PackedR{Rp}, steer + steer_offset(d, sys), wout + (long long)sys * d.S * D,
-                           info_out ? info_out + sys : nullptr,
-                           d, lds + (REFINE ? PACK : 0), PARK ? Rp : nullptr);
+  const float2* V = steer + steer_offset(d, sys);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const Slots<B> sl(D, d.S, wave);
+  floatx4 accR[NSL], accI[NSL];
+  int tI[NSL], tJ[NSL];
+#pragma unroll
+  for (int t = 0; t < NSL; ++t) {
+    tI[t] = sl.lv[t] ? sl.lr[t] : -1;
+    tJ[t] = sl.lc[t];
+  }
+  cov_accumulate<C, true>(X, d.R, D, d.N, train_cells(d, b), lds, red, tI, tJ, accR, accI);
+  Acc al[NSL], am[NSM];
+  load_steer(sl, V, D, d.S, am);  // in flight across the trace
+  const float dl = cov_delta<C>(accR, tI, tJ, D, d.eps, dsum);  // its barrier retires the staging buffer
+
+  float* const Rb = reinterpret_cast<float*>(lds);
+  const SolveLds<B, REFINE> L(lds + (REFINE ? RBYTES : 0), sl.NB, sl.NS);
+  const int lane = lane_tid() & 63, m = lane & 15, q = lane >> 4, nat = nat_ofs();
+#pragma unroll
+  for (int t = 0; t < NSL; ++t) {
+    al[t].re = accR[t];
+    al[t].im = accI[t];
+    if (sl.lv[t]) {
+      float* const blk = REFINE ? Rb + lblock(sl.NB, sl.lr[t], sl.lc[t]) * kBlk : L.xb + sl.lr[t] * kBlk;  // (FP32 exchange blocks)
+      if (sl.lr[t] == sl.lc[t]) {
+        // both triangles from the lower one, diagonal real with the loading,
+        // identity beyond D; a wave's LDS accesses keep their order
+        blk_store(blk, al[t], nat);
+        const Acc T = blk_load_t(blk);
+        const int r = 16 * sl.lr[t] + m;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int c = 4 * q + i;
+          if (c > m) {
+            al[t].re[i] = T.re[i];
+            al[t].im[i] = -T.im[i];
+          } else if (c == m) {
+            al[t].re[i] = r < D ? al[t].re[i] + dl : 1.f;
+            al[t].im[i] = 0.f;
+            L.rdiag[r] = al[t].re[i];
+          }
+        }
+      }
+      if (REFINE) blk_store(blk, al[t], nat);
+      al[t] = acc_neg(al[t]);
+    }
+  }
+  for (int r = threadIdx.x; r < 16 * sl.NB; r += B::NT) L.d64[r] = 0.0;
+  // the R_L blocks are dead after the last residual: u of that step is kept
+  // there when it fits (their number at run time covers NS NB blocks)
+  const bool park = REFINE && sl.NB + 1 >= 2 * sl.NS;
+  bsolve_blocks<B, REFINE>(sl, al, am, L, LdsR{Rb, sl.NB}, V, wout + (long long)sys * d.S * D,
+                           info_out ? info_out + sys : nullptr, d, park ? Rb : nullptr);
 }
 
-// With 8 waves and up to 6 block columns the register allocation is capped
-// at 128 so that two systems share a compute unit (with refinement a few
-// registers spill).  With 4 waves and up to 2 block rows of steering
-// vectors: the one-cube kernel is capped at 168 up to 4 block columns (three
-// systems per compute unit instead of two); the persistent batched kernel,
-// which left to itself holds more registers across its loop (up to 196),
-// at 128 up to 2 block columns and 168 at 3 (four and three systems per
-// compute unit) -- all without spills.
-template <int NB, int NS, int NW, bool BATCHED>
+// Register budgets (waves per SIMD) that the kernels meet with no or few
+// spills: 128 registers with 8 waves and up to 6 block columns, so that two
+// systems share a compute unit (16 registers spill), with 4 waves up to 3
+// and with one wave; 168 with 4 waves and 4 block columns and with 2 waves.
+template <int NB, int NS, int NW>
 constexpr int bfused_min_waves() {
   if (NW == 8 && NB <= 6) return 4;
-  if (NW == 4 && NS <= 2) return BATCHED ? (NB <= 2 ? 4 : NB == 3 ? 3 : 1) : (NB <= 4 ? 3 : 1);
-  return 1;
+  if (NW == 4 && NS <= 2) return NB <= 3 ? 4 : NB == 4 ? 3 : 1;
+  if (NW == 1 && NS <= 2) return 4;
+  return NW <= 2 ? 3 : 1;
 }
 
 template <int NB, int NS, int NSL, int NSM, int NW, int MODE, bool REFINE>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(bfused_min_waves<NB, NS, NW, false>())))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(bfused_min_waves<NB, NS, NW>())))
 void bfused_kernel(const float2* __restrict__ snap,
                                                          const float2* __restrict__ steer,
                                                          float2* __restrict__ wout, int* __restrict__ info_out,
@@ -158,7 +216,7 @@ void bfused_kernel(const float2* __restrict__ snap,
 }
 
 template <int NB, int NS, int NSL, int NSM, int NW, int MODE, bool REFINE>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(bfused_min_waves<NB, NS, NW, true>())))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(bfused_min_waves<NB, NS, NW>())))
 void bfused_batched_kernel(const ProbDesc* __restrict__ desc, int n,
                                                                  long long total, unsigned long long* queue) {
   __shared__ long long slot;
