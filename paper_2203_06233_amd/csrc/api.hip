@@ -376,33 +376,44 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
   }
   const int prec = probs[0].precision, refine = probs[0].refine_steps;
 
-  // Doppler launches, one per pulse count (at most kMaxBatchArg cubes each).
-  std::vector<std::pair<stap::BatchIndex, int>> dop;
-  for (int P : {32, 64, 100, 128, 256, 512}) {
+  // Doppler launches, one per pulse count (at most kMaxBatchArg cubes each),
+  // in the tile shape that the launch's cubes fill together.
+  struct Dop {
     stap::BatchIndex bi;
-    bi.n = 0;
-    int tiles = 0;
-    for (int i = 0; i < n_probs; ++i) {
-      if (desc[i].d.P != P) continue;
-      if (bi.n == stap::kMaxBatchArg) {
-        bi.tile_begin[bi.n] = tiles;
-        dop.push_back({bi, P});
-        bi.n = 0;
-        tiles = 0;
+    int P;
+    bool wide, sub;
+  };
+  std::vector<Dop> dop;
+  for (int P : {32, 64, 100, 128, 256, 512}) {
+    std::vector<int> at;
+    for (int i = 0; i < n_probs; ++i)
+      if (desc[i].d.P == P) at.push_back(i);
+    for (size_t first = 0; first < at.size(); first += stap::kMaxBatchArg) {
+      const int n = (int)std::min<size_t>(stap::kMaxBatchArg, at.size() - first);
+      Dop x;
+      x.P = P;
+      x.sub = false;
+      long long wide_tiles = 0;
+      for (int j = 0; j < n; ++j) {
+        const Dims& d = desc[at[first + j]].d;
+        x.sub = x.sub || d.sub > 1;
+        wide_tiles += stap::doppler_tiles(d, true);
       }
-      bi.prob[bi.n] = i;
-      bi.tile_begin[bi.n] = tiles;
-      tiles += stap::doppler_tiles(desc[i].d);
-      ++bi.n;
-    }
-    if (bi.n > 0) {
-      bi.tile_begin[bi.n] = tiles;
-      dop.push_back({bi, P});
+      x.wide = stap::doppler_wide(P, x.sub, wide_tiles);
+      x.bi.n = n;
+      int tiles = 0;
+      for (int j = 0; j < n; ++j) {
+        x.bi.prob[j] = at[first + j];
+        x.bi.tile_begin[j] = tiles;
+        tiles += stap::doppler_tiles(desc[at[first + j]].d, x.wide);
+      }
+      x.bi.tile_begin[n] = tiles;
+      dop.push_back(x);
     }
   }
   auto enqueue = [&](hipStream_t s) -> hipError_t {
     for (auto& x : dop) {
-      hipError_t e = stap::launch_doppler_batched(x.second, table, x.first, x.first.tile_begin[x.first.n], s);
+      hipError_t e = stap::launch_doppler_batched(x.P, table, x.bi, x.bi.tile_begin[x.bi.n], x.wide, x.sub, s);
       if (e != hipSuccess) return e;
     }
     for (size_t i = 0; i < groups.size(); ++i) {
@@ -428,6 +439,7 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
   std::string key = std::to_string(dev) + "|" + std::to_string((uintptr_t)ws0) + "|" +
                     std::to_string(prec) + "|" + std::to_string(refine);
   for (const Group& g : groups) key += "|v" + std::to_string(g.ty);
+  for (const Dop& x : dop) key += x.wide ? (x.sub ? "|ws" : "|w") : (x.sub ? "|s" : "|n");
   for (auto& pd : desc) {
     key += "|" + std::to_string(pd.d.C) + "," + std::to_string(pd.d.P) + "," + std::to_string(pd.d.R) + "," +
            std::to_string(pd.d.T) + "," + std::to_string(pd.d.B) + "," + std::to_string(pd.d.S);

@@ -21,31 +21,59 @@
 // direct in-register DFTs.  Twiddles of the inner DFTs
 // are compile-time constants; the P-point twiddles and the Hann window come
 // from correctly rounded compile-time tables, staged once per workgroup in LDS.
+//
+// The pass is bound by HBM, and how close it comes is set by the length of
+// the runs it touches (RT cells of 8 bytes in each of P rows read and P T
+// rows written) and by the waves in flight.  Copies of the same access
+// pattern without the arithmetic reach 4.6 TB/s with 128-byte runs and 5.0
+// with 256-byte ones on the 32 x 256 x 16384 cube.  Every pulse count
+// therefore has a narrow tile (256 threads) and, where the registers allow
+// it, a wide one that needs enough cells to fill the chip:
+//                                             before    narrow     wide
+//    64 pulses, 64 channels,  4096 cells                 0.102    0.097 ms
+//   128 pulses, 16 channels,  4096 cells      0.056      0.055    0.050
+//   256 pulses, 32 channels, 16384 cells      0.94       0.94     0.86
+//   512 pulses, 64 channels,  4096 cells      1.45       1.01     0.90
+//   100 pulses, 1000 elements, 30000 cells    5.03       5.0      4.08
+// (before: the narrow tile with the subarray loads in every kernel).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
 namespace stap {
 
-template <int P>
+// P = P1 * P2; RT range cells and NT threads per workgroup; WPE waves per
+// SIMD the registers are held to.  WIDE: the tile for large launches.
+template <int P, bool WIDE>
 struct FftShape {
   static constexpr int LOG = ilog2(P);
   static constexpr int P1 = 1 << ((LOG + 1) / 2);
   static constexpr int P2 = P / P1;
-  static constexpr int NT = 256;       // threads per workgroup
-  static constexpr int RT = NT / P2;   // range cells per workgroup
+  static constexpr int RT = !WIDE ? 256 / P2 : P == 64 ? 128 : P == 128 ? 64 : P >= 256 ? 32 : 256 / P2;
+  static constexpr int NT = P2 * RT;
+  static constexpr int WPE = P == 512 ? 1 : P == 256 && !WIDE ? 3 : 4;
+  static constexpr int ELEMS = 1;  // elements loaded at a time (subarrays)
 };
-// The paper's 100 pulses: 10 x 10 on 320 threads, 32 cells per workgroup, so
-// that every wave reads whole 128-byte lines of two pulse rows.
-template <>
-struct FftShape<100> {
-  static constexpr int P1 = 10, P2 = 10, NT = 320, RT = 32;
+// The paper's 100 pulses: 10 x 10, 32 or 96 cells (whole 128-byte lines).
+// With subarrays the loads of several elements are issued before their
+// additions so that enough of them are in flight to stream the cube; the
+// wide tile, with three times the waves per workgroup, needs fewer.
+template <bool WIDE>
+struct FftShape<100, WIDE> {
+  static constexpr int P1 = 10, P2 = 10, RT = WIDE ? 96 : 32, NT = 10 * RT, WPE = 4, ELEMS = WIDE ? 2 : 4;
 };
 
 // One workgroup's tile: channel c, range cells r0 .. r0+RT-1 of one cube.
-template <int P>
+// The groups between sched_barriers keep the compiler from gathering all
+// window, twiddle and address values of an unrolled loop before their use.
+// SUB is a template parameter because the subarray loads of a kernel that
+// has them set its register count (256 instead of 140 at 512 pulses) whether
+// or not a cube uses them.
+template <int P, bool WIDE, bool SUB>
 __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, float2* __restrict__ snap,
                                              const Dims& d, int c, int r0) {
-  using Sh = FftShape<P>;
+  using Sh = FftShape<P, WIDE>;
   constexpr int P1 = Sh::P1, P2 = Sh::P2, RT = Sh::RT, NT = Sh::NT;
   __shared__ float2 ybuf[P1 * P2 * RT];  // [k1][n2][cell]
   __shared__ float2 tw[P];
@@ -60,21 +88,21 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
 
   const int col = tid % RT, n2 = tid / RT;
   const int r = r0 + col;
-  const bool live = r < d.R && n2 < P2;
+  const bool live = r < d.R;
   float2 x[P1];
 #pragma unroll
   for (int n1 = 0; n1 < P1; ++n1) x[n1] = make_float2(0.f, 0.f);
-  if (live && d.sub == 1) {
-    const float2* src = cube + (long long)c * d.sc + r;
+  if (live && (!SUB || d.sub == 1)) {
+    const float2* src = cube + (long long)c * d.sc + (long long)n2 * d.sp + r;
 #pragma unroll
-    for (int n1 = 0; n1 < P1; ++n1) x[n1] = load_stream(src + (long long)(P2 * n1 + n2) * d.sp);
+    for (int n1 = 0; n1 < P1; ++n1) {
+      x[n1] = load_stream(src + (long long)(P2 * n1) * d.sp);
+      if (n1 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
   } else if (live) {
     // channel c is the sum of array elements c*sub .. c*sub + sub - 1,
-    // added in element order; with few samples per thread the loads of four
-    // elements are issued before their additions so that enough of them are
-    // in flight to stream the cube (more would cost the registers that set
-    // the occupancy of the whole kernel)
-    constexpr int EU = P1 <= 10 ? 4 : 1;
+    // added in element order
+    constexpr int EU = Sh::ELEMS;
     int e = 0;
     for (; e + EU <= d.sub; e += EU) {
       float2 v[EU][P1];
@@ -111,14 +139,14 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
       const int q = P2 * n1 + n2 - t;
       const float h = (q >= 0 && q < P) ? hwin[q] : 0.f;
       v[n1] = make_float2(x[n1].x * h, x[n1].y * h);
+      if (n1 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
     dft_any<P1>(v);
-    if (n2 < P2) {
 #pragma unroll
-      for (int k1 = 0; k1 < P1; ++k1) {
-        const float2 y = (k1 == 0) ? v[k1] : cmul(v[k1], tw[k1 * n2]);
-        ybuf[(k1 * P2 + n2) * RT + col] = y;
-      }
+    for (int k1 = 0; k1 < P1; ++k1) {
+      const float2 y = (k1 == 0) ? v[k1] : cmul(v[k1], tw[k1 * n2]);
+      ybuf[(k1 * P2 + n2) * RT + col] = y;
+      if (k1 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
     const int dof = t * d.C + c;
@@ -132,86 +160,119 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
       if (d.tap_rel && t > 0) {
         // tap t referenced to its own first pulse: times exp(+2 pi i k t / P)
 #pragma unroll
-        for (int k2 = 0; k2 < P2; ++k2) z[k2] = cmulc(z[k2], tw[((k1 + P1 * k2) * t) % P]);
+        for (int k2 = 0; k2 < P2; ++k2) {
+          z[k2] = cmulc(z[k2], tw[((k1 + P1 * k2) * t) % P]);
+          if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
       }
       if (r3 < d.R) {
-        float2* dst = snap + (long long)dof * d.R + r3;
+        float2* dst = snap + ((long long)k1 * d.D + dof) * d.R + r3;
+        const long long step = (long long)P1 * d.D * d.R;
 #pragma unroll
-        for (int k2 = 0; k2 < P2; ++k2) store_stream(dst + (long long)(k1 + P1 * k2) * d.D * d.R, z[k2]);
+        for (int k2 = 0; k2 < P2; ++k2) {
+          store_stream(dst, z[k2]);
+          dst += step;
+          if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
     __syncthreads();
   }
 }
 
-// More workgroups per compute unit for more loads in flight, where the
-// registers allow it without spills: three at 256 pulses (168 VGPRs), three
-// 320-thread groups at 100 pulses (128 VGPRs).
-template <int P>
-__global__ __launch_bounds__(FftShape<P>::NT) __attribute__((amdgpu_waves_per_eu(P == 256 ? 3 : P == 100 ? 4 : 1)))
-void doppler_kernel(const float2* __restrict__ cube,
-                                                      float2* __restrict__ snap, Dims d) {
-  doppler_tile<P>(cube, snap, d, blockIdx.y, blockIdx.x * FftShape<P>::RT);
+// Tile of a workgroup.  Workgroups go round-robin over the eight XCDs; with
+// long transforms each XCD takes one contiguous part of the tiles instead,
+// so that neighbouring runs of a row are written through the same L2 at about
+// the same time (0.88 -> 0.86 ms on the 32 x 256 x 16384 cube; with up to
+// 128 pulses the plain order is as fast or faster).
+template <int P, bool WIDE>
+__device__ __forceinline__ int tile_of(int id, int n) {
+  if (!WIDE || P < 256) return id;
+  const int xcd = id & 7;
+  return xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);
+}
+
+template <int P, bool WIDE, bool SUB>
+__global__ __launch_bounds__((FftShape<P, WIDE>::NT)) __attribute__((amdgpu_waves_per_eu(FftShape<P, WIDE>::WPE)))
+void doppler_kernel(const float2* __restrict__ cube, float2* __restrict__ snap, Dims d) {
+  constexpr int RT = FftShape<P, WIDE>::RT;
+  const int ntr = (d.R + RT - 1) / RT;
+  const int u = tile_of<P, WIDE>(blockIdx.x, gridDim.x);
+  doppler_tile<P, WIDE, SUB>(cube, snap, d, u / ntr, (u % ntr) * RT);
 }
 
 // Batched: the workgroups of several cubes with the same P in one grid.
-template <int P>
-__global__ __launch_bounds__(FftShape<P>::NT) __attribute__((amdgpu_waves_per_eu(P == 256 ? 3 : P == 100 ? 4 : 1)))
+template <int P, bool WIDE, bool SUB>
+__global__ __launch_bounds__((FftShape<P, WIDE>::NT)) __attribute__((amdgpu_waves_per_eu(FftShape<P, WIDE>::WPE)))
 void doppler_batched_kernel(const ProbDesc* __restrict__ desc, BatchIndex bi) {
-  constexpr int RT = FftShape<P>::RT;
-  const int g = blockIdx.x;
+  constexpr int RT = FftShape<P, WIDE>::RT;
+  const int g = tile_of<P, WIDE>(blockIdx.x, gridDim.x);
   int j = 0;
   while (j + 1 < bi.n && bi.tile_begin[j + 1] <= g) ++j;
   const ProbDesc& pd = desc[bi.prob[j]];
   const Dims d = pd.d;
   const int local = g - bi.tile_begin[j];
   const int ntr = (d.R + RT - 1) / RT;
-  doppler_tile<P>(pd.cube, pd.snap, d, local / ntr, (local % ntr) * RT);
+  doppler_tile<P, WIDE, SUB>(pd.cube, pd.snap, d, local / ntr, (local % ntr) * RT);
 }
 
-int doppler_tiles(const Dims& d) {
-  int rt = 0;
-  switch (d.P) {
-    case 32: rt = FftShape<32>::RT; break;
-    case 64: rt = FftShape<64>::RT; break;
-    case 100: rt = FftShape<100>::RT; break;
-    case 128: rt = FftShape<128>::RT; break;
-    case 256: rt = FftShape<256>::RT; break;
-    case 512: rt = FftShape<512>::RT; break;
-    default: return 0;
-  }
-  return ((d.R + rt - 1) / rt) * d.C;
-}
+namespace {
 
-hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex& bi, int tiles, hipStream_t st) {
-  if (tiles <= 0) return hipSuccess;
+template <class F>
+auto by_pulse(int P, F&& f) {
   switch (P) {
-    case 32: hipLaunchKernelGGL(doppler_batched_kernel<32>, dim3(tiles), dim3(FftShape<32>::NT), 0, st, desc, bi); break;
-    case 64: hipLaunchKernelGGL(doppler_batched_kernel<64>, dim3(tiles), dim3(FftShape<64>::NT), 0, st, desc, bi); break;
-    case 100: hipLaunchKernelGGL(doppler_batched_kernel<100>, dim3(tiles), dim3(FftShape<100>::NT), 0, st, desc, bi); break;
-    case 128: hipLaunchKernelGGL(doppler_batched_kernel<128>, dim3(tiles), dim3(FftShape<128>::NT), 0, st, desc, bi); break;
-    case 256: hipLaunchKernelGGL(doppler_batched_kernel<256>, dim3(tiles), dim3(FftShape<256>::NT), 0, st, desc, bi); break;
-    case 512: hipLaunchKernelGGL(doppler_batched_kernel<512>, dim3(tiles), dim3(FftShape<512>::NT), 0, st, desc, bi); break;
-    default: return hipErrorInvalidValue;
+    case 32: return f(std::integral_constant<int, 32>{});
+    case 64: return f(std::integral_constant<int, 64>{});
+    case 100: return f(std::integral_constant<int, 100>{});
+    case 128: return f(std::integral_constant<int, 128>{});
+    case 256: return f(std::integral_constant<int, 256>{});
   }
-  return hipGetLastError();
+  return f(std::integral_constant<int, 512>{});
+}
+
+}  // namespace
+
+int doppler_tiles(const Dims& d, bool wide) {
+  return by_pulse(d.P, [&](auto p) {
+    const int rt = wide ? FftShape<p.value, true>::RT : FftShape<p.value, false>::RT;
+    return (d.R + rt - 1) / rt * d.C;
+  });
+}
+
+// Wide tiles where their workgroups give every compute unit 16 waves; with
+// subarrays only the 100-pulse shape has one.
+bool doppler_wide(int P, bool sub, long long wide_tiles) {
+  if (P == 32 || (sub && P != 100)) return false;
+  return by_pulse(P, [&](auto p) { return wide_tiles * FftShape<p.value, true>::NT >= 256LL * 1024; });
+}
+
+hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex& bi, int tiles, bool wide, bool sub,
+                                  hipStream_t st) {
+  if (tiles <= 0) return hipSuccess;
+  return by_pulse(P, [&](auto p) {
+    constexpr int Q = p.value;
+    constexpr bool W = Q != 32, WS = Q == 100;
+    const dim3 g(tiles), wt(FftShape<Q, W>::NT), nt(FftShape<Q, false>::NT);
+    if (!sub && wide) hipLaunchKernelGGL((doppler_batched_kernel<Q, W, false>), g, wt, 0, st, desc, bi);
+    else if (!sub) hipLaunchKernelGGL((doppler_batched_kernel<Q, false, false>), g, nt, 0, st, desc, bi);
+    else if (WS && wide) hipLaunchKernelGGL((doppler_batched_kernel<Q, WS, true>), g, wt, 0, st, desc, bi);
+    else hipLaunchKernelGGL((doppler_batched_kernel<Q, false, true>), g, nt, 0, st, desc, bi);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipStream_t st) {
-  auto go = [&](auto kern, int rt, int nt) {
-    dim3 grid((d.R + rt - 1) / rt, d.C);
-    hipLaunchKernelGGL(kern, grid, dim3(nt), 0, st, cube, snap, d);
+  const bool sub = d.sub > 1, wide = doppler_wide(d.P, sub, doppler_tiles(d, true));
+  return by_pulse(d.P, [&](auto p) {
+    constexpr int Q = p.value;
+    constexpr bool W = Q != 32, WS = Q == 100;
+    const dim3 g(doppler_tiles(d, wide)), wt(FftShape<Q, W>::NT), nt(FftShape<Q, false>::NT);
+    if (!sub && wide) hipLaunchKernelGGL((doppler_kernel<Q, W, false>), g, wt, 0, st, cube, snap, d);
+    else if (!sub) hipLaunchKernelGGL((doppler_kernel<Q, false, false>), g, nt, 0, st, cube, snap, d);
+    else if (WS && wide) hipLaunchKernelGGL((doppler_kernel<Q, WS, true>), g, wt, 0, st, cube, snap, d);
+    else hipLaunchKernelGGL((doppler_kernel<Q, false, true>), g, nt, 0, st, cube, snap, d);
     return hipGetLastError();
-  };
-  switch (d.P) {
-    case 32: return go(doppler_kernel<32>, FftShape<32>::RT, FftShape<32>::NT);
-    case 64: return go(doppler_kernel<64>, FftShape<64>::RT, FftShape<64>::NT);
-    case 100: return go(doppler_kernel<100>, FftShape<100>::RT, FftShape<100>::NT);
-    case 128: return go(doppler_kernel<128>, FftShape<128>::RT, FftShape<128>::NT);
-    case 256: return go(doppler_kernel<256>, FftShape<256>::RT, FftShape<256>::NT);
-    case 512: return go(doppler_kernel<512>, FftShape<512>::RT, FftShape<512>::NT);
-  }
-  return hipErrorInvalidValue;
+  });
 }
 
 }  // namespace stap

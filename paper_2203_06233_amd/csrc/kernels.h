@@ -28,9 +28,13 @@ struct BatchIndex {
   int tile_begin[kMaxBatchArg + 1];
 };
 
-// Workgroups of the Doppler kernel for one cube; batched Doppler launch.
-int doppler_tiles(const Dims& d);
-hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex& bi, int tiles, hipStream_t st);
+// Doppler tiles (workgroups) of one cube in the narrow or the wide shape,
+// whether a launch with that many wide tiles (with subarrays or not) takes the
+// wide shape, and the batched launch.
+int doppler_tiles(const Dims& d, bool wide);
+bool doppler_wide(int P, bool sub, long long wide_tiles);
+hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex& bi, int tiles, bool wide, bool sub,
+                                  hipStream_t st);
 
 // Persistent fused covariance -> solve over every system of every cube of the
 // table (all fused_supported, one precision; max_dof / max_steer the largest
