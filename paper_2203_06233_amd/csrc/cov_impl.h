@@ -110,11 +110,14 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
 
   float qscale = 1.f;
   if (MODE == 2) {
+    // half waves take rows, so that no element index has to be divided by N
     float mx = 0.f;
-    for (int e = tid; e < D * N; e += NT) {
-      const int row = e / N, cc = e - (e / N) * N;
-      const float2 v = X[(long long)row * rstride + cm.cell(cc)];
-      mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+    for (int row = tid >> 5; row < D; row += NT / 32) {
+      const float2* const src = X + (long long)row * rstride;
+      for (int c = tid & 31; c < N; c += 32) {
+        const float2 v = src[cm.cell(c)];
+        mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+      }
     }
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     if (lane == 0) red[wave] = mx;
@@ -135,58 +138,48 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
   constexpr int PF = (NE + NT - 1) / NT;
   constexpr int PV = MODE == 1 ? 2 : 1;
   float2 pf[PF][PV];
-  // Training cell c lives at lo[c] for c < nl and at hi[c] beyond (both
-  // bases workgroup-uniform; in block mode nl = N and only lo is used).  A
-  // pair of cells straddles the two runs only at c = nl - 1.
-  const float2* const lo = X + cm.a0;
-  const float2* const hi = X + (cm.a1 - cm.nl);
-  const int nl = cm.nl;
+  // Every thread loads the same cells of each chunk, PV of them, from PF rows.
+  // Cells beyond N and rows beyond D are read from the last one instead (a
+  // valid address) and cleared when they are staged: a load that only some
+  // lanes make, or that comes from one of several branches, ends in register
+  // copies, which wait for it and undo the prefetch.
+  constexpr int PER_ROW = MODE == 1 ? kCovChunk / 2 : kCovChunk;  // staging elements of a row
+  constexpr int ROWS = NT / PER_ROW;                              // rows per step of the workgroup
+  static_assert(NT % PER_ROW == 0, "a staging step covers whole rows");
+  const int row0 = tid / PER_ROW, cell0 = PV * (tid % PER_ROW);
+  const float2* rp[PF];
+#pragma unroll
+  for (int i = 0; i < PF; ++i) rp[i] = X + (long long)min(row0 + ROWS * i, D - 1) * rstride;
   auto load_chunk = [&](int c0) {
-    const int nc = min(kCovChunk, N - c0);
+    int at[PV];
 #pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      const int e = tid + NT * i;
-      if (MODE == 1) {
-        const int row = e / (kCovChunk / 2), cp = e % (kCovChunk / 2);
-        float2 v0 = make_float2(0.f, 0.f), v1 = v0;
-        if (e < NE && row < D) {
-          const int c = c0 + 2 * cp;
-          const long long ro = (long long)row * rstride + c;
-          if (c + 1 != nl) {
-            const float2* src = (c < nl ? lo : hi) + ro;
-            if (2 * cp < nc) v0 = src[0];
-            if (2 * cp + 1 < nc) v1 = src[1];
-          } else {
-            if (2 * cp < nc) v0 = lo[ro];
-            if (2 * cp + 1 < nc) v1 = hi[ro + 1];
-          }
-        }
-        pf[i][0] = v0;
-        pf[i][PV - 1] = v1;
-      } else {
-        const int row = e / kCovChunk, cc = e % kCovChunk;
-        float2 v = make_float2(0.f, 0.f);
-        const int c = c0 + cc;
-        if (e < NE && row < D && cc < nc) v = (c < nl ? lo : hi)[(long long)row * rstride + c];
-        pf[i][0] = v;
-      }
-    }
+    for (int k = 0; k < PV; ++k) at[k] = cm.cell(min(c0 + cell0 + k, N - 1));
+#pragma unroll
+    for (int i = 0; i < PF; ++i)
+#pragma unroll
+      for (int k = 0; k < PV; ++k) pf[i][k] = rp[i][at[k]];
   };
-  auto store_chunk = [&]() {
+  auto store_chunk = [&](int nc) {
+    if (nc < kCovChunk || D < DP) {
+#pragma unroll
+      for (int i = 0; i < PF; ++i)
+#pragma unroll
+        for (int k = 0; k < PV; ++k)
+          if (row0 + ROWS * i >= D || cell0 + k >= nc) pf[i][k] = make_float2(0.f, 0.f);
+    }
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
-      const int e = tid + NT * i;
-      if (e >= NE) continue;
+      const int row = row0 + ROWS * i;
+      if ((DP % ROWS) != 0 && row >= DP) continue;
       if (MODE == 0) {
         float2* xs = reinterpret_cast<float2*>(lds);
-        xs[(e / kCovChunk) * F32_PITCH + e % kCovChunk] = pf[i][0];
+        xs[row * F32_PITCH + cell0] = pf[i][0];
       } else if (MODE == 1) {
         unsigned int* pl = reinterpret_cast<unsigned int*>(lds);
         constexpr int PS = DP * BF_PITCH / 2;  // plane stride, uint32
-        const int row = e / (kCovChunk / 2), cp = e % (kCovChunk / 2);
         const float2 v0 = pf[i][0], v1 = pf[i][PV - 1];
         unsigned int h, m, l;
-        const int base = row * (BF_PITCH / 2) + cp;
+        const int base = row * (BF_PITCH / 2) + cell0 / 2;
         split3x2(v0.x, v1.x, h, m, l);
         pl[0 * PS + base] = h;
         pl[1 * PS + base] = m;
@@ -197,9 +190,8 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
         pl[5 * PS + base] = l;
       } else {
         unsigned char* pl = lds;
-        const int row = e / kCovChunk, cc = e % kCovChunk;
-        pl[row * F8_PITCH + cc] = (unsigned char)f2e4m3(pf[i][0].x * qscale);
-        pl[DP * F8_PITCH + row * F8_PITCH + cc] = (unsigned char)f2e4m3(pf[i][0].y * qscale);
+        pl[row * F8_PITCH + cell0] = (unsigned char)f2e4m3(pf[i][0].x * qscale);
+        pl[DP * F8_PITCH + row * F8_PITCH + cell0] = (unsigned char)f2e4m3(pf[i][0].y * qscale);
       }
     }
   };
@@ -217,7 +209,7 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
   for (int c0 = 0; c0 < N; c0 += kCovChunk) {
     const int nc = min(kCovChunk, N - c0);
     __syncthreads();  // the previous chunk's products are done with the staging buffer
-    store_chunk();
+    store_chunk(nc);
     __syncthreads();
     if (c0 + kCovChunk < N) load_chunk(c0 + kCovChunk);
 
@@ -261,25 +253,46 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
           constexpr int PS4 = DP * BF_PITCH / 8;
           const int oa = ra * (BF_PITCH / 8) + (lane >> 4);
           const int ob = rb * (BF_PITCH / 8) + (lane >> 4);
-          uint4 A[6], Bv[6];
-#pragma unroll
-          for (int p = 0; p < 6; ++p) {
-            A[p] = pl[p * PS4 + oa];
-            Bv[p] = pl[p * PS4 + ob];
-          }
-          accR[i] = mmb(A[0], Bv[0], accR[i]);
-          accR[i] = mmb(A[3], Bv[3], accR[i]);
-          accI[i] = mmb(A[3], Bv[0], accI[i]);
-          accI[i] = mmb(negbf8(A[0]), Bv[3], accI[i]);
-          constexpr int PA[5] = {0, 1, 0, 2, 1};
-          constexpr int PB[5] = {1, 0, 2, 0, 1};
-#pragma unroll
-          for (int q = 0; q < 5; ++q) {
-            corR[i] = mmb(A[PA[q]], Bv[PB[q]], corR[i]);
-            corR[i] = mmb(A[3 + PA[q]], Bv[3 + PB[q]], corR[i]);
-            corI[i] = mmb(A[3 + PA[q]], Bv[PB[q]], corI[i]);
-            corI[i] = mmb(negbf8(A[PA[q]]), Bv[3 + PB[q]], corI[i]);
-          }
+          // cor takes one pair of terms: rows (xr, xi), columns (yr, yi)
+          auto cross = [&](const uint4& xr, const uint4& xi, const uint4& nxr, const uint4& yr, const uint4& yi) {
+            corR[i] = mmb(xr, yr, corR[i]);
+            corR[i] = mmb(xi, yi, corR[i]);
+            corI[i] = mmb(xi, yr, corI[i]);
+            corI[i] = mmb(nxr, yi, corI[i]);
+          };
+          // Where the budget of 128 registers would spill with all twelve
+          // planes of the operands at hand (48 registers; three tiles a wave
+          // on 8 waves, five on 16), they are fetched as the products need
+          // them, with fences that keep the compiler from gathering them;
+          // elsewhere that only exposes the LDS latency.
+          constexpr bool STEPS = (DP == 96 && NW == 8) || (DP == 192 && NW == 16);
+          auto fence = [] {
+            if (STEPS) __builtin_amdgcn_sched_barrier(0);
+          };
+          auto ld = [&](int p, int o) { return pl[p * PS4 + o]; };
+          uint4 Ar = ld(0, oa), Ai = ld(3, oa), Br = ld(0, ob), Bi = ld(3, ob);
+          uint4 nAr = negbf8(Ar);
+          uint4 br = ld(1, ob), bi = ld(4, ob);
+          fence();
+          accR[i] = mmb(Ar, Br, accR[i]);
+          accR[i] = mmb(Ai, Bi, accR[i]);
+          accI[i] = mmb(Ai, Br, accI[i]);
+          accI[i] = mmb(nAr, Bi, accI[i]);
+          uint4 ar = ld(1, oa), ai = ld(4, oa);
+          fence();
+          cross(Ar, Ai, nAr, br, bi);  // h m
+          uint4 cr = ld(2, ob), ci = ld(5, ob);
+          const uint4 nar = negbf8(ar);
+          fence();
+          cross(ar, ai, nar, Br, Bi);  // m h
+          fence();
+          cross(Ar, Ai, nAr, cr, ci);  // h l
+          Ar = ld(2, oa);
+          Ai = ld(5, oa);
+          fence();
+          nAr = negbf8(Ar);
+          cross(Ar, Ai, nAr, Br, Bi);  // l h
+          cross(ar, ai, nar, br, bi);  // m m
         } else {
           const unsigned char* pl = lds;
           const long ar = *reinterpret_cast<const long*>(pl + ra * F8_PITCH + 8 * (lane >> 4));
@@ -298,13 +311,24 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
 
   const float invs2 = (MODE == 2) ? 1.f / (qscale * qscale) : 1.f;
   const float fN = (float)N;
+  if ((N & (N - 1)) == 0) {  // the reciprocal is exact: same bits, a tenth of the instructions
+    const float rN = 1.f / fN;
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
+    for (int i = 0; i < TPW; ++i)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      accR[i][r] = ((accR[i][r] + corR[i][r]) * invs2) / fN;
-      accI[i][r] = ((accI[i][r] + corI[i][r]) * invs2) / fN;
-    }
+      for (int r = 0; r < 4; ++r) {
+        accR[i][r] = ((accR[i][r] + corR[i][r]) * invs2) * rN;
+        accI[i][r] = ((accI[i][r] + corI[i][r]) * invs2) * rN;
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        accR[i][r] = ((accR[i][r] + corR[i][r]) * invs2) / fN;
+        accI[i][r] = ((accI[i][r] + corI[i][r]) * invs2) / fN;
+      }
+  }
 }
 
 // delta = eps * Re tr(R_hat) / D with the trace summed in FP64.  dsum holds
