@@ -81,7 +81,9 @@ typedef enum stap_status {
 
 typedef enum stap_precision {
   /* FP32 throughout: FP32 FFT, FP32 covariance on FP32 MFMA, FP32
-   * Cholesky/solves, FP32 inner products. */
+   * Cholesky/solves, inner products with FP32-level error (each FP32 operand
+   * split exactly into three BF16 terms, FP32 accumulation, as on the mixed
+   * path). */
   STAP_PREC_FP32 = 0,
   /* Mixed: covariance and inner products as BF16 MFMA products with FP32
    * accumulation (each FP32 operand split exactly into three BF16 terms),
@@ -282,9 +284,9 @@ stap_status stap_run_noalloc(const stap_problem* probs, int32_t n_probs,
  * kernel), by stap_solve_weights and the stage path of stap_run (kind 1),
  * by stap_covariance and the stage path of stap_run (kind 2: waves per
  * system, 4, 8 or 16 where the DOF class offers them, every choice giving
- * the same covariance bit for bit) and by stap_inner_products and the
- * single-cube stap_run (kind 3: 1, 2 or 4 range tiles of 16 cells per wave
- * step, at most 2 on the split-BF16 form; the same output bit for bit).
+ * the same covariance bit for bit).  Kind 3 (range tiles per wave step of
+ * the inner products, 1, 2 or 4) is stored and has no effect: the kernel takes
+ * one tile, the fastest everywhere; every choice gave the same bits.
  * An entry applies to the shape class containing (dof, n_steer): dof classes
  * end at 16, 32, 48, 64, 96, 128, 160, 192 and steering classes at 16, 32, 64.
  * variant: 0 = built-in default;

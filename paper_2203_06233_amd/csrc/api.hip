@@ -102,8 +102,9 @@ stap_status hip_status(hipError_t e) { return e == hipSuccess ? STAP_OK : STAP_E
 // Kernel-variant table written by the autotuner: [kind][dof class][steer
 // class][precision][refine] -> variant (0 = built-in default).  Kind 0 is
 // the fused covariance -> solve of stap_run, kind 1 the stage weight solve,
-// kind 2 the stage covariance (waves per system), kind 3 the inner products
-// (range tiles per wave step).
+// kind 2 the stage covariance (waves per system); kind 3 (range tiles per wave
+// step of the inner products) is kept but no longer read, one tile being the
+// fastest everywhere.
 constexpr int kDofClass[] = {16, 32, 48, 64, 96, 128, 160, 192};
 constexpr int kSteerClass[] = {16, 32, 64};
 constexpr int kKinds = 4;
@@ -338,7 +339,7 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
         if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d));
         if (e == hipSuccess) e = stage_solve(d, cov, pd.steer, pd.w, pd.info, st);
       }
-      if (e == hipSuccess) e = stap::launch_inner(d, pd.w, pd.snap, pd.power, nullptr, st, tuned(3, d));
+      if (e == hipSuccess) e = stap::launch_inner(d, pd.w, pd.snap, pd.power, nullptr, st);
       if (e != hipSuccess) return STAP_ERR_HIP;
     }
     return STAP_OK;
@@ -423,7 +424,7 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
       if (e != hipSuccess) return e;
     }
     for (const Group& g : groups) {
-      const hipError_t e = stap::launch_inner_batched(table + g.lo, g.n, g.total, g.max_dof, g.max_steer, prec, s);
+      const hipError_t e = stap::launch_inner_batched(table + g.lo, g.n, g.total, g.max_dof, g.max_steer, s);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -531,7 +532,7 @@ stap_status stap_inner_products(const stap_problem* prob, const stap_cf32* w, co
   const Dims d = dims_of(prob);
   return hip_status(stap::launch_inner(d, reinterpret_cast<const float2*>(w),
                                        reinterpret_cast<const float2*>(snap), power,
-                                       reinterpret_cast<float2*>(y), (hipStream_t)stream, tuned(3, d)));
+                                       reinterpret_cast<float2*>(y), (hipStream_t)stream));
 }
 
 stap_status stap_cfar(const stap_problem* prob, const stap_cfar_params* cfar, const float* power, uint8_t* detect,

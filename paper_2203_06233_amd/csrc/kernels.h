@@ -45,7 +45,7 @@ hipError_t launch_fused_batched(const ProbDesc* desc, int n, long long total_sys
 
 // Inner products over every system of every cube of the table.
 hipError_t launch_inner_batched(const ProbDesc* desc, int n, long long total_sys, int max_dof, int max_steer,
-                                int prec, hipStream_t st);
+                                hipStream_t st);
 
 // X[P][D][R] <- windowed, time-staggered Doppler DFT of cube[C][P][R].
 hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipStream_t st);
@@ -85,9 +85,7 @@ hipError_t launch_fused32(const Dims& d, const float2* snap, const float2* steer
 hipError_t launch_cfar(const Dims& d, int n_ref, int n_guard, double alpha, const float* power,
                        unsigned char* detect, hipStream_t st);
 
-// power[P][S][R] (and y if non-null) from W and X; rtw = range tiles per
-// wave step (0 = default).
-hipError_t launch_inner(const Dims& d, const float2* w, const float2* snap, float* power, float2* y,
-                        hipStream_t st, int rtw = 0);
+// power[P][S][R] (and y if non-null) from W and X.
+hipError_t launch_inner(const Dims& d, const float2* w, const float2* snap, float* power, float2* y, hipStream_t st);
 
 }  // namespace stap
