@@ -58,6 +58,26 @@ __device__ __forceinline__ void back_solve(const Acc (&L)[NB * (NB + 1) / 2], Ac
   }
 }
 
+// Forward solve Y^H L^H = M with the factor in L (Linv_JJ on the diagonal):
+// M_J := M_J Linv_JJ^H, then M_K -= M_J L_KJ^H for K > J, block by block in
+// the order of the factorisation's own updates of M.
+template <int NB, int NS>
+__device__ __forceinline__ void forward_solve(const Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[NS * NB]) {
+#pragma unroll
+  for (int J = 0; J < NB; ++J) {
+#pragma unroll
+    for (int N = 0; N < NS; ++N) {
+      Acc x = acc_zero();
+      mma_pqh<false>(x, M[N * NB + J], L[tri(J, J)]);
+      M[N * NB + J] = x;
+    }
+#pragma unroll
+    for (int K = J + 1; K < NB; ++K)
+#pragma unroll
+      for (int N = 0; N < NS; ++N) mma_pqh<true>(M[N * NB + K], M[N * NB + J], L[tri(K, J)]);
+  }
+}
+
 // The trailing updates of factorisation step J other than the one of
 // diagonal block J+1, numbered 0..COUNT-1: first the L blocks (I, K),
 // K = J+1.., I = K.., then the M blocks (N, K).
@@ -153,75 +173,36 @@ struct WsLds {
   static constexpr int COMPLEX = SLOTS * kBlk / 2 + PIV;
 };
 
-// Solve one system: R is its loaded covariance, full Hermitian [D][D]
-// row-major, W its [S][D] weights, info its status word (may be null);
-// D <= 16 NB, S <= 16 NS.  lds points at WsLds<NB>::COMPLEX complex of
-// 16-byte aligned LDS.  Blocks beyond D carry the identity, steering rows
-// beyond S are zero.
+// M = V^H of steering rows 16 N0 .. on.
 template <int NB, int NS>
-__device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, const float2* __restrict__ steer,
-                                              float2* __restrict__ W, int* __restrict__ info, const Dims& d,
-                                              float2* lds) {
-  using LY = WsLds<NB>;
-  constexpr int NL = NB * (NB + 1) / 2;
-  const int D = d.D, S = d.S;
+__device__ __forceinline__ void load_m(const float2* __restrict__ steer, int N0, int D, int S, Acc (&M)[NS * NB]) {
   const int lane = lane_tid() & 63, m = lane & 15, q = lane >> 4;
-  float* tb = reinterpret_cast<float*>(lds);
-  const int nat = nat_ofs();
-  double* d64 = reinterpret_cast<double*>(tb + LY::SLOTS * kBlk);
-  float* rdiag = reinterpret_cast<float*>(d64 + 16 * NB);
-  for (int r = lane; r < 16 * NB; r += 64) d64[r] = 0.0;
-
-  Acc L[NL], M[NS * NB];
-#pragma unroll
-  for (int I = 0; I < NB; ++I) {
-#pragma unroll
-    for (int J = 0; J <= I; ++J) {
-      const int r = 16 * I + m;
-      Acc a;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = 16 * J + 4 * q + i;
-        const float2 v = (r < D && c < D) ? R[(long long)r * D + c] : make_float2(r == c ? 1.f : 0.f, 0.f);
-        a.re[i] = v.x;
-        a.im[i] = v.y;
-        if (I == J && c == r) rdiag[r] = v.x;
-      }
-      L[tri(I, J)] = a;
-    }
-  }
+  const bool vec = rows16(steer, D);
 #pragma unroll
   for (int N = 0; N < NS; ++N) {
 #pragma unroll
     for (int J = 0; J < NB; ++J) {
-      const int s = 16 * N + m;
+      const int s = 16 * (N0 + N) + m;
+      float2 v[4];
+      load4(steer, s, 16 * J + 4 * q, s < S, D, vec, v);
       Acc a;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int k = 16 * J + 4 * q + i;
-        const float2 v = (s < S && k < D) ? steer[s * D + k] : make_float2(0.f, 0.f);
-        a.re[i] = v.x;
-        a.im[i] = -v.y;
+        a.re[i] = v[i].x;
+        a.im[i] = -v[i].y;
       }
       M[N * NB + J] = a;
     }
   }
+}
 
-  // ---- factorisation with the forward solve of the steering rows
-  int fail = 0;
-  {
-    Acc X;
-    fail = diag_factor_inv<1>(L[0], X, (double)blk_diag(L[0]));
-    L[0] = X;
-  }
-  fact_step<NB, NS, 0>(L, M, fail, d64, rdiag);
-  if (fail) {
-    for (int e = lane; e < S * D; e += 64) W[e] = make_float2(0.f, 0.f);
-    if (lane == 0 && info) *info = fail;
-    return;
-  }
-
-  // ---- gamma_s = ||y_s||^2, summed over the row's blocks
+// From Y^H in M to the weights of steering rows 16 N0 .. on: gamma_s =
+// ||y_s||^2 summed over the row's blocks, back solve, w_s = u_s /
+// sqrt(gamma_s) with u_s = conj(z_s).
+template <int NB, int NS>
+__device__ __forceinline__ void finish_m(const Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[NS * NB], int N0,
+                                         float2* __restrict__ W, int D, int S, float* tb, int nat) {
+  const int lane = lane_tid() & 63, m = lane & 15, q = lane >> 4;
   double gam[NS];
 #pragma unroll
   for (int N = 0; N < NS; ++N) {
@@ -237,24 +218,87 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
       gam[N] += p;
     }
   }
-
-  back_solve<NB, NS, LY::SLOTS>(L, M, tb, nat);
-
-  // ---- w_s = u_s / sqrt(gamma_s), u_s = conj(z_s)
+  back_solve<NB, NS, WsLds<NB>::SLOTS>(L, M, tb, nat);
+  const bool vec = rows16(W, D);
 #pragma unroll
   for (int N = 0; N < NS; ++N) {
-    const int s = 16 * N + m;
+    const int s = 16 * (N0 + N) + m;
     const float sc = 1.f / sqrtf((float)gam[N]);
-    if (s < S) {
 #pragma unroll
-      for (int J = 0; J < NB; ++J) {
+    for (int J = 0; J < NB; ++J) {
+      float2 w[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = 16 * J + 4 * q + i;
-          if (k < D) W[s * D + k] = make_float2(M[N * NB + J].re[i] * sc, -M[N * NB + J].im[i] * sc);
-        }
-      }
+      for (int i = 0; i < 4; ++i) w[i] = make_float2(M[N * NB + J].re[i] * sc, -M[N * NB + J].im[i] * sc);
+      store4(W, s, 16 * J + 4 * q, s < S, D, vec, w);
     }
+  }
+}
+
+// Steering blocks in registers at a time: with 6 block columns two of them
+// (264 registers with L) leave one wave on a SIMD, which waits out every
+// dependency; one fits two waves.
+constexpr int steer_group(int NB, int NS) { return NB >= 5 ? 1 : NS; }
+
+// Solve one system: R is its loaded covariance, full Hermitian [D][D]
+// row-major, W its [S][D] weights, info its status word (may be null);
+// D <= 16 NB, S <= 16 NS.  lds points at WsLds<NB>::COMPLEX complex of
+// 16-byte aligned LDS.  Blocks beyond D carry the identity, steering rows
+// beyond S are zero.  The first group of steering blocks rides along with the
+// factorisation, the others take their forward solve from the stored factor.
+template <int NB, int NS>
+__device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, const float2* __restrict__ steer,
+                                              float2* __restrict__ W, int* __restrict__ info, const Dims& d,
+                                              float2* lds) {
+  constexpr int NL = NB * (NB + 1) / 2, G = steer_group(NB, NS);
+  const int D = d.D, S = d.S;
+  const int lane = lane_tid() & 63, m = lane & 15, q = lane >> 4;
+  float* tb = reinterpret_cast<float*>(lds);
+  const int nat = nat_ofs();
+  double* d64 = reinterpret_cast<double*>(tb + WsLds<NB>::SLOTS * kBlk);
+  float* rdiag = reinterpret_cast<float*>(d64 + 16 * NB);
+  for (int r = lane; r < 16 * NB; r += 64) d64[r] = 0.0;
+
+  Acc L[NL], M[G * NB];
+  const bool vec = rows16(R, D);
+#pragma unroll
+  for (int I = 0; I < NB; ++I) {
+#pragma unroll
+    for (int J = 0; J <= I; ++J) {
+      const int r = 16 * I + m;
+      Acc a;
+      float2 v[4];
+      load4(R, r, 16 * J + 4 * q, r < D, D, vec, v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = 16 * J + 4 * q + i;
+        a.re[i] = I == J && r >= D && c == r ? 1.f : v[i].x;
+        a.im[i] = v[i].y;
+        if (I == J && c == r) rdiag[r] = a.re[i];
+      }
+      L[tri(I, J)] = a;
+    }
+  }
+  load_m<NB, G>(steer, 0, D, S, M);
+
+  // ---- factorisation with the forward solve of the first steering rows
+  int fail = 0;
+  {
+    Acc X;
+    fail = diag_factor_inv<1>(L[0], X, (double)blk_diag(L[0]));
+    L[0] = X;
+  }
+  fact_step<NB, G, 0>(L, M, fail, d64, rdiag);
+  if (fail) {
+    for (int e = lane; e < S * D; e += 64) W[e] = make_float2(0.f, 0.f);
+    if (lane == 0 && info) *info = fail;
+    return;
+  }
+  finish_m<NB, G>(L, M, 0, W, D, S, tb, nat);
+#pragma unroll 1
+  for (int N0 = G; 16 * N0 < S; N0 += G) {
+    load_m<NB, G>(steer, N0, D, S, M);
+    forward_solve<NB, G>(L, M);
+    finish_m<NB, G>(L, M, N0, W, D, S, tb, nat);
   }
   if (lane == 0 && info) *info = 0;
 }

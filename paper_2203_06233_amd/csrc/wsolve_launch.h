@@ -8,8 +8,16 @@
 namespace stap {
 namespace wsv {
 
+// Waves per SIMD that the blocks of a system leave registers for: eight a
+// block and about 60 to work with.
+constexpr int wsolve_waves(int NB, int NS) {
+  const int blocks = NB * (NB + 1) / 2 + steer_group(NB, NS) * NB;
+  return blocks <= 8 ? 4 : blocks <= 13 ? 3 : 2;
+}
+
 template <int NB, int NS>
-__global__ __launch_bounds__(64) void wsolve_kernel(const float2* __restrict__ cov, const float2* __restrict__ steer,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(wsolve_waves(NB, NS))))
+void wsolve_kernel(const float2* __restrict__ cov, const float2* __restrict__ steer,
                                                     float2* __restrict__ wout, int* __restrict__ info_out, Dims d) {
   __shared__ __align__(16) float2 lds[WsLds<NB>::COMPLEX];
   const int sys = blockIdx.x;

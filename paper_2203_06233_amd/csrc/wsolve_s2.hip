@@ -1,5 +1,4 @@
 // One-wave stage solve, steering class 2 (S <= 32).
-#define STAP_TID_DIRECT
 #include "wsolve_launch.h"
 
 namespace stap {
