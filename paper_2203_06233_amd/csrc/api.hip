@@ -331,12 +331,12 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
       wsp += p.total();
       hipError_t e = stap::launch_doppler(d, pd.cube, pd.snap, st);
       if (one_wave_route(d)) {
-        if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d));
+        if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d), false);
         if (e == hipSuccess) e = stap::launch_wsolve(d, cov, pd.steer, pd.w, pd.info, st);
       } else if (stap::fused_supported(d)) {
         if (e == hipSuccess) e = stap::launch_fused(d, pd.snap, pd.steer, pd.w, pd.info, st, fused_variant(d));
       } else {
-        if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d));
+        if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d), false);
         if (e == hipSuccess) e = stage_solve(d, cov, pd.steer, pd.w, pd.info, st);
       }
       if (e == hipSuccess) e = stap::launch_inner(d, pd.w, pd.snap, pd.power, nullptr, st);
@@ -496,7 +496,7 @@ stap_status stap_covariance(const stap_problem* prob, const stap_cf32* snap, sta
   const Dims d = dims_of(prob);
   return hip_status(stap::launch_covariance(d, reinterpret_cast<const float2*>(snap),
                                             reinterpret_cast<float2*>(cov), delta, (hipStream_t)stream,
-                                            tuned(2, d)));
+                                            tuned(2, d), true));
 }
 
 stap_status stap_solve_weights(const stap_problem* prob, const stap_cf32* cov, const stap_cf32* steer,

@@ -50,10 +50,11 @@ hipError_t launch_inner_batched(const ProbDesc* desc, int n, long long total_sys
 // X[P][D][R] <- windowed, time-staggered Doppler DFT of cube[C][P][R].
 hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipStream_t st);
 
-// cov[P][B][D][D] (loaded, full Hermitian) and delta[P][B] from X; nw =
-// waves per system (0 = default of the DOF class).
+// cov[P][B][D][D] (loaded, Hermitian) and delta[P][B] from X; nw = waves per
+// system (0 = default of the DOF class); without `full` the 16 x 16 blocks
+// above the diagonal are not written.
 hipError_t launch_covariance(const Dims& d, const float2* snap, float2* cov, float* delta,
-                             hipStream_t st, int nw = 0);
+                             hipStream_t st, int nw, bool full);
 
 // W[P][B][S][D] and info[P][B] from loaded covariances and steering V[S][D].
 hipError_t launch_solve(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info,
