@@ -152,7 +152,6 @@ struct OpF32 {
   static __device__ __forceinline__ Frag frag(const Acc& a) { return a; }
   static __device__ __forceinline__ Frag load(const float* blk, int nat) { return blk_load(blk, nat); }
   static __device__ __forceinline__ void store(float* blk, const Frag& f, int nat) { blk_store(blk, f, nat); }
-  static __device__ __forceinline__ void store_t(float* blk, const Acc& a, int) { blk_store_t(blk, a); }
   static __device__ __forceinline__ void pqh(Acc& x, const Frag& P, const Frag& Q) { mma_pqh<false>(x, P, Q); }
   static __device__ __forceinline__ void pq(Acc& x, const Frag& P, const Frag& Qt) { mma_pq<false>(x, P, Qt); }
 };
@@ -178,11 +177,6 @@ struct OpSplit {
   static __device__ __forceinline__ void store(float* blk, const Frag& f, int nat) {
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(blk + 256 * p + nat) = f.t[p];
-  }
-  // transposed in FP32 through the block's own place, then split
-  static __device__ __forceinline__ void store_t(float* blk, const Acc& a, int nat) {
-    blk_store_t(blk, a);
-    store(blk, frag(blk_load(blk, nat)), nat);
   }
   static __device__ __forceinline__ unsigned int neg2(unsigned int u) { return u ^ 0x80008000u; }
   static __device__ __forceinline__ floatx4 mm(const uint4& a, const uint4& b, floatx4 c) {
@@ -446,15 +440,25 @@ struct BCfg {
   // L and M slots per wave a (NB, NS) system needs
   __host__ __device__ static constexpr int lslots(int NB) { return (NB * (NB + 1) / 2 + NW - 1) / NW; }
   __host__ __device__ static constexpr int mslots(int NB, int NS) { return (NS * NB + NW - 1) / NW; }
-  // LDS: exchange blocks (NB + NS + 1 for the factorisation and solves; with
-  // refinement, all NS NB blocks of Z in FP32 for the residual), the gamma
+  // Whether the blocks of L that the solves multiply by are split by their
+  // owner, once, or by each of their users.  By the users the split is off
+  // the path between two barriers; from three M blocks per wave on its
+  // repetition costs more than that (256 bins x 64 blocks: 192 DOF, 48
+  // steering vectors 21.99 ms per pass split by the users, 21.49 by the
+  // owner; 96 DOF, 64 vectors, 128 x 32 systems 1078 and 1035 us; 96 DOF, 16
+  // vectors 7.13 and 7.30 ms).
+  static constexpr bool kOwnerSplits = NSM > 2;
+  // LDS: exchange blocks (NB + NS + 1 for the factorisation; two times NB
+  // blocks of L and NS for the solves; with refinement, all NS NB blocks
+  // of Z in FP32 for the residual), the gamma
   // partials [NB][16 NS] (FP64), a flag, the FP64 row sums of |L|^2 over the
   // finished block columns [16 NB] and the loaded diagonal [16 NB] (for the
   // FP64 pivots)
   __host__ __device__ static constexpr size_t xbytes(int NB, int NS, bool refine) {
-    const size_t x = (size_t)(NB + NS + 1) * (refine ? OpSplit::kB : OpF32::kB) * 4;
+    const size_t kB = refine ? OpSplit::kB : OpF32::kB;
+    const size_t f = (NB + NS + 1) * kB * 4, s = (2 * NB * (kOwnerSplits ? kB : kBlk) + NS * kB) * 4;
     const size_t z = refine ? (size_t)NS * NB * kBlk * 4 : 0;
-    return x > z ? x : z;
+    return f > s ? (f > z ? f : z) : (s > z ? s : z);
   }
   __host__ __device__ static constexpr size_t lds_bytes(int NB, int NS, bool refine) {
     return xbytes(NB, NS, refine) + (size_t)NB * 16 * NS * 8 + 16 + (size_t)NB * 16 * (8 + 4);
@@ -709,35 +713,82 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
     }
   }
 
-  // ---- back solve, row form Z L = Y^H (M holds Y^H on entry, Z on exit)
+  // ---- triangular solves with the stored factor.  The blocks of L that a
+  // step multiplies by pass through LDS, two steps' worth in turn: a step's
+  // products run while the owners put the next step's blocks into the other
+  // half, so a step has two barriers.
+  constexpr bool kOwner = C::kOwnerSplits && kB != kBlk;
+  constexpr int kL = kOwner ? kB : kBlk;
+  float* const zb = xb + (size_t)2 * NB * kL;
+  auto half = [&](int J, int I) { return xb + (size_t)((J & 1) * NB + I) * kL; };
+  auto l_frag = [&](int J, int I) { return kOwner ? Op::load(half(J, I), nat) : Op::frag(blk_load(half(J, I), nat)); };
+  // Back solve, row form Z L = Y^H (M holds Y^H on entry, Z on exit).
   auto back_solve = [&]() {
-    float* zb = xb + (size_t)NB * kB;
+    auto publish = [&](int J) {  // L_JI^T at I (-Linv_JJ^T at I = J)
+#pragma unroll
+      for (int t = 0; t < NSL; ++t)
+        if (sl.lv[t] && sl.lr[t] == J) {
+          float* const b = half(J, sl.lc[t]);
+          blk_store_t(b, al[t]);
+          if (kOwner) Op::store(b, Op::frag(blk_load(b, nat)), nat);
+        }
+    };
 #pragma unroll
     for (int t = 0; t < NSM; ++t) am[t] = acc_neg(am[t]);
+    __syncthreads();  // earlier readers of the exchange blocks are done
+    publish(NB - 1);
     for (int J = NB - 1; J >= 0; --J) {
-      __syncthreads();  // previous readers of the exchange blocks are done
-#pragma unroll
-      for (int t = 0; t < NSL; ++t)  // L_JI^T (-Linv_JJ^T at I = J)
-        if (sl.lv[t] && sl.lr[t] == J) {
-          pin(al[t]);
-          Op::store_t(xb + sl.lc[t] * kB, al[t], nat);
-        }
-      __syncthreads();
+      __syncthreads();  // row J is there; the updates of step J + 1 are done
 #pragma unroll
       for (int t = 0; t < NSM; ++t) {
         if (sl.mv[t] && sl.mc[t] == J) {
           Acc x = acc_zero();
-          Op::pq(x, Op::frag(am[t]), Op::load(xb + J * kB, nat));
+          Op::pq(x, Op::frag(am[t]), l_frag(J, J));
           am[t] = x;
           if (J > 0) Op::store(zb + sl.mr[t] * kB, Op::frag(x), nat);
         }
       }
       if (J > 0) {
+        publish(J - 1);
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < NSM; ++t)
           if (sl.mv[t] && sl.mc[t] < J)
-            Op::pq(am[t], Op::load(zb + sl.mr[t] * kB, nat), Op::load(xb + sl.mc[t] * kB, nat));
+            Op::pq(am[t], Op::load(zb + sl.mr[t] * kB, nat), l_frag(J, sl.mc[t]));
+      }
+    }
+  };
+  // Forward solve Y^H L^H = M (M negated on entry, Y^H on exit).
+  auto forward_solve = [&]() {
+    auto publish = [&](int J) {  // column J of L (-Linv_JJ at the diagonal)
+#pragma unroll
+      for (int t = 0; t < NSL; ++t)
+        if (sl.lv[t] && sl.lc[t] == J) {
+          pin(al[t]);
+          if (kOwner) Op::store(half(J, sl.lr[t]), Op::frag(al[t]), nat);
+          else blk_store(half(J, sl.lr[t]), al[t], nat);
+        }
+    };
+    __syncthreads();
+    publish(0);
+    for (int J = 0; J < NB; ++J) {
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NSM; ++t) {
+        if (sl.mv[t] && sl.mc[t] == J) {
+          Acc x = acc_zero();
+          Op::pqh(x, Op::frag(am[t]), l_frag(J, J));
+          am[t] = x;
+          if (J + 1 < NB) Op::store(zb + sl.mr[t] * kB, Op::frag(x), nat);
+        }
+      }
+      if (J + 1 < NB) {
+        publish(J + 1);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NSM; ++t)
+          if (sl.mv[t] && sl.mc[t] > J)
+            Op::pqh(am[t], Op::load(zb + sl.mr[t] * kB, nat), l_frag(J, sl.mc[t]));
       }
     }
   };
@@ -822,33 +873,7 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
           if (lds_park) blk_store(tb, blk_load(zb, nat), nat);
         }
       }
-      // forward solve Y^H L^H = r^H with the stored factor
-      for (int J = 0; J < NB; ++J) {
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < NSL; ++t)  // column J of L (-Linv_JJ at the diagonal)
-          if (sl.lv[t] && sl.lc[t] == J) {
-            pin(al[t]);
-            Op::store(xb + sl.lr[t] * kB, Op::frag(al[t]), nat);
-          }
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < NSM; ++t) {
-          if (sl.mv[t] && sl.mc[t] == J) {
-            Acc x = acc_zero();
-            Op::pqh(x, Op::frag(am[t]), Op::load(xb + J * kB, nat));
-            am[t] = x;
-            if (J + 1 < NB) Op::store(xb + (NB + sl.mr[t]) * kB, Op::frag(x), nat);
-          }
-        }
-        if (J + 1 < NB) {
-          __syncthreads();
-#pragma unroll
-          for (int t = 0; t < NSM; ++t)
-            if (sl.mv[t] && sl.mc[t] > J)
-              Op::pqh(am[t], Op::load(xb + (NB + sl.mr[t]) * kB, nat), Op::load(xb + sl.mc[t] * kB, nat));
-        }
-      }
+      forward_solve();  // Y^H L^H = r^H
       back_solve();
       // Z += the correction (u kept in W or park)
 #pragma unroll
