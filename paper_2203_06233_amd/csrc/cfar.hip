@@ -27,9 +27,14 @@
 // windows start at kRun times the thread index and once for the right ones,
 // with a pad word every kRun: a window's m-th value then sits at a constant
 // distance from the thread's base (no address arithmetic per read) and the
-// lanes' reads fall in distinct banks.  256 x 32 x 16384 cells with 16
-// reference cells a side: 334 us with the ordered sums throughout, 261 so
-// (2.6 TB/s of 4 bytes in and 1 out per cell).
+// lanes' reads fall in distinct banks.  (Four pad words and 16-byte reads take
+// half as much LDS again, two workgroups fewer per CU: 315 us against 261.)
+// A tile's loads are issued together, at clamped addresses: behind a bounds
+// check each is waited for by itself (250 us with that, all else as here).
+// 256 x 32 x 16384 cells with 16 reference cells a side: 334 us with the
+// ordered sums throughout, 161 so (4.2 TB/s of 4 bytes in and 1 out per
+// cell); what is left is arithmetic that overlaps the loads of other
+// workgroups only in part.
 #include "common.h"
 #include "kernels.h"
 
@@ -68,30 +73,22 @@ __device__ __forceinline__ void window_sums(const float* s, int base, int n, dou
 }
 
 // The same sums in any order and in FP32, n >= kRun, w[m] at a[lds_index(m)]
-// (a the thread's base).  The sign bit of `sign` is set if any value has it.
-__device__ __forceinline__ void window_sums_any(const float* a, int n, float (&acc)[kRun], unsigned int& sign) {
-  auto take = [&](float v) {
-    sign |= __float_as_uint(v);
-    return v;
-  };
+// (a the thread's base).
+__device__ __forceinline__ void window_sums_any(const float* a, int n, float (&acc)[kRun]) {
   float suf[kRun];
   suf[kRun - 1] = 0.f;
 #pragma unroll
-  for (int m = kRun - 2; m >= 0; --m) suf[m] = suf[m + 1] + take(a[m]);
-  float mid = take(a[kRun - 1]);
+  for (int m = kRun - 2; m >= 0; --m) suf[m] = suf[m + 1] + a[m];
+  float mid = a[kRun - 1];
   const float* p = a + kRun + 1;
   int m = kRun;
-  for (; m + kRun <= n; m += kRun, p += kRun + 1) {
-    float w[kRun];
-#pragma unroll
-    for (int i = 0; i < kRun; ++i) w[i] = take(p[i]);
-    mid += ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
-  }
-  for (int i = 0; m + i < n; ++i) mid += take(p[i]);
+  for (; m + kRun <= n; m += kRun, p += kRun + 1)
+    mid += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+  for (int i = 0; m + i < n; ++i) mid += p[i];
 #pragma unroll
   for (int j = 0; j < kRun; ++j) {
     acc[j] += suf[j] + mid;
-    if (j + 1 < kRun) mid += take(a[lds_index(n + j)]);
+    if (j + 1 < kRun) mid += a[lds_index(n + j)];
   }
 }
 
@@ -100,6 +97,7 @@ __global__ __launch_bounds__(kThreads) void cfar_kernel(const float* __restrict_
                                                         int n_ref, int n_guard, double alpha) {
 #pragma clang fp contract(off)
   __shared__ float sl[kLeftWords], sr[kRightWords];
+  __shared__ int negative[kThreads / 64];
   const int row = blockIdx.x / tiles_per_row;
   const int tile = blockIdx.x - row * tiles_per_row;
   const int t0 = tile * kTile;          // first cell of the tile
@@ -108,19 +106,51 @@ __global__ __launch_bounds__(kThreads) void cfar_kernel(const float* __restrict_
   // stage cells t0 - H .. t0 + kTile + H - 1 (zero outside the row), plus
   // kRun zeros of look-ahead
   const int nl = kTile + H + kRun, off = H + n_guard + 1, span = kTile + 2 * H;
-  for (int i = threadIdx.x; i < span + kRun; i += kThreads) {
-    const int c = t0 - H + i;
-    const float v = (i < span && c >= 0 && c < R) ? prow[c] : 0.f;
-    if (i < nl) sl[lds_index(i)] = v;
-    if (i >= off) sr[lds_index(i - off)] = v;
+  const bool inside = t0 >= H && t0 + kTile + H <= R;
+  // staged value i is cell t0 - H + i; first and last of them in the row
+  const float* const p0 = prow + (t0 - H);
+  const int first = max(H - t0, 0), last = min(span, R - t0 + H) - 1;
+  unsigned int sign = 0;  // the sign bit is set if any value has it
+  float v[kRun + 1];      // the tile's loads at once: none behind a branch
+#pragma unroll
+  for (int u = 0; u <= kRun; ++u) v[u] = p0[(unsigned)min(max((int)threadIdx.x + u * kThreads, first), last)];
+#pragma unroll
+  for (int u = 0; u <= kRun; ++u) asm volatile("" : "+v"(v[u]));
+  if (!inside) {
+#pragma unroll
+    for (int u = 0; u <= kRun; ++u) {
+      const int i = threadIdx.x + u * kThreads;
+      if (i < first || i > last) v[u] = 0.f;
+    }
   }
+#pragma unroll
+  for (int u = 0; u <= kRun; ++u) sign |= __float_as_uint(v[u]);
+  // lds_index(i + u kThreads) = lds_index(i) + u kStep; from u = 1 on every
+  // value belongs to both copies, up to the tile's last cell to the left one
+  constexpr int kStep = lds_index(kThreads);
+  static_assert(kThreads % 8 == 0 && kThreads > 2 * kMaxCfarGuard + kMaxCfarRef, "");
+  float* const pl = sl + lds_index(threadIdx.x);
+  const int ir = lds_index((int)threadIdx.x - off);
+  if ((int)threadIdx.x >= off) sr[ir] = v[0];
+#pragma unroll
+  for (int u = 0; u < kRun; ++u) {
+    pl[u * kStep] = v[u];
+    if (u > 0) sr[ir + u * kStep] = v[u];
+  }
+  for (int i = threadIdx.x + kTile; i < span + kRun; i += kThreads) {
+    const float x = i < kTile + kThreads ? v[kRun] : i <= last ? p0[i] : 0.f;
+    sign |= __float_as_uint(x);
+    if (i < nl) sl[lds_index(i)] = x;
+    sr[lds_index(i - off)] = x;
+  }
+  const bool neg = __any(sign >> 31);
+  if ((threadIdx.x & 63) == 0) negative[threadIdx.x >> 6] = neg;
   __syncthreads();
 
   const int base = kRun * threadIdx.x, c0 = t0 + base;  // the thread's first cell
   if (c0 >= R) return;
   // Reference cells of cell j that exist: left [c-g-n, c-g-1] and right
   // [c+g+1, c+g+n]; all of them away from the ends of the row.
-  const bool inside = t0 >= H && t0 + kTile + H <= R;
   auto used = [&](int j) {
     if (inside) return 2 * n_ref;
     const int c = c0 + j;
@@ -130,31 +160,38 @@ __global__ __launch_bounds__(kThreads) void cfar_kernel(const float* __restrict_
   };
   unsigned int lo = 0, hi = 0;  // the mask bytes of cells 0-3 and 4-7
   auto put = [&](int j, bool hit) {
-    const unsigned int b = c0 + j < R && hit ? 1u << (8 * (j & 3)) : 0u;
+    const unsigned int b = hit ? 1u << (8 * (j & 3)) : 0u;
     if (j < 4) lo |= b;
     else hi |= b;
   };
   const float al = (float)alpha;
   bool settled = n_ref >= kRun && al > 0x1p-60f && al < 0x1p60f;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) settled = settled && !negative[w];
   if (settled) {
-    float acc[kRun];
+    float acc[kRun], top = 0.f;
 #pragma unroll
     for (int j = 0; j < kRun; ++j) acc[j] = 0.f;
-    unsigned int sign = 0;
-    window_sums_any(sl + lds_index(base), n_ref, acc, sign);
-    window_sums_any(sr + lds_index(base), n_ref, acc, sign);
-    settled = !(sign >> 31);
+    window_sums_any(sl + lds_index(base), n_ref, acc);
+    window_sums_any(sr + lds_index(base), n_ref, acc);
+    // A cell is settled if its distance from the threshold exceeds the margin
+    // (2^-100 more where products lose bits): false for a NaN on either side
+    // and for an infinite sum.  An infinite threshold product is above any
+    // cell below 2^120.  A zero sum of values that are not negative is zero
+    // in any order.
+    const float almargin = al * kMargin;
+    bool clear = true, clear_or_zero = true;
 #pragma unroll
     for (int j = 0; j < kRun; ++j) {
-      const float lhs = sl[lds_index(base + H + j)] * (float)used(j), rhs = al * acc[j];
-      const float gap = fabsf(lhs - rhs);
-      // false for a NaN or an infinity on either side and for a threshold
-      // where FP32 loses bits; a zero sum of values that are not negative is
-      // zero in any order
-      settled = settled && gap < 0x1p120f && rhs < 0x1p120f &&
-                ((gap > kMargin * rhs && rhs > 0x1p-100f) || acc[j] == 0.f);
-      put(j, lhs > rhs);
+      const float p = sl[lds_index(base + H + j)];
+      const float gap = fmaf(-al, acc[j], p * (float)used(j));
+      const bool ok = fabsf(gap) > fmaf(almargin, acc[j], 0x1p-100f);
+      top = fmaxf(top, p);
+      clear = clear && ok;
+      clear_or_zero = clear_or_zero && (ok || acc[j] == 0.f);
+      put(j, gap > 0.f);
     }
+    settled = top < 0x1p120f && (clear || clear_or_zero);
   }
   if (!settled) {
     lo = hi = 0;
