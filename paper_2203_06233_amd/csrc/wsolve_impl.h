@@ -173,18 +173,47 @@ struct WsLds {
   static constexpr int COMPLEX = SLOTS * kBlk / 2 + PIV;
 };
 
+// Elements k .. k+3 of row s of a [rows][D] array, zero outside it; TAIL if
+// columns from D on can be among them.  The loads are at clamped indices and
+// behind no branch, so those of all blocks are in flight together (a bounds
+// check around each costs a memory latency per block: the 16 x 128 x 4096
+// cube, 48 DOF, 274 us per pass with those, 262 without; 96 DOF, 32768
+// systems, 5.24 and 5.06-5.20 ms).
+template <bool TAIL>
+__device__ __forceinline__ void load_row4(const float2* __restrict__ base, int s, int k, int rows, int D, float2 (&v)[4]) {
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
+  const bool row_ok = s < rows;
+  const float2* const p = base + min(s, rows - 1) * D;
+  if (TAIL) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = p[min(k + i, D - 1)];
+  } else {
+    const f4 a = *reinterpret_cast<const f4*>(p + k), b = *reinterpret_cast<const f4*>(p + k + 2);
+    v[0] = make_float2(a.x, a.y);
+    v[1] = make_float2(a.z, a.w);
+    v[2] = make_float2(b.x, b.y);
+    v[3] = make_float2(b.z, b.w);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool ok = row_ok & (!TAIL | (k + i < D));
+    v[i].x = ok ? v[i].x : 0.f;
+    v[i].y = ok ? v[i].y : 0.f;
+  }
+}
+
 // M = V^H of steering rows 16 N0 .. on.
 template <int NB, int NS>
 __device__ __forceinline__ void load_m(const float2* __restrict__ steer, int N0, int D, int S, Acc (&M)[NS * NB]) {
   const int lane = lane_tid() & 63, m = lane & 15, q = lane >> 4;
-  const bool vec = rows16(steer, D);
 #pragma unroll
   for (int N = 0; N < NS; ++N) {
 #pragma unroll
     for (int J = 0; J < NB; ++J) {
       const int s = 16 * (N0 + N) + m;
       float2 v[4];
-      load4(steer, s, 16 * J + 4 * q, s < S, D, vec, v);
+      if (J == NB - 1) load_row4<true>(steer, s, 16 * J + 4 * q, S, D, v);
+      else load_row4<false>(steer, s, 16 * J + 4 * q, S, D, v);
       Acc a;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -259,7 +288,6 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
   for (int r = lane; r < 16 * NB; r += 64) d64[r] = 0.0;
 
   Acc L[NL], M[G * NB];
-  const bool vec = rows16(R, D);
 #pragma unroll
   for (int I = 0; I < NB; ++I) {
 #pragma unroll
@@ -267,7 +295,8 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
       const int r = 16 * I + m;
       Acc a;
       float2 v[4];
-      load4(R, r, 16 * J + 4 * q, r < D, D, vec, v);
+      if (J == NB - 1) load_row4<true>(R, r, 16 * J + 4 * q, D, D, v);
+      else load_row4<false>(R, r, 16 * J + 4 * q, D, D, v);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int c = 16 * J + 4 * q + i;
