@@ -87,7 +87,8 @@ typedef enum stap_precision {
   STAP_PREC_FP32 = 0,
   /* Mixed: covariance and inner products as BF16 MFMA products with FP32
    * accumulation (each FP32 operand split exactly into three BF16 terms),
-   * FP32 Cholesky/solves, FP64 refinement residual. */
+   * FP32 Cholesky/solves (with refinement their products split in the same
+   * way), FP64 refinement residual. */
   STAP_PREC_BF16 = 1,
   /* As BF16 but the covariance is one FP8 (OCP E4M3) product per element
    * with a power-of-two scale per (bin, block) and FP32 accumulation. */
@@ -292,14 +293,18 @@ stap_status stap_run_noalloc(const stap_problem* probs, int32_t n_probs,
  * variant: 0 = built-in default;
  *          16 or 32 = column-sweep solve with 16 or 32 rows per register
  *                     slot (a 16 x 16 or 32 x 16 thread grid per system);
- *          4 or 8   = blocked solve on the FP32 matrix cores with 4 or 8
- *                     waves per system (8 runs D > 128 on 16 waves);
+ *          4 or 8   = blocked solve on the matrix cores (FP32; with
+ *                     refinement each FP32 operand split exactly into three
+ *                     BF16 terms) with up to 4 or 8 waves per system, fewer
+ *                     for few blocks (8 runs D > 128 on 16 waves);
  *          1        = one wave per system with every block of the solve in
- *                     its registers (D <= 96, S <= 32): the stage solve
- *                     (kind 1), and for kind 0 a route of single-cube
- *                     stap_run calls through the stage covariance and that
- *                     solve (stap_covariance_solve then takes variant 8).
- *          Requests a variant does not cover take the default. 
+ *                     its registers (D <= 96, S <= 32, no refinement): the
+ *                     stage solve (kind 1), and for kind 0 a route of
+ *                     single-cube stap_run calls through the stage covariance
+ *                     and that solve (stap_covariance_solve, and stap_run
+ *                     with refinement, then take variant 8).
+ *          Requests a variant does not cover take the default: the blocked
+ *          solve with refinement, else the column sweep.
  * Not thread-safe with respect to concurrent stap_run calls.  Returns
  * STAP_ERR_ARG for values out of range. */
 stap_status stap_tune_set(int32_t kind, int32_t dof, int32_t n_steer, int32_t precision, int32_t refine,

@@ -1,17 +1,17 @@
 // Blocked Cholesky solve of one system inside one wave, every block held in
 // that wave's registers for the whole solve (up to NB = 6 block columns of
-// R_L and NS = 2 blocks of steering vectors: D <= 96, S <= 32).
+// R_L and NS = 2 blocks of steering vectors: D <= 96, S <= 32), without
+// refinement.
 //
 // The steps and the block algebra are those of bsolve_system()
 // (bsolve_impl.h): right-looking factorisation with the in-wave diagonal
 // factor-and-invert, the forward solve of the steering rows M = V^H riding
-// along as extra rows, the back solve in row form Z L = Y^H, and the FP64
-// refinement residual conj(r) = conj(v) - Z R_L.  What differs is the
-// placement: with the block coordinates known at compile time every loop is
+// along as extra rows, and the back solve in row form Z L = Y^H.  What
+// differs is the placement: with the block coordinates known at compile time every loop is
 // unrolled, the operands of a block product are read straight from the
 // registers of the blocks they come from (no exchange through LDS and no
 // barrier), and the only LDS traffic is the transposition of the L blocks a
-// back-solve step multiplies by (and the reordering of a residual block).
+// back-solve step multiplies by.
 // One wave per system leaves the four SIMDs of a compute unit on four
 // systems at once; the instruction stream of the wave interleaves the
 // serial diagonal work with the matrix-core products of the same step.

@@ -8,8 +8,9 @@ followed by the one-wave solve), keeps the fastest by HIP-event time, and
 stores the choice in a JSON cache keyed by GPU architecture, kernel kind,
 DOF class, steering class, precision and refinement.  It then times the
 stage covariance kernel under each wave count per system and the inner
-products under each number of range tiles per wave step (kinds "cov" and
-"inner"), which must reproduce the default bit for bit.  The binding applies the cache
+products under each stored number of range tiles per wave step (kinds "cov"
+and "inner"; the latter no longer has an effect), which must reproduce the
+default bit for bit.  The binding applies the cache
 (``tune_cache.json`` beside this file, or ``$STAP_TUNE_CACHE``) at import.
 
     python -m paper_2203_06233_amd.tune [--workload large] [--reps 10]
