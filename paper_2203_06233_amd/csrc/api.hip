@@ -394,13 +394,15 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
       Dop x;
       x.P = P;
       x.sub = false;
+      bool one_tap = true;
       long long wide_tiles = 0;
       for (int j = 0; j < n; ++j) {
         const Dims& d = desc[at[first + j]].d;
         x.sub = x.sub || d.sub > 1;
+        one_tap = one_tap && d.T == 1;
         wide_tiles += stap::doppler_tiles(d, true);
       }
-      x.wide = stap::doppler_wide(P, x.sub, wide_tiles);
+      x.wide = stap::doppler_wide(P, x.sub, one_tap, wide_tiles);
       x.bi.n = n;
       int tiles = 0;
       for (int j = 0; j < n; ++j) {

@@ -240,9 +240,13 @@ int doppler_tiles(const Dims& d, bool wide) {
 }
 
 // Wide tiles where their workgroups give every compute unit 16 waves; with
-// subarrays only the 100-pulse shape has one.
-bool doppler_wide(int P, bool sub, long long wide_tiles) {
-  if (P == 32 || (sub && P != 100)) return false;
+// subarrays only the 100-pulse shape has one.  With a single tap a tile's
+// loads and stores take equally long, and a compute unit that holds one wide
+// workgroup does them in turn: at 64, 256 and 512 pulses narrow tiles are as
+// fast or faster then (32 channels, 4096 cells: 25, 100 and 214 us against
+// 28, 108 and 236), at 128 and 100 not (48 and 50 against 46 and 47).
+bool doppler_wide(int P, bool sub, bool one_tap, long long wide_tiles) {
+  if (P == 32 || (sub && P != 100) || (one_tap && P != 128 && P != 100)) return false;
   return by_pulse(P, [&](auto p) { return wide_tiles * FftShape<p.value, true>::NT >= 256LL * 1024; });
 }
 
@@ -262,7 +266,7 @@ hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex&
 }
 
 hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipStream_t st) {
-  const bool sub = d.sub > 1, wide = doppler_wide(d.P, sub, doppler_tiles(d, true));
+  const bool sub = d.sub > 1, wide = doppler_wide(d.P, sub, d.T == 1, doppler_tiles(d, true));
   return by_pulse(d.P, [&](auto p) {
     constexpr int Q = p.value;
     constexpr bool W = Q != 32, WS = Q == 100;
