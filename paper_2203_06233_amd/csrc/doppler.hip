@@ -186,8 +186,10 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
 // the same time (0.88 -> 0.86 ms on the 32 x 256 x 16384 cube; with up to
 // 128 pulses the plain order is as fast or faster).
 template <int P, bool WIDE>
+constexpr bool kByXcd = WIDE && P >= 256;
+template <int P, bool WIDE>
 __device__ __forceinline__ int tile_of(int id, int n) {
-  if (!WIDE || P < 256) return id;
+  if (!kByXcd<P, WIDE>) return id;
   const int xcd = id & 7;
   return xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);
 }
@@ -196,9 +198,13 @@ template <int P, bool WIDE, bool SUB>
 __global__ __launch_bounds__((FftShape<P, WIDE>::NT)) __attribute__((amdgpu_waves_per_eu(FftShape<P, WIDE>::WPE)))
 void doppler_kernel(const float2* __restrict__ cube, float2* __restrict__ snap, Dims d) {
   constexpr int RT = FftShape<P, WIDE>::RT;
-  const int ntr = (d.R + RT - 1) / RT;
-  const int u = tile_of<P, WIDE>(blockIdx.x, gridDim.x);
-  doppler_tile<P, WIDE, SUB>(cube, snap, d, u / ntr, (u % ntr) * RT);
+  if constexpr (kByXcd<P, WIDE>) {
+    const int ntr = (d.R + RT - 1) / RT;
+    const int u = tile_of<P, WIDE>(blockIdx.x, gridDim.x);
+    doppler_tile<P, WIDE, SUB>(cube, snap, d, u / ntr, (u % ntr) * RT);
+  } else {  // a grid of tiles x channels: no division
+    doppler_tile<P, WIDE, SUB>(cube, snap, d, blockIdx.y, blockIdx.x * RT);
+  }
 }
 
 // Batched: the workgroups of several cubes with the same P in one grid.
@@ -270,7 +276,9 @@ hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipSt
   return by_pulse(d.P, [&](auto p) {
     constexpr int Q = p.value;
     constexpr bool W = Q != 32, WS = Q == 100;
-    const dim3 g(doppler_tiles(d, wide)), wt(FftShape<Q, W>::NT), nt(FftShape<Q, false>::NT);
+    const int tiles = doppler_tiles(d, wide);
+    const dim3 g = wide && kByXcd<Q, true> ? dim3(tiles) : dim3(tiles / d.C, d.C);
+    const dim3 wt(FftShape<Q, W>::NT), nt(FftShape<Q, false>::NT);
     if (!sub && wide) hipLaunchKernelGGL((doppler_kernel<Q, W, false>), g, wt, 0, st, cube, snap, d);
     else if (!sub) hipLaunchKernelGGL((doppler_kernel<Q, false, false>), g, nt, 0, st, cube, snap, d);
     else if (WS && wide) hipLaunchKernelGGL((doppler_kernel<Q, WS, true>), g, wt, 0, st, cube, snap, d);
