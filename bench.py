@@ -76,8 +76,6 @@ def kernel_work(wl, precision, refine):
     chol = (4.0 / 3.0) * D ** 3 * sysn
     solves = 8.0 * D * D * S * sysn
     cov_key = {"fp32": "fp32", "bf16": "bf16", "fp8": "fp8"}[precision]
-    # the inner products run on BF16 matrix cores on the mixed paths
-    inner_key = "fp32" if precision == "fp32" else "bf16"
     return {
         "doppler": dict(bytes=cube_b + snap_b, fp32=5.0 * T * C * R * P * np.log2(P)),
         "covariance": {"bytes": snap_b + cov_b, cov_key: herm},
@@ -85,7 +83,7 @@ def kernel_work(wl, precision, refine):
         # fused: snapshots in, weights out; covariance products plus the solve
         "covariance_solve": {"bytes": snap_b + w_b, cov_key: herm,
                              "fp32": chol + solves * (1 + refine), "fp64": solves * refine},
-        "inner": {"bytes": snap_b + w_b + pw_b, inner_key: 8.0 * S * D * N * sysn},
+        "inner": {"bytes": snap_b + w_b + pw_b, "bf16": 8.0 * S * D * N * sysn},  # BF16 matrix cores on every path
     }
 
 

@@ -1,4 +1,4 @@
-// Blocked Cholesky solve of one system on the FP32 matrix cores.
+// Blocked Cholesky solve of one system on the matrix cores.
 //
 // The loaded covariance R_L (D x D, padded to 16 NB with an identity tail)
 // and the conjugated steering rows M = V^H (S x D, padded to 16 NS rows with
@@ -19,8 +19,9 @@
 //                  Z_J = M_J Linv_JJ, then M_I -= Z_J L_JI for I < J.
 //   output         w_s = u_s / sqrt(gamma_s), u_s = conj(row s of Z).
 //
-// Block products are 16 x 16 x 16 complex, four real 16 x 16 x 4 MFMAs per
-// k-quarter.  Fragment layout (lane l, m = l % 16, q = l / 16): the lane holds
+// Block products are 16 x 16 x 16 complex: without refinement four real
+// 16 x 16 x 4 FP32 MFMAs per k-quarter (OpF32), with refinement six
+// 16 x 16 x 32 BF16 MFMAs per component (OpSplit).  Fragment layout (lane l, m = l % 16, q = l / 16): the lane holds
 // X[m][4q + i], i = 0..3.  This is the MFMA result layout of X^T, and the A
 // and B operand layouts of a product whose k index runs over the block
 // columns, so every product is formed transposed (X^T -= conj(Q) P^T) and no
