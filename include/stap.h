@@ -81,14 +81,14 @@ typedef enum stap_status {
 
 typedef enum stap_precision {
   /* FP32 throughout: FP32 FFT, FP32 covariance on FP32 MFMA, FP32
-   * Cholesky/solves, inner products with FP32-level error (each FP32 operand
+   * Cholesky/solves (with refinement as in STAP_PREC_BF16), inner products with FP32-level error (each FP32 operand
    * split exactly into three BF16 terms, FP32 accumulation, as on the mixed
    * path). */
   STAP_PREC_FP32 = 0,
   /* Mixed: covariance and inner products as BF16 MFMA products with FP32
    * accumulation (each FP32 operand split exactly into three BF16 terms),
-   * FP32 Cholesky/solves (with refinement their products split in the same
-   * way), FP64 refinement residual. */
+   * FP32 Cholesky/solves (with refinement the block products of the blocked
+   * solve split in the same way), FP64 refinement residual. */
   STAP_PREC_BF16 = 1,
   /* As BF16 but the covariance is one FP8 (OCP E4M3) product per element
    * with a power-of-two scale per (bin, block) and FP32 accumulation. */
@@ -303,8 +303,11 @@ stap_status stap_run_noalloc(const stap_problem* probs, int32_t n_probs,
  *                     single-cube stap_run calls through the stage covariance
  *                     and that solve (stap_covariance_solve, and stap_run
  *                     with refinement, then take variant 8).
- *          Requests a variant does not cover take the default: the blocked
- *          solve with refinement, else the column sweep.
+ *          Requests a variant does not cover take the column sweep.  The
+ *          default (0) is the column sweep without refinement; with it, the
+ *          blocked solve with corrected panels and one step more than
+ *          requested, no less exact than the sweep (kind 1 up to 48 DOF: the
+ *          column sweep).
  * Not thread-safe with respect to concurrent stap_run calls.  Returns
  * STAP_ERR_ARG for values out of range. */
 stap_status stap_tune_set(int32_t kind, int32_t dof, int32_t n_steer, int32_t precision, int32_t refine,

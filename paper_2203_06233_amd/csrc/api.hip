@@ -82,6 +82,7 @@ Dims dims_of(const stap_problem* q) {
   d.eps = q->load_eps;
   d.prec = q->precision;
   d.refine = q->refine_steps;
+  d.corr = 0;
   d.sp = q->cube_stride_pulse ? q->cube_stride_pulse : d.R;
   d.sc = q->cube_stride_chan ? q->cube_stride_chan : (long long)d.P * d.sp;
   d.train = q->training;
@@ -133,13 +134,28 @@ int tuned(int kind, const Dims& d) {
 // Variant of the fused covariance -> solve kernel; variant 1 of kind 0 is
 // not a fused kernel but stap_run's stage route (one_wave_route()), so the
 // fused entry point takes the blocked 8-wave kernel for it.  The default of
-// a class that nobody tuned is the blocked solve with refinement (120 DOF,
-// 20 steering vectors, 2048 systems: 1.1 against 2.9 ms for the column
-// sweep) and the column sweep without, whose FP32 rounding those classes
-// keep.
+// a class that nobody tuned is the blocked solve with refinement, in the form
+// of default_dims(), and the column sweep without, whose FP32 rounding those
+// classes keep.
 int fused_variant(const Dims& d) {
   const int v = tuned(0, d);
   return v == 0 ? (d.refine > 0 ? 8 : 16) : v == 1 ? 8 : v;
+}
+// The blocked solve where no tuned entry asked for it (kind 0 or 1): panels
+// corrected and one refinement step more than requested.  Its weights are then
+// no further from the 64-bit ones than the column sweep's with the requested
+// steps, up to condition numbers of 5e6; with one step alone the corrected
+// form is up to 2 times as far, and the tuned form further still (96 DOF, 64
+// vectors, 4096 systems: sweep 4.49 ms, error 6.3e-8; blocked with corrections
+// and two steps 1.65 ms, 5.4e-8.  120 DOF, 20 vectors, 2048 systems, whole
+// chain: sweep 3.15 ms, so 1.53).
+Dims default_dims(int kind, const Dims& d) {
+  Dims r = d;
+  if (d.refine > 0 && tuned(kind, d) == 0) {
+    r.corr = 1;
+    ++r.refine;
+  }
+  return r;
 }
 // stap_run on one cube: the stage covariance and the one-wave solve instead
 // of the fused kernel, where the table asks for it (kind 0, variant 1) and
@@ -147,13 +163,17 @@ int fused_variant(const Dims& d) {
 bool one_wave_route(const Dims& d) { return tuned(0, d) == 1 && stap::wsolve_supported(d); }
 // Stage solve: the one-wave register-resident solve (variant 1) or the
 // blocked matrix-core solve (variant 4 or 8 waves) where the table asks for
-// it and the shape allows, else the column-sweep solve.
+// it and the shape allows; with refinement the blocked solve of
+// default_dims() above 48 DOF, else the column sweep, which costs less there
+// than the additional step (2048 systems, 24 DOF, 4 vectors: 81 against 103
+// us; 48 DOF 169 against 157; 64 DOF 312 against 211).
 hipError_t stage_solve(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info,
                        hipStream_t st) {
   const int t = tuned(1, d);
-  const int v = (t == 0 || t == 1) && d.refine > 0 ? 8 : t;  // as in fused_variant()
+  const int v = d.refine > 0 && (t == 1 || (t == 0 && d.D > 48)) ? 8 : t;  // as in fused_variant()
   if (v == 1 && stap::wsolve_supported(d)) return stap::launch_wsolve(d, cov, steer, w, info, st);
-  if ((v == 4 || v == 8) && stap::bsolve_supported(d, v)) return stap::launch_bsolve(d, cov, steer, w, info, st, v);
+  if ((v == 4 || v == 8) && stap::bsolve_supported(d, v))
+    return stap::launch_bsolve(default_dims(1, d), cov, steer, w, info, st, v);
   return stap::launch_solve(d, cov, steer, w, info, st);
 }
 
@@ -334,7 +354,8 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
         if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d), false);
         if (e == hipSuccess) e = stap::launch_wsolve(d, cov, pd.steer, pd.w, pd.info, st);
       } else if (stap::fused_supported(d)) {
-        if (e == hipSuccess) e = stap::launch_fused(d, pd.snap, pd.steer, pd.w, pd.info, st, fused_variant(d));
+        if (e == hipSuccess)
+          e = stap::launch_fused(default_dims(0, d), pd.snap, pd.steer, pd.w, pd.info, st, fused_variant(d));
       } else {
         if (e == hipSuccess) e = stap::launch_covariance(d, pd.snap, cov, delta, st, tuned(2, d), false);
         if (e == hipSuccess) e = stage_solve(d, cov, pd.steer, pd.w, pd.info, st);
@@ -345,6 +366,7 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
     return STAP_OK;
   }
 
+  for (stap::ProbDesc& pd : desc) pd.d = default_dims(0, pd.d);
   // Batched: group the cubes by shape class (largest class first), order
   // each class by per-system cost, number its systems, upload the table.
   std::stable_sort(desc.begin(), desc.end(), [](const stap::ProbDesc& a, const stap::ProbDesc& b) {
@@ -521,8 +543,9 @@ stap_status stap_covariance_solve(const stap_problem* prob, const stap_cf32* sna
   if (!aligned(snap, 8) || !aligned(steer, 8) || !aligned(w, 8) || !aligned(info, 4)) return STAP_ERR_ALIGN;
   const Dims d = dims_of(prob);
   if (!stap::fused_supported(d)) return STAP_ERR_UNSUPPORTED;
-  return hip_status(stap::launch_fused(d, reinterpret_cast<const float2*>(snap), reinterpret_cast<const float2*>(steer),
-                                       reinterpret_cast<float2*>(w), info, (hipStream_t)stream, fused_variant(d)));
+  return hip_status(stap::launch_fused(default_dims(0, d), reinterpret_cast<const float2*>(snap),
+                                       reinterpret_cast<const float2*>(steer), reinterpret_cast<float2*>(w), info,
+                                       (hipStream_t)stream, fused_variant(d)));
 }
 
 stap_status stap_inner_products(const stap_problem* prob, const stap_cf32* w, const stap_cf32* snap,

@@ -234,39 +234,52 @@ __device__ __forceinline__ double bcast64(double v, int lane) {
 }
 
 // State of the in-wave factorisation and inversion of a 16 x 16 diagonal
-// block.
+// block.  KEEP: the factor itself goes to LDS as well.
+template <bool KEEP>
 struct Diag {
+  static constexpr bool kKeep = KEEP;
   Acc A;           // row m: columns > j of A, columns <= j of Y
-  floatx4 cr, ci;  // columns 4 (j / 4) .. + 3 of A at row m, on every lane
+  floatx4 cr, ci;  // conjugates of rows 4 (j / 4) .. + 3 of A at column m, on every lane
   float rs;        // 1 / d_j of the column to come
   float rsm;       // 1 / d_m
   int fail;
   double p64;      // FP64 Schur diagonal of row m (on the lane holding (m, m))
+  float* rows;     // LDS scratch of kBlk floats, 16-byte aligned
+  float* keep;     // with KEEP: kBlk floats of LDS that take the factor below its diagonal, zero
+                   // elsewhere: real part of column j, row m at 16 j + m, imaginary part 256 further
   int m, q;
 };
 
-// v -= l * (row J of v) on every lane for the register pairs (re, im) listed,
-// l = lx + i ly: the row broadcast is a DPP operand of the FMA (the compiler
-// folds DPP moves into multiplications but not into FMAs, and separate moves
-// are a third of the column's instructions).  Per value the order is
-// fma(-lx, b, fma(+-ly, b', v)).  l is zero on row J itself, so the broadcast
-// reads the row's old value whatever has been written, and every register's
-// uses are at least 4 instructions apart (DPP reads need two wait states
-// after a write); the s_nops keep that distance to the compiler's
-// instructions on both sides.
-#define STAP_F(D, S, L) "v_fmac_f32_dpp " D ", " S ", " L " row_newbcast:%[j] row_mask:0xf bank_mask:0xf\n"
+// v -= l * (row j of v) on every lane for the register pairs (re, im) of A
+// and Y, l = lx + i ly: the row broadcast is a DPP operand of the FMA (the
+// compiler folds DPP moves into multiplications but not into FMAs, and
+// separate moves are a third of the column's instructions).  Per value the
+// order is fma(-lx, b, fma(+-ly, b', v)).  The copies c of rows j + 1 .. take
+// c -= conj(l of that row) a, a = ax + i ay the lane's own copy of row j, in
+// the same order, which gives them the bits of the rows that they copy.
+// l is zero on row j itself, so the broadcast reads the row's old value
+// whatever has been written, and every register's uses are at least 4
+// instructions apart (DPP reads need two wait states after a write); the
+// s_nops keep that distance to the compiler's instructions on both sides.
+#define STAP_DPP(J) " row_newbcast:%[" J "] row_mask:0xf bank_mask:0xf\n"
+#define STAP_F(D, S, L) "v_fmac_f32_dpp " D ", " S ", " L STAP_DPP("j")
 #define STAP_ROWUPD(P) P("%[r0]", "%[i0]") P("%[r1]", "%[i1]") P("%[r2]", "%[i2]") P("%[r3]", "%[i3]")
 #define STAP_P1(R, I) STAP_F(R, I, "%[ly]")
 #define STAP_P2(R, I) STAP_F(I, "-" R, "%[ly]")
 #define STAP_P3(R, I) STAP_F(R, "-" R, "%[lx]")
 #define STAP_P4(R, I) STAP_F(I, "-" I, "%[lx]")
+#define STAP_C1(N) "v_fmac_f32_dpp %[c" N "], -%[ly], %[ay]" STAP_DPP("j" N)
+#define STAP_C2(N) "v_fmac_f32_dpp %[e" N "], %[ly], %[ax]" STAP_DPP("j" N)
+#define STAP_C3(N) "v_fmac_f32_dpp %[c" N "], -%[lx], %[ax]" STAP_DPP("j" N)
+#define STAP_C4(N) "v_fmac_f32_dpp %[e" N "], -%[lx], %[ay]" STAP_DPP("j" N)
 #define STAP_COLS(C1, C2, C3, C4)                                                                          \
   asm("s_nop 1\n" C1 STAP_ROWUPD(STAP_P1) C2 STAP_ROWUPD(STAP_P2) C3 STAP_ROWUPD(STAP_P3) C4               \
           STAP_ROWUPD(STAP_P4) "s_nop 1"                                                                   \
       : [r0] "+v"(ar0), [r1] "+v"(ar1), [r2] "+v"(ar2), [r3] "+v"(ar3), [i0] "+v"(ai0), [i1] "+v"(ai1),     \
         [i2] "+v"(ai2), [i3] "+v"(ai3), [c1] "+v"(cr1), [c2] "+v"(cr2), [c3] "+v"(cr3), [e1] "+v"(ci1),     \
         [e2] "+v"(ci2), [e3] "+v"(ci3)                                                                     \
-      : [lx] "v"(lx), [ly] "v"(ly), [j] "n"(j))
+      : [lx] "v"(lx), [ly] "v"(ly), [ax] "v"(ax), [ay] "v"(ay), [j] "n"(j), [j1] "n"(4 * jq + 1),           \
+        [j2] "n"(4 * jq + 2), [j3] "n"(4 * jq + 3))
 
 // Column j of diag_factor_inv().  The inverse is formed in place: once the
 // multipliers l_mj of column j are taken, A's column j is dead and Y's column
@@ -276,10 +289,15 @@ struct Diag {
 // of row j records 1 / d_j for the final scaling.  What is left above the
 // diagonal at the end is dropped by diag_end().
 //
-// The multipliers of a column are read from a copy of the current four
-// columns that every lane of a row keeps (cr, ci), updated like A itself and
-// refreshed every fourth column: a cross-lane read through the LDS pipe, with
-// its latency, once per four columns instead of once per column.
+// The multipliers l_mj come from row j, as conj(A[j][m]), and not from column
+// j: row and column of a Hermitian block drift apart in the rounding of the
+// earlier columns, and products of a multiplier from the one and a row from
+// the other magnify the difference by |l| / d (the factor's backward error
+// was up to 45 times that of products which agree).  Every lane keeps a copy
+// of the current four rows at column m (cr, ci), updated with the same bits as
+// the rows and refreshed every fourth column through LDS, with its latency
+// once per four columns instead of once per column.  Below the diagonal A
+// itself is never read.
 //
 // The pivot is taken in FP64: every lane keeps, for its row m, p64 =
 // (loaded diagonal R_mm) - (sum over earlier block columns of |L_mk|^2, FP64
@@ -290,28 +308,35 @@ struct Diag {
 // There is no branch: after a non-positive pivot the remaining columns run
 // on meaningless values and only the first failing index is kept, so the 16
 // columns form one straight-line block the compiler can overlap.
-template <int j>
-__device__ __forceinline__ void diag_pivot(Diag& s) {
+template <int j, class S>
+__device__ __forceinline__ void diag_pivot(S& s) {
   const double piv64 = bcast64(s.p64, j + 16 * (j >> 2));  // row j's FP64 Schur diagonal, wave-uniform
   s.fail = (s.fail == 0 && !(piv64 > 0.0)) ? j + 1 : s.fail;
   s.rs = __builtin_amdgcn_rsqf((float)piv64);
 }
-template <int j>
-__device__ __forceinline__ void diag_col(Diag& s) {
+template <int j, class S>
+__device__ __forceinline__ void diag_col(S& s) {
   constexpr int jq = j >> 2, ji = j & 3;
   if constexpr (ji == 0) {
+    // all rows go out, which spares a mask; a wave's LDS accesses keep their order
+    *reinterpret_cast<floatx4*>(s.rows + 16 * s.m + 4 * s.q) = s.A.re;
+    *reinterpret_cast<floatx4*>(s.rows + 256 + 16 * s.m + 4 * s.q) = s.A.im;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      s.cr[i] = __shfl(s.A.re[i], s.m + 16 * jq);
-      s.ci[i] = __shfl(s.A.im[i], s.m + 16 * jq);
+      s.cr[i] = s.rows[16 * (4 * jq + i) + s.m];
+      s.ci[i] = -s.rows[256 + 16 * (4 * jq + i) + s.m];
     }
   }
   const float rs = s.rs, r2 = rs * rs;
-  const float ax = s.m > j ? s.cr[ji] : 0.f, ay = s.m > j ? s.ci[ji] : 0.f;  // A[m][j]
+  const float ax = s.m > j ? s.cr[ji] : 0.f, ay = s.m > j ? s.ci[ji] : 0.f;  // conj(A[j][m])
   const float lx = ax * r2, ly = ay * r2;                                    // l_mj / d_j
   s.rsm = (s.m == j) ? rs : s.rsm;
-  // l_mj = A[m][j] / d_j in FP32, squared and summed in FP64 for row m
+  // l_mj = conj(A[j][m]) / d_j in FP32, squared and summed in FP64 for row m
   const float lr = ax * rs, li = ay * rs;
+  if (S::kKeep) {  // the four lanes of row m write the same
+    s.keep[16 * j + s.m] = lr;
+    s.keep[256 + 16 * j + s.m] = li;
+  }
   s.p64 -= (double)lr * (double)lr + (double)li * (double)li;
   if constexpr (j < 15) diag_pivot<j + 1>(s);  // its latency passes behind the update
   s.A.re[ji] = s.q == jq ? (s.m == j ? 1.f : 0.f) : s.A.re[ji];
@@ -321,18 +346,13 @@ __device__ __forceinline__ void diag_col(Diag& s) {
   float cr1 = s.cr[1], cr2 = s.cr[2], cr3 = s.cr[3], ci1 = s.ci[1], ci2 = s.ci[2], ci3 = s.ci[3];
   // A[m][c] -= l_mj conj(l_cj) = (A[m][j] / d_j^2) A[j][c], and Y likewise
   if constexpr (ji == 0)
-    STAP_COLS(STAP_P1("%[c1]", "%[e1]") STAP_P1("%[c2]", "%[e2]") STAP_P1("%[c3]", "%[e3]"),
-              STAP_P2("%[c1]", "%[e1]") STAP_P2("%[c2]", "%[e2]") STAP_P2("%[c3]", "%[e3]"),
-              STAP_P3("%[c1]", "%[e1]") STAP_P3("%[c2]", "%[e2]") STAP_P3("%[c3]", "%[e3]"),
-              STAP_P4("%[c1]", "%[e1]") STAP_P4("%[c2]", "%[e2]") STAP_P4("%[c3]", "%[e3]"));
+    STAP_COLS(STAP_C1("1") STAP_C1("2") STAP_C1("3"), STAP_C2("1") STAP_C2("2") STAP_C2("3"),
+              STAP_C3("1") STAP_C3("2") STAP_C3("3"), STAP_C4("1") STAP_C4("2") STAP_C4("3"));
   else if constexpr (ji == 1)
-    STAP_COLS(STAP_P1("%[c2]", "%[e2]") STAP_P1("%[c3]", "%[e3]"),
-              STAP_P2("%[c2]", "%[e2]") STAP_P2("%[c3]", "%[e3]"),
-              STAP_P3("%[c2]", "%[e2]") STAP_P3("%[c3]", "%[e3]"),
-              STAP_P4("%[c2]", "%[e2]") STAP_P4("%[c3]", "%[e3]"));
+    STAP_COLS(STAP_C1("2") STAP_C1("3"), STAP_C2("2") STAP_C2("3"), STAP_C3("2") STAP_C3("3"),
+              STAP_C4("2") STAP_C4("3"));
   else if constexpr (ji == 2)
-    STAP_COLS(STAP_P1("%[c3]", "%[e3]"), STAP_P2("%[c3]", "%[e3]"), STAP_P3("%[c3]", "%[e3]"),
-              STAP_P4("%[c3]", "%[e3]"));
+    STAP_COLS(STAP_C1("3"), STAP_C2("3"), STAP_C3("3"), STAP_C4("3"));
   else
     STAP_COLS("", "", "", "");
   s.A.re = floatx4{ar0, ar1, ar2, ar3};
@@ -340,22 +360,30 @@ __device__ __forceinline__ void diag_col(Diag& s) {
   s.cr = floatx4{s.cr[0], cr1, cr2, cr3};
   s.ci = floatx4{s.ci[0], ci1, ci2, ci3};
 }
-template <int j>
-__device__ __forceinline__ void diag_cols(Diag& s) {
+template <int j, class S>
+__device__ __forceinline__ void diag_cols(S& s) {
   diag_col<j>(s);
   if constexpr (j < 15) diag_cols<j + 1>(s);
 }
+#undef STAP_DPP
 #undef STAP_F
 #undef STAP_ROWUPD
 #undef STAP_P1
 #undef STAP_P2
 #undef STAP_P3
 #undef STAP_P4
+#undef STAP_C1
+#undef STAP_C2
+#undef STAP_C3
+#undef STAP_C4
 #undef STAP_COLS
 
-__device__ __forceinline__ void diag_begin(Diag& s, const Acc& A, double p64) {
+template <class S>
+__device__ __forceinline__ void diag_begin(S& s, const Acc& A, double p64, float* rows, float* keep = nullptr) {
   const int l = lane_tid() & 63;
   s.A = A;
+  s.rows = rows;
+  s.keep = keep;
   s.cr = s.ci = floatx4{0.f, 0.f, 0.f, 0.f};
   s.rsm = 1.f;
   s.fail = 0;
@@ -365,8 +393,8 @@ __device__ __forceinline__ void diag_begin(Diag& s, const Acc& A, double p64) {
   diag_pivot<0>(s);
 }
 // SIGN / d_m times row m of Y, zero above the diagonal.
-template <int SIGN>
-__device__ __forceinline__ Acc diag_end(const Diag& s) {
+template <int SIGN, class S>
+__device__ __forceinline__ Acc diag_end(const S& s) {
   const float sc = SIGN < 0 ? -s.rsm : s.rsm;
   Acc X;
 #pragma unroll
@@ -378,26 +406,28 @@ __device__ __forceinline__ Acc diag_end(const Diag& s) {
   return X;
 }
 
-// Factor the Hermitian 16 x 16 block A (full, both triangles) as L L^H inside
-// one wave and return X = SIGN L^-1 (lower triangular).  Column j: pivot
-// d_j = sqrt(A[j][j]) (taken in FP64 as above, p64 the lane's starting
-// value for its row: loaded diagonal minus the earlier block columns),
-// l_mj = A[m][j] / d_j for m > j, then A[m][c] -= l_mj conj(l_cj) for
-// m, c > j; the inverse is accumulated as X <- L_j^-1 X with L_j the
-// identity carrying column j of L (row j of X divided by d_j, then row m -=
-// l_mj row j), the row divisions deferred.  A[c][j] is read as conj(A[j][c])
-// from row j, which lives in the same 16-lane row of the wave (a DPP
-// broadcast).  Returns 0 or the 1-based index of the first non-positive
-// pivot.  The wave runs at raised priority: the other waves of its system
-// wait for it.
-template <int SIGN>
-__device__ __forceinline__ int diag_factor_inv(const Acc& A, Acc& X, double p64) {
-  Diag s;
-  diag_begin(s, A, p64);
+// Factor the Hermitian 16 x 16 block A (of which the upper triangle is read)
+// as L L^H inside one wave and return X = SIGN L^-1 (lower triangular) and,
+// with KEEP, leave L in LDS at keep, but for its diagonal, which dm returns
+// (row m's element on the lanes of row m).  Column j: pivot d_j =
+// sqrt(A[j][j]) (taken in FP64 as above, p64 the lane's starting value for
+// its row: loaded diagonal minus the earlier block columns), l_mj =
+// conj(A[j][m]) / d_j for m > j, then A[m][c] -= l_mj conj(l_cj) for m, c >
+// j; the inverse is accumulated as X <- L_j^-1 X with L_j the identity
+// carrying column j of L (row j of X divided by d_j, then row m -= l_mj row
+// j), the row divisions deferred.  Row j of A and X lives in the same 16-lane
+// row of the wave (a DPP broadcast).  Returns 0 or the 1-based index of the
+// first non-positive pivot.  The wave runs at raised priority: the other
+// waves of its system wait for it.
+template <int SIGN, bool KEEP>
+__device__ __forceinline__ int diag_factor_inv(const Acc& A, Acc& X, float& dm, double p64, float* rows, float* keep) {
+  Diag<KEEP> s;
+  diag_begin(s, A, p64, rows, keep);
   __builtin_amdgcn_s_setprio(3);
   diag_cols<0>(s);
   __builtin_amdgcn_s_setprio(0);
   X = diag_end<SIGN>(s);
+  if (KEEP) dm = 1.f / s.rsm;
   return s.fail;
 }
 
@@ -449,7 +479,8 @@ struct BCfg {
   // owner; 96 DOF, 64 vectors, 128 x 32 systems 1078 and 1035 us; 96 DOF, 16
   // vectors 7.13 and 7.30 ms).
   static constexpr bool kOwnerSplits = NSM > 2;
-  // LDS: exchange blocks (NB + NS + 1 for the factorisation; two times NB
+  // LDS: exchange blocks (NB + NS + 1 for the factorisation, one more with
+  // refinement; two times NB
   // blocks of L and NS for the solves; with refinement, all NS NB blocks
   // of Z in FP32 for the residual), the gamma
   // partials [NB][16 NS] (FP64), a flag, the FP64 row sums of |L|^2 over the
@@ -457,7 +488,7 @@ struct BCfg {
   // FP64 pivots)
   __host__ __device__ static constexpr size_t xbytes(int NB, int NS, bool refine) {
     const size_t kB = refine ? OpSplit::kB : OpF32::kB;
-    const size_t f = (NB + NS + 1) * kB * 4, s = (2 * NB * (kOwnerSplits ? kB : kBlk) + NS * kB) * 4;
+    const size_t f = (NB + NS + (refine ? 2 : 1)) * kB * 4, s = (2 * NB * (kOwnerSplits ? kB : kBlk) + NS * kB) * 4;
     const size_t z = refine ? (size_t)NS * NB * kBlk * 4 : 0;
     return f > s ? (f > z ? f : z) : (s > z ? s : z);
   }
@@ -508,7 +539,8 @@ template <class C, bool REFINE>
 struct SolveLds {
   typedef std::conditional_t<REFINE, OpSplit, OpF32> Op;
   float* xb;      // exchange blocks
-  float* dinv;    // minus the inverse of the current diagonal block
+  float* dinv;    // minus the inverse of the current diagonal block's factor
+  float* diag;    // that factor (with refinement)
   double* gpart;  // gamma partials
   int* sflag;     // pivot status
   double* d64;    // FP64 row sums of |L|^2
@@ -516,6 +548,7 @@ struct SolveLds {
   __device__ __forceinline__ SolveLds(unsigned char* xlds, int NB, int NS) {
     xb = reinterpret_cast<float*>(xlds);
     dinv = xb + (size_t)(NB + NS) * Op::kB;
+    diag = dinv + Op::kB;
     gpart = reinterpret_cast<double*>(xlds + C::xbytes(NB, NS, REFINE));
     sflag = reinterpret_cast<int*>(gpart + NB * 16 * NS);
     d64 = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(sflag) + 16);
@@ -632,6 +665,14 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
         if (sl.lv[t] && sl.lc[t] == J && sl.lr[t] != J) {
           Acc x = acc_zero();
           Op::pqh(x, Op::frag(al[t]), Q);
+          if (REFINE && d.corr) {
+            // X = A Linv^H carries the inverse's error, |L| |Linv| times that
+            // of a substitution, into everything that follows; one step of
+            // X += (A - X L^H) Linv^H takes it out
+            Acc e = al[t];
+            Op::pqh(e, Op::frag(x), Op::load(L.diag, nat));
+            Op::pqh(x, Op::frag(e), Q);
+          }
           al[t] = x;
           Op::store(xb + sl.lr[t] * kB, Op::frag(x), nat);
           // FP64 row sums of |L|^2 for the pivots of block row lr (one
@@ -671,8 +712,19 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
       const int r = 16 * (J + 1) + m;
       const double p64 = (double)L.rdiag[r] - (J >= 0 ? L.d64[r] : 0.0);
       Acc X;
-      const int f = diag_factor_inv<-1>(acc_neg(A), X, p64);
+      float dm = 0.f;
+      const int f = diag_factor_inv<-1, REFINE>(acc_neg(A), X, dm, p64, L.dinv, L.diag);
       Op::store(L.dinv, Op::frag(X), nat);
+      if (REFINE && d.corr) {
+        Acc F;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int c = 4 * q + i;
+          F.re[i] = c == m ? dm : L.diag[16 * c + m];
+          F.im[i] = L.diag[256 + 16 * c + m];
+        }
+        Op::store(L.diag, Op::frag(F), nat);
+      }
 #pragma unroll
       for (int t = 0; t < NSL; ++t)
         if (tn == t) {

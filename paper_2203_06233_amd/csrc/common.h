@@ -37,6 +37,7 @@ struct Dims {
   int L;   // P-T+1, sub-CPI (window) length
   float eps;
   int prec, refine;
+  int corr;  // 1: the blocked solve corrects its panels (with refinement)
   long long sc, sp;  // cube strides of channel and pulse (elements)
   int train;         // stap_training
   int guard;         // guard cells per side (STAP_TRAIN_EXCLUDE)

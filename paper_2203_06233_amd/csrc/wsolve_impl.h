@@ -121,7 +121,7 @@ __device__ __forceinline__ void step_work(Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[
 // instruction stream interleaves the serial VALU work of diagonal block
 // J+1 with independent matrix-core products.
 template <int NB, int NS, int J, int j>
-__device__ __forceinline__ void diag_cols_work(Diag& s, Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[NS * NB]) {
+__device__ __forceinline__ void diag_cols_work(Diag<false>& s, Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[NS * NB]) {
   constexpr int C = StepWork<NB, NS, J>::COUNT;
   diag_col<j>(s);
   step_work<NB, NS, J, j * C / 16, (j + 1) * C / 16>(L, M);
@@ -136,7 +136,7 @@ __device__ __forceinline__ void diag_cols_work(Diag& s, Acc (&L)[NB * (NB + 1) /
 // difference.
 template <int NB, int NS, int J>
 __device__ __forceinline__ void fact_step(Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[NS * NB], int& fail, double* d64,
-                                          const float* rdiag) {
+                                          const float* rdiag, float* rows) {
   const int lane = lane_tid() & 63;
 #pragma unroll
   for (int I = J + 1; I < NB; ++I) {
@@ -155,12 +155,12 @@ __device__ __forceinline__ void fact_step(Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[
   if constexpr (J + 1 < NB) {
     mma_pqh<true>(L[tri(J + 1, J + 1)], L[tri(J + 1, J)], L[tri(J + 1, J)]);
     const int m = lane & 15;
-    Diag s;
-    diag_begin(s, L[tri(J + 1, J + 1)], (double)rdiag[16 * (J + 1) + m] - d64[16 * (J + 1) + m]);
+    Diag<false> s;
+    diag_begin(s, L[tri(J + 1, J + 1)], (double)rdiag[16 * (J + 1) + m] - d64[16 * (J + 1) + m], rows);
     diag_cols_work<NB, NS, J, 0>(s, L, M);
     fail = (fail == 0 && s.fail != 0) ? 16 * (J + 1) + s.fail : fail;
     L[tri(J + 1, J + 1)] = diag_end<1>(s);
-    fact_step<NB, NS, J + 1>(L, M, fail, d64, rdiag);
+    fact_step<NB, NS, J + 1>(L, M, fail, d64, rdiag, rows);
   }
 }
 
@@ -313,10 +313,11 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
   int fail = 0;
   {
     Acc X;
-    fail = diag_factor_inv<1>(L[0], X, (double)blk_diag(L[0]));
+    float unused;
+    fail = diag_factor_inv<1, false>(L[0], X, unused, (double)blk_diag(L[0]), tb, nullptr);
     L[0] = X;
   }
-  fact_step<NB, G, 0>(L, M, fail, d64, rdiag);
+  fact_step<NB, G, 0>(L, M, fail, d64, rdiag, tb);  // tb is free until the back solve
   if (fail) {
     for (int e = lane; e < S * D; e += 64) W[e] = make_float2(0.f, 0.f);
     if (lane == 0 && info) *info = fail;
