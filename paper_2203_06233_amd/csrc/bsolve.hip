@@ -13,7 +13,8 @@ struct GlobalRB {
   const float2* A;
   int D;
   bool vec;  // rows16(A, D)
-  // Lane (m, q): R[16I + m][16J + 4q + i], i = 0..3 (J <= I), identity beyond D.
+  // Lane (m, q): R[16I + m][16J + 4q + i], i = 0..3 (J <= I), identity beyond
+  // D; the diagonal's imaginary part is not looked at.
   __device__ __forceinline__ Acc block(int I, int J) const {
     const int l = lane_tid() & 63, m = l & 15, q = l >> 4;
     const int r = 16 * I + m, c0 = 16 * J + 4 * q;
@@ -28,7 +29,7 @@ struct GlobalRB {
         v[i] = make_float2(r == c ? 1.f : 0.f, 0.f);
         if (r < D && c < D) {
           v[i] = c <= r ? A[r * D + c] : A[c * D + r];
-          if (c > r) v[i].y = -v[i].y;
+          v[i].y = c > r ? -v[i].y : c == r ? 0.f : v[i].y;
         }
       }
     }

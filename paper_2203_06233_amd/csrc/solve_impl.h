@@ -176,13 +176,14 @@ __device__ __forceinline__ void residual_mfma(const RSrc& src, const float2* Rp,
   for (int a = 0; a < NVS; ++a)
 #pragma unroll
     for (int b = 0; b < NB; ++b) rv[a][b] = make_float2(0.f, 0.f);
-  // R_L[m][k] from the stored lower triangle, zero outside D x D
+  // R_L[m][k] from the stored lower triangle, zero outside D x D; the
+  // diagonal's imaginary part is not looked at
   auto relem = [&](int m, int k) -> float2 {
     const int mc = min(m, D - 1), kc = min(k, D - 1);
     const bool lower = kc <= mc;
     const int hi = lower ? mc : kc, lo = lower ? kc : mc;
     float2 v = RP_LDS ? Rp[hi * (hi + 1) / 2 + lo] : src.lower(hi, lo);
-    v.y = lower ? v.y : -v.y;
+    v.y = kc == mc ? 0.f : lower ? v.y : -v.y;
     return (m < D && k < D) ? v : make_float2(0.f, 0.f);
   };
   for (int N = 0; N < nslab; ++N) {

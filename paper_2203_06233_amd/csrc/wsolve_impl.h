@@ -268,8 +268,8 @@ __device__ __forceinline__ void finish_m(const Acc (&L)[NB * (NB + 1) / 2], Acc 
 // dependency; one fits two waves.
 constexpr int steer_group(int NB, int NS) { return NB >= 5 ? 1 : NS; }
 
-// Solve one system: R is its loaded covariance, full Hermitian [D][D]
-// row-major, W its [S][D] weights, info its status word (may be null);
+// Solve one system: R is its loaded covariance, of which the lower triangle is
+// read, [D][D] row-major, W its [S][D] weights, info its status word (may be null);
 // D <= 16 NB, S <= 16 NS.  lds points at WsLds<NB>::COMPLEX complex of
 // 16-byte aligned LDS.  Blocks beyond D carry the identity, steering rows
 // beyond S are zero.  The first group of steering blocks rides along with the
@@ -295,14 +295,25 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
       const int r = 16 * I + m;
       Acc a;
       float2 v[4];
-      if (J == NB - 1) load_row4<true>(R, r, 16 * J + 4 * q, D, D, v);
-      else load_row4<false>(R, r, 16 * J + 4 * q, D, D, v);
+      if (I == J) {
+        // the factorisation reads a diagonal block above its diagonal, which
+        // comes from the lower triangle: element (r, c) is conj(R[c][r])
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = 16 * J + 4 * q + i;
-        a.re[i] = I == J && r >= D && c == r ? 1.f : v[i].x;
-        a.im[i] = v[i].y;
-        if (I == J && c == r) rdiag[r] = a.re[i];
+        for (int i = 0; i < 4; ++i) {
+          const int c = 16 * J + 4 * q + i;
+          const float2 x = R[min(max(c, r), D - 1) * D + min(min(c, r), D - 1)];
+          const bool ok = c < D && r < D;
+          a.re[i] = ok ? x.x : r == c ? 1.f : 0.f;
+          a.im[i] = ok && c > r ? -x.y : 0.f;
+          if (c == r) rdiag[r] = a.re[i];
+        }
+      } else {
+        load_row4<false>(R, r, 16 * J + 4 * q, D, D, v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          a.re[i] = v[i].x;
+          a.im[i] = v[i].y;
+        }
       }
       L[tri(I, J)] = a;
     }
