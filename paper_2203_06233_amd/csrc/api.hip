@@ -415,16 +415,17 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
       const int n = (int)std::min<size_t>(stap::kMaxBatchArg, at.size() - first);
       Dop x;
       x.P = P;
-      x.sub = false;
+      int sub = 1;
       bool one_tap = true;
       long long wide_tiles = 0;
       for (int j = 0; j < n; ++j) {
         const Dims& d = desc[at[first + j]].d;
-        x.sub = x.sub || d.sub > 1;
+        sub = std::max(sub, d.sub);
         one_tap = one_tap && d.T == 1;
         wide_tiles += stap::doppler_tiles(d, true);
       }
-      x.wide = stap::doppler_wide(P, x.sub, one_tap, wide_tiles);
+      x.sub = sub > 1;
+      x.wide = stap::doppler_wide(P, sub, one_tap, wide_tiles);
       x.bi.n = n;
       int tiles = 0;
       for (int j = 0; j < n; ++j) {

@@ -54,6 +54,16 @@ struct FftShape {
   static constexpr int NT = P2 * RT;
   static constexpr int WPE = P == 512 ? 1 : P == 256 && !WIDE ? 3 : 4;
   static constexpr int ELEMS = 1;  // elements loaded at a time (subarrays)
+  // Whether the compiler is kept from gathering all window, twiddle and
+  // address values of an unrolled loop before their use: only where the
+  // registers need it (256 pulses, narrow, 8 channels x 1024 cells: 12.4 us
+  // with it, 11.3 without).
+  static constexpr bool FENCE = WIDE || P == 512;
+  // Complex values of the transpose tile.  Narrow tiles of up to 64 pulses take
+  // 40 KB of LDS, which holds a compute unit to four workgroups: with the six
+  // to eight that their registers allow, more rows are open in memory at a time
+  // (32 pulses, 32 channels x 16384 cells, T = 3: 105 us, so 100).
+  static constexpr int TILE = !WIDE && P <= 64 ? 4900 : P1 * P2 * RT;
 };
 // The paper's 100 pulses: 10 x 10, 32 or 96 cells (whole 128-byte lines).
 // With subarrays the loads of several elements are issued before their
@@ -62,20 +72,18 @@ struct FftShape {
 template <bool WIDE>
 struct FftShape<100, WIDE> {
   static constexpr int P1 = 10, P2 = 10, RT = WIDE ? 96 : 32, NT = 10 * RT, WPE = 4, ELEMS = WIDE ? 2 : 4;
+  static constexpr bool FENCE = WIDE;
+  static constexpr int TILE = 100 * RT;
 };
 
 // One workgroup's tile: channel c, range cells r0 .. r0+RT-1 of one cube.
-// The groups between sched_barriers keep the compiler from gathering all
-// window, twiddle and address values of an unrolled loop before their use.
-// SUB is a template parameter because the subarray loads of a kernel that
-// has them set its register count (256 instead of 140 at 512 pulses) whether
-// or not a cube uses them.
+// SUB: the subarray loads are compiled in (with d.sub == 1 they are not used).
 template <int P, bool WIDE, bool SUB>
 __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, float2* __restrict__ snap,
                                              const Dims& d, int c, int r0) {
   using Sh = FftShape<P, WIDE>;
   constexpr int P1 = Sh::P1, P2 = Sh::P2, RT = Sh::RT, NT = Sh::NT;
-  __shared__ float2 ybuf[P1 * P2 * RT];  // [k1][n2][cell]
+  __shared__ float2 ybuf[Sh::TILE];  // [k1][n2][cell]
   __shared__ float2 tw[P];
   __shared__ float hwin[P];
 
@@ -97,7 +105,7 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
 #pragma unroll
     for (int n1 = 0; n1 < P1; ++n1) {
       x[n1] = load_stream(src + (long long)(P2 * n1) * d.sp);
-      if (n1 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      if (Sh::FENCE && n1 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
   } else if (live) {
     // channel c is the sum of array elements c*sub .. c*sub + sub - 1,
@@ -139,14 +147,14 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
       const int q = P2 * n1 + n2 - t;
       const float h = (q >= 0 && q < P) ? hwin[q] : 0.f;
       v[n1] = make_float2(x[n1].x * h, x[n1].y * h);
-      if (n1 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      if (Sh::FENCE && n1 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
     dft_any<P1>(v);
 #pragma unroll
     for (int k1 = 0; k1 < P1; ++k1) {
       const float2 y = (k1 == 0) ? v[k1] : cmul(v[k1], tw[k1 * n2]);
       ybuf[(k1 * P2 + n2) * RT + col] = y;
-      if (k1 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      if (Sh::FENCE && k1 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
     const int dof = t * d.C + c;
@@ -162,7 +170,7 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
 #pragma unroll
         for (int k2 = 0; k2 < P2; ++k2) {
           z[k2] = cmulc(z[k2], tw[((k1 + P1 * k2) * t) % P]);
-          if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          if (Sh::FENCE && k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
       }
       if (r3 < d.R) {
@@ -172,7 +180,7 @@ __device__ __forceinline__ void doppler_tile(const float2* __restrict__ cube, fl
         for (int k2 = 0; k2 < P2; ++k2) {
           store_stream(dst, z[k2]);
           dst += step;
-          if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          if (Sh::FENCE && k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -248,13 +256,21 @@ int doppler_tiles(const Dims& d, bool wide) {
 // Wide tiles where their workgroups give every compute unit 16 waves; with
 // subarrays only the 100-pulse shape has one.  With a single tap a tile's
 // loads and stores take equally long, and a compute unit that holds one wide
-// workgroup does them in turn: at 64, 256 and 512 pulses narrow tiles are as
-// fast or faster then (32 channels, 4096 cells: 25, 100 and 214 us against
-// 28, 108 and 236), at 128 and 100 not (48 and 50 against 46 and 47).
-bool doppler_wide(int P, bool sub, bool one_tap, long long wide_tiles) {
-  if (P == 32 || (sub && P != 100) || (one_tap && P != 128 && P != 100)) return false;
+// workgroup does them in turn: at 64, 100, 256 and 512 pulses narrow tiles are
+// as fast or faster then (32 channels, 4096 cells: 23, 44, 100 and 214 us
+// against 28, 47, 108 and 236), at 128 not (48 against 46), and at 100 not
+// where many elements a subarray make the loads long (20 channels x 3000
+// cells of 10 elements: 115 against 100 us; 8 x 4096 of 4: 26 against 28).
+bool doppler_wide(int P, int sub, bool one_tap, long long wide_tiles) {
+  if (P == 32 || (sub > 1 && P != 100) || (one_tap && P != 128 && !(P == 100 && sub >= 8))) return false;
   return by_pulse(P, [&](auto p) { return wide_tiles * FftShape<p.value, true>::NT >= 256LL * 1024; });
 }
+
+// The narrow kernel without subarrays.  At 100 pulses it is the one that has
+// their loads too: its registers are allocated better (one tap, 32 channels x
+// 4096 cells 44 us, without those loads 47).
+template <int P>
+constexpr bool kPlainSub = P == 100;
 
 hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex& bi, int tiles, bool wide, bool sub,
                                   hipStream_t st) {
@@ -264,7 +280,7 @@ hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex&
     constexpr bool W = Q != 32, WS = Q == 100;
     const dim3 g(tiles), wt(FftShape<Q, W>::NT), nt(FftShape<Q, false>::NT);
     if (!sub && wide) hipLaunchKernelGGL((doppler_batched_kernel<Q, W, false>), g, wt, 0, st, desc, bi);
-    else if (!sub) hipLaunchKernelGGL((doppler_batched_kernel<Q, false, false>), g, nt, 0, st, desc, bi);
+    else if (!sub) hipLaunchKernelGGL((doppler_batched_kernel<Q, false, kPlainSub<Q>>), g, nt, 0, st, desc, bi);
     else if (WS && wide) hipLaunchKernelGGL((doppler_batched_kernel<Q, WS, true>), g, wt, 0, st, desc, bi);
     else hipLaunchKernelGGL((doppler_batched_kernel<Q, false, true>), g, nt, 0, st, desc, bi);
     return hipGetLastError();
@@ -272,7 +288,7 @@ hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex&
 }
 
 hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipStream_t st) {
-  const bool sub = d.sub > 1, wide = doppler_wide(d.P, sub, d.T == 1, doppler_tiles(d, true));
+  const bool sub = d.sub > 1, wide = doppler_wide(d.P, d.sub, d.T == 1, doppler_tiles(d, true));
   return by_pulse(d.P, [&](auto p) {
     constexpr int Q = p.value;
     constexpr bool W = Q != 32, WS = Q == 100;
@@ -280,7 +296,7 @@ hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipSt
     const dim3 g = wide && kByXcd<Q, true> ? dim3(tiles) : dim3(tiles / d.C, d.C);
     const dim3 wt(FftShape<Q, W>::NT), nt(FftShape<Q, false>::NT);
     if (!sub && wide) hipLaunchKernelGGL((doppler_kernel<Q, W, false>), g, wt, 0, st, cube, snap, d);
-    else if (!sub) hipLaunchKernelGGL((doppler_kernel<Q, false, false>), g, nt, 0, st, cube, snap, d);
+    else if (!sub) hipLaunchKernelGGL((doppler_kernel<Q, false, kPlainSub<Q>>), g, nt, 0, st, cube, snap, d);
     else if (WS && wide) hipLaunchKernelGGL((doppler_kernel<Q, WS, true>), g, wt, 0, st, cube, snap, d);
     else hipLaunchKernelGGL((doppler_kernel<Q, false, true>), g, nt, 0, st, cube, snap, d);
     return hipGetLastError();

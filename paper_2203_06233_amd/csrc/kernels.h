@@ -29,10 +29,11 @@ struct BatchIndex {
 };
 
 // Doppler tiles (workgroups) of one cube in the narrow or the wide shape,
-// whether a launch with that many wide tiles (with subarrays or not, with one
-// tap only or more) takes the wide shape, and the batched launch.
+// whether a launch with that many wide tiles (of subarrays of up to `sub`
+// elements, with one tap only or more) takes the wide shape, and the batched
+// launch.
 int doppler_tiles(const Dims& d, bool wide);
-bool doppler_wide(int P, bool sub, bool one_tap, long long wide_tiles);
+bool doppler_wide(int P, int sub, bool one_tap, long long wide_tiles);
 hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex& bi, int tiles, bool wide, bool sub,
                                   hipStream_t st);
 
