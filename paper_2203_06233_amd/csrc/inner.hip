@@ -18,6 +18,19 @@
 // leaves the pass to HBM.  It is also the more exact form: relative error of the
 // power against 64 bits 2.9e-7 -> 0.95e-7 at 12 DOF, 9.8e-7 -> 3.2e-7 at 96,
 // 1.6e-6 -> 3.7e-7 at 192 (FP32 MFMA -> split).
+//
+// The split covers the values that three BF16 terms hold: an infinite value,
+// or one that rounds to infinity in BF16 (above 3.39e38), leaves NaN in its
+// second term, and the lower terms of a value below 2^-110 are denormal, which
+// the matrix cores flush (relative error 2.7e-5 at 1e-36).  Tiles where that
+// can show are formed again from the FP32 operands on v_mfma_f32_16x16x4_f32
+// once the wave has done its tiles: those with an output that is not finite,
+// or below 2^-46 and not zero, and all of a system with weights of 2^40 and
+// more or a pair of them that are below 2^-95 and not zero.  Below 2^40 a cell
+// whose values are all under 2^-95 gives outputs under 2^-46 (192 DOF), so no
+// look at the samples is needed (one costs 4 %); forming the tiles again in the
+// loop itself takes the registers of the others (48 DOF, 32 vectors, 4096
+// blocks of 48 cells: 31 -> 40 us).
 #include <type_traits>
 
 #include "common.h"
@@ -34,6 +47,37 @@ __device__ __forceinline__ floatx4 mfma_bf16x(uint4 a, uint4 b, floatx4 c) {
 }
 
 
+// Whether a pair of weights is outside what the split and the test on its
+// outputs cover: 2^40 or more, or not zero and nothing of 2^-95 or more.
+__device__ __forceinline__ bool odd_pair(float2 a, float2 b) {
+  const float top = fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(b.x), fabsf(b.y)));
+  return (top >= 0x1p40f) | ((top < 0x1p-95f) & (top != 0.f));
+}
+
+// The lane's outputs of a range tile, rows s of steering tile t in register i:
+// power (and y) at o + s R.  Returns whether one is not finite, or below 2^-46
+// and not zero.
+template <int ST>
+__device__ __forceinline__ bool store_tile(const floatx4 (&re)[ST], const floatx4 (&im)[ST], float* __restrict__ power,
+                                           float2* __restrict__ yout, long long o, int S, int R, int lane) {
+  constexpr unsigned int kLow = (127 - 46) << 23, kInf = 0x7f800000u;
+  unsigned int out = 0;
+#pragma unroll
+  for (int t = 0; t < ST; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int s = t * 16 + 4 * (lane >> 4) + i;
+      if (s < S) {
+        const long long at = o + (long long)s * R;
+        power[at] = re[t][i] * re[t][i] + im[t][i] * im[t][i];
+        if (yout) yout[at] = make_float2(re[t][i], im[t][i]);
+        const unsigned int u = __float_as_uint(fabsf(re[t][i]) + fabsf(im[t][i]));
+        out = max(out, u == 0 ? 0u : u - kLow);
+      }
+    }
+  return out >= kInf - kLow;
+}
+
 // One system on NW waves.  LDS holds the weights as six planes
 // [re h, re m, re l, im h, im m, im l][s][d] (d padded to DP, pitch DP + 8).
 template <int ST, int DP, int NW>
@@ -44,10 +88,12 @@ __device__ __forceinline__ void inner_system(const float2* __restrict__ wts, con
   constexpr int PITCH = DP + 8;              // bf16 units per row
   constexpr int PS = SP * PITCH / 2;         // plane stride in uint32
   __shared__ __align__(16) unsigned int wp[6 * PS];
+  __shared__ int odd_w[NW];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int k = sys / d.B, b = sys - (sys / d.B) * d.B;
   const int D = d.D, S = d.S, N = d.N;
   const float2* W = wts + (long long)sys * S * D;
+  bool odd = false;
   for (int e = tid; e < SP * (DP / 2); e += 64 * NW) {
     const int s = e / (DP / 2), q = 2 * (e % (DP / 2));
     float2 w0 = make_float2(0.f, 0.f), w1 = w0;
@@ -55,6 +101,7 @@ __device__ __forceinline__ void inner_system(const float2* __restrict__ wts, con
       if (q < D) w0 = W[s * D + q];
       if (q + 1 < D) w1 = W[s * D + q + 1];
     }
+    odd |= odd_pair(w0, w1);
     unsigned int h, m, l;
     const int o = s * (PITCH / 2) + q / 2;
     split3x2(w0.x, w1.x, h, m, l);
@@ -66,6 +113,8 @@ __device__ __forceinline__ void inner_system(const float2* __restrict__ wts, con
     wp[4 * PS + o] = m;
     wp[5 * PS + o] = l;
   }
+  odd = __any(odd);
+  if (lane == 0) odd_w[wave] = odd;
   __syncthreads();
   const uint4* wp4 = reinterpret_cast<const uint4*>(wp);
   const float2* X = snap + (long long)k * D * d.R + (long long)b * N;
@@ -75,6 +124,9 @@ __device__ __forceinline__ void inner_system(const float2* __restrict__ wts, con
   // Each wave takes one range tile at a time: two tiles would share the
   // weights' fragments, but cost the registers of a workgroup per compute
   // unit (1.68 against 1.00 ms on the 32 x 256 x 16384 cube).
+  unsigned long long again = 0;  // bit rt / NW (mod 64): tile rt is to be formed from FP32
+#pragma unroll
+  for (int w = 0; w < NW; ++w) again = odd_w[w] ? ~0ULL : again;
   for (int rt = wave; rt < ntile; rt += NW) {
     const int r = rt * 16 + (lane & 15);
     const bool live = r < N;
@@ -121,20 +173,39 @@ __device__ __forceinline__ void inner_system(const float2* __restrict__ wts, con
         }
       }
     }
-    if (!live) continue;
-    const long long rr = (long long)b * N + r;
 #pragma unroll
-    for (int t = 0; t < ST; ++t)
+    for (int t = 0; t < ST; ++t) {
+      accR[t] += corR[t];
+      accI[t] += corI[t];
+    }
+    bool out = false;
+    if (live) out = store_tile<ST>(accR, accI, power, yout, (long long)k * S * d.R + (long long)b * N + r, S, d.R, lane);
+    if (__any(out)) again |= 1ULL << (rt / NW & 63);
+  }
+  if (!again) return;
+  const int l = lane_tid() & 63;  // apart from the first loop's: nothing is kept live for this
+  for (int rt = wave; rt < ntile; rt += NW) {
+    if (!(again >> (rt / NW & 63) & 1)) continue;
+    const int r = rt * 16 + (l & 15);
+    const bool live = r < N;
+    floatx4 re[ST], im[ST];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int s = t * 16 + 4 * (lane >> 4) + i;
-        if (s < S) {
-          const float re = accR[t][i] + corR[t][i], im = accI[t][i] + corI[t][i];
-          const long long o = ((long long)k * S + s) * d.R + rr;
-          power[o] = re * re + im * im;
-          if (yout) yout[o] = make_float2(re, im);
-        }
+    for (int t = 0; t < ST; ++t) re[t] = im[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int q0 = 0; q0 < D; q0 += 4) {
+      const int q = q0 + (l >> 4);
+      const float2 x = live && q < D ? X[(long long)q * d.R + r] : make_float2(0.f, 0.f);
+#pragma unroll
+      for (int t = 0; t < ST; ++t) {
+        const int s = t * 16 + (l & 15);
+        const float2 w = s < S && q < D ? W[s * D + q] : make_float2(0.f, 0.f);
+        re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, x.x, re[t], 0, 0, 0);
+        re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, x.y, re[t], 0, 0, 0);
+        im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, x.y, im[t], 0, 0, 0);
+        im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(-w.y, x.x, im[t], 0, 0, 0);
       }
+    }
+    if (live) store_tile<ST>(re, im, power, yout, (long long)k * S * d.R + (long long)b * N + r, S, d.R, l);
   }
 }
 
