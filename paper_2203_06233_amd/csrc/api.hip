@@ -377,13 +377,13 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
   struct Group {
     int lo, n, key;
     long long total;
-    int max_dof, max_steer, ty;
+    int max_dof, max_steer, ty, cells;
   };
   std::vector<Group> groups;
   for (int i = 0; i < n_probs; ++i) {
     stap::ProbDesc& pd = desc[i];
     const int key = shape_class(pd.d);
-    if (groups.empty() || groups.back().key != key) groups.push_back(Group{i, 0, key, 0, 0, 0, 0});
+    if (groups.empty() || groups.back().key != key) groups.push_back(Group{i, 0, key, 0, 0, 0, 0, pd.d.N});
     Group& g = groups.back();
     pd.sys_begin = g.total;
     g.total += (long long)pd.d.P * pd.d.B;
@@ -449,7 +449,8 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
       if (e != hipSuccess) return e;
     }
     for (const Group& g : groups) {
-      const hipError_t e = stap::launch_inner_batched(table + g.lo, g.n, g.total, g.max_dof, g.max_steer, s);
+      const hipError_t e = stap::launch_inner_batched(table + g.lo, g.n, g.total, g.max_dof, g.max_steer, prec,
+                                                      g.cells, s);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -44,9 +44,10 @@ hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex&
 hipError_t launch_fused_batched(const ProbDesc* desc, int n, long long total_sys, int max_dof, int max_steer,
                                 int prec, int refine, int ty, hipStream_t st, unsigned long long* queue);
 
-// Inner products over every system of every cube of the table.
-hipError_t launch_inner_batched(const ProbDesc* desc, int n, long long total_sys, int max_dof, int max_steer,
-                                hipStream_t st);
+// Inner products over every system of every cube of the table; cells is the
+// block length of the cube with the most work.
+hipError_t launch_inner_batched(const ProbDesc* desc, int n, long long total_sys, int max_dof, int max_steer, int prec,
+                                int cells, hipStream_t st);
 
 // X[P][D][R] <- windowed, time-staggered Doppler DFT of cube[C][P][R].
 hipError_t launch_doppler(const Dims& d, const float2* cube, float2* snap, hipStream_t st);
