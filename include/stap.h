@@ -323,8 +323,7 @@ void stap_use_graphs(int32_t enable);
 
 /* Bytes of device workspace stap_run needs for these problems (per cube:
  * snapshots, weights and info, plus the covariance and delta for D > 128,
- * FP8, or D <= 96 with S <= 32); 0 on invalid
- * arguments. */
+ * FP8, or D <= 96 with S <= 32 without refinement); 0 on invalid arguments. */
 size_t stap_workspace_size(const stap_problem* probs, int32_t n_probs);
 
 /* Validate one problem without touching the GPU (host-only check). */

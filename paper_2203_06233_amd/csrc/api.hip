@@ -182,7 +182,8 @@ size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Workspace of one cube: snapshots, weights and info (when the caller passes
 // none), and the covariance and delta where the fused kernel does not apply
-// (D > 128 or FP8) or the one-wave stage route may (D <= 96, S <= 32).
+// (D > 128 or FP8) or the one-wave stage route may (D <= 96, S <= 32, no
+// refinement).
 struct Parts {
   size_t snap, cov, delta, w, info;
   size_t total() const { return snap + cov + delta + w + info; }
@@ -191,7 +192,7 @@ Parts parts_of(const stap_problem* q) {
   const size_t P = q->n_pulse, D = (size_t)q->tdof * (q->n_chan / sub_of(q)), R = q->n_range, B = q->n_block,
                S = q->n_steer;
   const Dims d = dims_of(q);
-  const bool fused = stap::fused_supported(d) && !stap::wsolve_shape(d);
+  const bool fused = stap::fused_supported(d) && !stap::wsolve_supported(d);
   Parts p;
   p.snap = up(P * D * R * 8);
   p.cov = fused ? 0 : up(P * B * D * D * 8);

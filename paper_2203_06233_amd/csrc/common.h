@@ -37,13 +37,13 @@ struct Dims {
   int L;   // P-T+1, sub-CPI (window) length
   float eps;
   int prec, refine;
-  int corr;  // 1: the blocked solve corrects its panels (with refinement)
   long long sc, sp;  // cube strides of channel and pulse (elements)
   int train;         // stap_training
   int guard;         // guard cells per side (STAP_TRAIN_EXCLUDE)
   int tap_rel;       // 1: each tap's DFT referenced to its own first pulse
   int steer_bin;     // 1: steering vectors given per Doppler bin, [P][S][D]
   int sub;           // array elements summed into each channel C (>= 1)
+  int corr;          // 1: the blocked solve corrects its panels (with refinement)
 };
 
 // The N range cells that train block b, as two runs: cells a0 .. a0+nl-1 and

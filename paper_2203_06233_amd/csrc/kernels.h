@@ -67,7 +67,6 @@ hipError_t launch_solve(const Dims& d, const float2* cov, const float2* steer, f
 bool bsolve_supported(const Dims& d, int waves);
 // One wave per system, every block in registers: shapes D <= 96, S <= 32,
 // without refinement.
-bool wsolve_shape(const Dims& d);
 bool wsolve_supported(const Dims& d);
 hipError_t launch_wsolve(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info,
                          hipStream_t st);

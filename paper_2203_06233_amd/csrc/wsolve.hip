@@ -8,8 +8,7 @@ namespace stap {
 hipError_t launch_wsolve_s1(const Dims&, const float2*, const float2*, float2*, int*, hipStream_t);
 hipError_t launch_wsolve_s2(const Dims&, const float2*, const float2*, float2*, int*, hipStream_t);
 
-bool wsolve_shape(const Dims& d) { return d.D >= 1 && d.D <= 96 && d.S >= 1 && d.S <= 32; }
-bool wsolve_supported(const Dims& d) { return wsolve_shape(d) && d.refine == 0; }
+bool wsolve_supported(const Dims& d) { return d.D >= 1 && d.D <= 96 && d.S >= 1 && d.S <= 32 && d.refine == 0; }
 
 hipError_t launch_wsolve(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info,
                          hipStream_t st) {
