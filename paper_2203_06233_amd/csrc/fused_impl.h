@@ -56,8 +56,20 @@ __device__ __forceinline__ void fused_system(const float2* __restrict__ snap, co
 }
 
 
+// Register budgets (waves per SIMD) of the one-cube column sweep without
+// refinement that are met without spills and that the compiler's own choice
+// misses: one block column with split-BF16 covariance (12 DOF, 30 vectors, 4096
+// systems: 58.7 us with 90 registers, 52.7 with 80) and three with more than
+// 32 steering vectors on FP32 (48 DOF, 64 vectors: 346 us with 98, 316 with 96).
+template <int TY, int NB, int NVS, int MODE, bool REFINE>
+constexpr int fused_min_waves() {
+  if (TY != 16 || REFINE) return 1;
+  return NB == 1 && MODE == 1 ? 6 : NB == 3 && NVS == 4 && MODE == 0 ? 5 : 1;
+}
+
 template <int TY, int NA, int NB, int NVS, int MODE, bool REFINE>
-__global__ __launch_bounds__(16 * TY) void fused_kernel(const float2* __restrict__ snap,
+__global__ __launch_bounds__(16 * TY) __attribute__((amdgpu_waves_per_eu(fused_min_waves<TY, NB, NVS, MODE, REFINE>())))
+void fused_kernel(const float2* __restrict__ snap,
                                                         const float2* __restrict__ steer,
                                                         float2* __restrict__ wout, int* __restrict__ info_out,
                                                         Dims d) {
