@@ -1,5 +1,5 @@
 // Stage weight solve on the matrix cores: one workgroup per system reads the
-// loaded covariance from global memory and runs bsolve_system()
+// loaded covariance from global memory and runs bsolve_blocks()
 // (bsolve_impl.h), with or without FP64 refinement.
 #include "bsolve_impl.h"
 #include "kernels.h"
@@ -60,7 +60,8 @@ struct GlobalRB {
 };
 
 // With refinement and 8 waves the register allocation is capped at 128 so
-// that two systems share a compute unit.
+// that two systems share a compute unit (no more than 4 registers spill with
+// up to 3 L and 2 M slots, 26 to 170 with more).
 template <int NSL, int NSM, int NW, bool REFINE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(REFINE && NW == 8 ? 4 : 1)))
 void bsolve_kernel(const float2* __restrict__ cov,
@@ -91,8 +92,19 @@ void bsolve_kernel(const float2* __restrict__ cov,
   }
   load_steer(sl, V, d.D, d.S, am);
   for (int r = threadIdx.x; r < 16 * sl.NB; r += C::NT) L.d64[r] = 0.0;
+  float top = 0.f;  // largest diagonal element, the same on every thread
+  if (REFINE) {
+    __syncthreads();
+    for (int r = threadIdx.x & 63; r < d.D; r += 64) top = fmaxf(top, L.rdiag[r]);
+    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+  }
+  const SysScale sc(top);
+  if (REFINE) {
+#pragma unroll
+    for (int t = 0; t < NSL; ++t) al[t] = acc_scale(al[t], sc.r);  // the identity beyond D scales with the rest
+  }
   bsolve_blocks<C, REFINE>(sl, al, am, L, R, V, wout + (long long)sys * d.S * d.D,
-                           info_out ? info_out + sys : nullptr, d, nullptr);
+                           info_out ? info_out + sys : nullptr, d, nullptr, sc);
 }
 
 template <int NSL, int NSM, int NW, bool REFINE>

@@ -145,8 +145,10 @@ __device__ __forceinline__ void mma_pq(Acc& x, const Acc& P, const Acc& Qt) {
 // instruction at any priority (measured: a wave's FMA goes from 5 cycles to
 // waiting until the stream ends; beside BF16 MFMA it takes 8), so the waves'
 // products froze the diagonal factorisation that everything else waits for.
-// The product errors are those of FP32 and the FP64 refinement removes them;
-// without refinement the FP32 arithmetic stays as it is.
+// The split form is the more exact of the two: against 64 bits, one refinement
+// step, on the same factorisation, 60 DOF 1.9e-6 with FP32 products and 1.5e-6
+// split, 96 DOF 1.2e-6 and 0.8e-6, 192 DOF 8.8e-7 and 5.2e-7.  Without
+// refinement the FP32 products stay as they are.
 struct OpF32 {
   typedef Acc Frag;
   static constexpr int kB = kBlk;  // floats of a published block
@@ -219,6 +221,12 @@ struct OpSplit {
 // split terms) ahead of the loop that uses it, for all slots at once.
 __device__ __forceinline__ void pin(Acc& a) { asm volatile("" : "+v"(a.re), "+v"(a.im)); }
 
+__device__ __forceinline__ Acc acc_scale(const Acc& a, float s) {
+  Acc b;
+  b.re = a.re * s;
+  b.im = a.im * s;
+  return b;
+}
 __device__ __forceinline__ Acc acc_neg(const Acc& a) {
   Acc b;
   b.re = -a.re;
@@ -292,8 +300,9 @@ struct Diag {
 // The multipliers l_mj come from row j, as conj(A[j][m]), and not from column
 // j: row and column of a Hermitian block drift apart in the rounding of the
 // earlier columns, and products of a multiplier from the one and a row from
-// the other magnify the difference by |l| / d (the factor's backward error
-// was up to 45 times that of products which agree).  Every lane keeps a copy
+// the other magnify the difference by |l| / d (on clutter covariances the
+// factor's backward error was up to 45 times that of products which agree, and
+// the once-refined error 2 to 3 times: 96 DOF 8.1e-7, so 4.8e-7).  Every lane keeps a copy
 // of the current four rows at column m (cr, ci), updated with the same bits as
 // the rows and refreshed every fourth column through LDS, with its latency
 // once per four columns instead of once per column.  Below the diagonal A
@@ -623,12 +632,31 @@ __device__ __forceinline__ void load_steer(const Slots<C>& sl, const float2* __r
   }
 }
 
+// With refinement a system is solved as 4^-k R_L, k such that its diagonal is
+// about 1: the solution then stays in the range of the split's low terms (from
+// 2^-110) and of the pivots' square roots (from 2^-126) for any R_L (96 DOF, 64
+// vectors, elements of 4e37: error 2.7e-6 without, 5.0e-8 with; of 1e-33 four
+// systems of 128 failed).  A power of 4 keeps every bit otherwise: weights come
+// out 2^k times too large and are scaled back as they are written.
+struct SysScale {
+  float r, w;  // 4^-k, 2^-k
+  __device__ __forceinline__ explicit SysScale(float diag) {
+    const int e = (int)((__float_as_uint(diag) >> 23) & 0xffu) - 127;  // 128: not finite
+    int k = diag > 0.f && e < 128 ? max(e, -126) >> 1 : 0;
+    k = __builtin_amdgcn_readfirstlane(k);
+    r = __uint_as_float((unsigned int)(127 - 2 * k) << 23);
+    w = __uint_as_float((unsigned int)(127 - k) << 23);
+  }
+};
+
 // Solve one system (D <= 16 NB, S <= 16 NS, lslots(NB) <= NSL,
 // mslots(NB, NS) <= NSM).  al holds the wave's blocks of minus the loaded
-// covariance (identity beyond D, diagonal blocks with both triangles), am
+// covariance (identity beyond D, diagonal blocks with both triangles), with
+// REFINE times sc.r, am
 // those of -M: blocks still to be finished are kept negated, so that every
 // update adds (x -= P Q^H is -x += P Q^H) and the panel product with
-// -Linv_JJ restores the sign, all exactly.  L.rdiag holds the loaded diagonal of the diagonal blocks
+// -Linv_JJ restores the sign, all exactly.  L.rdiag holds the loaded diagonal
+// of the diagonal blocks, unscaled
 // (written by the wave that owns them) and L.d64 zeros, visible after the
 // next barrier.  With REFINE src.get(J, I) yields, on lane (m, q), R_L[16J +
 // 4q + s][16I + m], s = 0..3; it must stay readable for the whole call.  W is
@@ -640,7 +668,7 @@ template <class C, bool REFINE, class RSrc>
 __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::NSL], Acc (&am)[C::NSM],
                                               const SolveLds<C, REFINE>& L, const RSrc& src,
                                               const float2* __restrict__ steer, float2* __restrict__ W,
-                                              int* __restrict__ info, const Dims& d, float* park) {
+                                              int* __restrict__ info, const Dims& d, float* park, SysScale sc) {
   typedef typename SolveLds<C, REFINE>::Op Op;
   typedef typename Op::Frag Frag;
   constexpr int NSL = C::NSL, NSM = C::NSM, kB = Op::kB;
@@ -668,7 +696,8 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
           if (REFINE && d.corr) {
             // X = A Linv^H carries the inverse's error, |L| |Linv| times that
             // of a substitution, into everything that follows; one step of
-            // X += (A - X L^H) Linv^H takes it out
+            // X += (A - X L^H) Linv^H takes it out (96 DOF 4.8e-7, so 7e-8
+            // to 1.1e-7; 5 to 9 % of the solve)
             Acc e = al[t];
             Op::pqh(e, Op::frag(x), Op::load(L.diag, nat));
             Op::pqh(x, Op::frag(e), Q);
@@ -710,7 +739,7 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
         Op::pqh(A, P, P);
       }
       const int r = 16 * (J + 1) + m;
-      const double p64 = (double)L.rdiag[r] - (J >= 0 ? L.d64[r] : 0.0);
+      const double p64 = (double)(REFINE ? L.rdiag[r] * sc.r : L.rdiag[r]) - (J >= 0 ? L.d64[r] : 0.0);
       Acc X;
       float dm = 0.f;
       const int f = diag_factor_inv<-1, REFINE>(acc_neg(A), X, dm, p64, L.dinv, L.diag);
@@ -892,7 +921,7 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
               a3 = mfma64(qr + qi, pr + pi, a3);
             }
           }
-          const doublex4 cr = a1 - a2, ci = a3 - a1 - a2;
+          const doublex4 cr = (a1 - a2) * (double)sc.r, ci = (a3 - a1 - a2) * (double)sc.r;
           const int s = 16 * sl.mr[t] + m;
           // the slot's Z is in LDS now: its registers hold minus the
           // residual, column q + 4i in register i
@@ -975,10 +1004,10 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
       const int s = 16 * sl.mr[t] + m;
       double gam = 0.0;
       for (int J = 0; J < NB; ++J) gam += L.gpart[J * 16 * NS + s];
-      const float sc = 1.f / sqrtf((float)gam);
+      const float g = REFINE ? 1.f / sqrtf((float)gam) * sc.w : 1.f / sqrtf((float)gam);
       float2 w[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = make_float2(am[t].re[i] * sc, -am[t].im[i] * sc);
+      for (int i = 0; i < 4; ++i) w[i] = make_float2(am[t].re[i] * g, -am[t].im[i] * g);
       store4(W, s, 16 * sl.mc[t] + 4 * q, s < S, D, vecW, w);
     }
   }

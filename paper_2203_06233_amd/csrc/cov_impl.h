@@ -334,10 +334,11 @@ __device__ __forceinline__ void cov_accumulate(const float2* __restrict__ X, lon
 // delta = eps * Re tr(R_hat) / D with the trace summed in FP64.  dsum holds
 // Cfg::DP doubles, to be written again only after another barrier; every
 // thread returns the same value.  Its barrier also ends the products' use of
-// the staging buffer.
+// the staging buffer.  mean, if asked for, takes tr(R_hat) / D.
 template <class Cfg>
 __device__ __forceinline__ float cov_delta(const floatx4 (&accR)[Cfg::TPW], const int (&tI)[Cfg::TPW],
-                                           const int (&tJ)[Cfg::TPW], int D, float eps, double* dsum) {
+                                           const int (&tJ)[Cfg::TPW], int D, float eps, double* dsum,
+                                           float* mean = nullptr) {
   constexpr int TPW = Cfg::TPW;
   const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -355,6 +356,7 @@ __device__ __forceinline__ float cov_delta(const floatx4 (&accR)[Cfg::TPW], cons
   double s = 0.0;
   for (int q = lane; q < D; q += 64) s += dsum[q];
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (mean) *mean = (float)(s / (double)D);
   return (float)((double)eps * s / (double)D);
 }
 

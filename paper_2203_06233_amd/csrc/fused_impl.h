@@ -2,10 +2,12 @@
 // the loaded covariance of a (Doppler bin, training block) never leaves the
 // compute unit.
 //   phase 1  cov_accumulate() (cov_impl.h) on MFMA; the FP64 trace gives
-//            delta; the tiles are written into LDS as the packed lower
-//            triangle of R_L, reusing the snapshot staging buffer;
-//   phase 2  solve_system() (solve_impl.h) reads R_L from that packed copy,
-//            which also feeds the FP64 refinement residual.
+//            delta;
+//   phase 2  the blocked solve, bsolve_blocks() (bsolve_impl.h), starts on the
+//            accumulators (bfused_system() below), or the column sweep,
+//            solve_system() (solve_impl.h), reads the packed lower triangle of
+//            R_L that phase 1 left in LDS over the snapshot staging buffer.
+// With refinement R_L stays in LDS for the FP64 residual, as blocks or packed.
 // Compared with the stage kernels this saves the covariance round trip
 // through HBM (P*B*D*D*8 bytes written and half of it read back).
 #pragma once
@@ -164,7 +166,9 @@ __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, c
   cov_accumulate<C, true>(X, d.R, D, d.N, train_cells(d, b), lds, red, tI, tJ, accR, accI);
   Acc al[NSL], am[NSM];
   load_steer(sl, V, D, d.S, am);  // in flight across the trace
-  const float dl = cov_delta<C>(accR, tI, tJ, D, d.eps, dsum);  // its barrier retires the staging buffer
+  float mean;
+  const float dl = cov_delta<C>(accR, tI, tJ, D, d.eps, dsum, &mean);  // its barrier retires the staging buffer
+  const SysScale sc(REFINE ? mean + dl : 1.f);
 
   float* const Rb = reinterpret_cast<float*>(lds);
   const SolveLds<B, REFINE> L(lds + (REFINE ? RBYTES : 0), sl.NB, sl.NS);
@@ -174,7 +178,7 @@ __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, c
     al[t].re = accR[t];
     al[t].im = accI[t];
     if (sl.lv[t]) {
-      float* const blk = REFINE ? Rb + lblock(sl.NB, sl.lr[t], sl.lc[t]) * kBlk : L.xb + sl.lr[t] * kBlk;  // (FP32 exchange blocks)
+      float* const blk = REFINE ? Rb + lblock(sl.NB, sl.lr[t], sl.lc[t]) * kBlk : L.xb + sl.lr[t] * kBlk;
       if (sl.lr[t] == sl.lc[t]) {
         // both triangles from the lower one, diagonal real with the loading,
         // identity beyond D; a wave's LDS accesses keep their order
@@ -194,8 +198,13 @@ __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, c
           }
         }
       }
-      if (REFINE) blk_store(blk, al[t], nat);
-      al[t] = acc_neg(al[t]);
+      if (REFINE) {
+        blk_store(blk, al[t], nat);
+        // (the identity beyond D scales with the rest)
+        al[t] = acc_scale(al[t], -sc.r);
+      } else {
+        al[t] = acc_neg(al[t]);
+      }
     }
   }
   for (int r = threadIdx.x; r < 16 * sl.NB; r += B::NT) L.d64[r] = 0.0;
@@ -203,13 +212,15 @@ __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, c
   // there when it fits (their number at run time covers NS NB blocks)
   const bool park = REFINE && sl.NB + 1 >= 2 * sl.NS;
   bsolve_blocks<B, REFINE>(sl, al, am, L, LdsR{Rb, sl.NB}, V, wout + (long long)sys * d.S * D,
-                           info_out ? info_out + sys : nullptr, d, park ? Rb : nullptr);
+                           info_out ? info_out + sys : nullptr, d, park ? Rb : nullptr, sc);
 }
 
 // Register budgets (waves per SIMD) that the kernels meet with no or few
 // spills: 128 registers with 8 waves and up to 6 block columns, so that two
-// systems share a compute unit (16 registers spill), with 4 waves up to 3
-// and with one wave; 168 with 4 waves and 4 block columns and with 2 waves.
+// systems share a compute unit (7 registers spill; with 4 steering blocks 146
+// are taken, and the 97 KB of LDS leave room for one system anyway), with 4
+// waves up to 3 and with one wave; 168 with 4 waves and 4 block columns and
+// with 2 waves.
 template <int NB, int NS, int NW>
 constexpr int bfused_min_waves() {
   if (NW == 8 && NB <= 6) return 4;
