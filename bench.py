@@ -76,27 +76,36 @@ def kernel_work(wl, precision, refine):
     chol = (4.0 / 3.0) * D ** 3 * sysn
     solves = 8.0 * D * D * S * sysn
     cov_key = {"fp32": "fp32", "bf16": "bf16", "fp8": "fp8"}[precision]
+    solve_key = "bf16" if refine else "fp32"  # with refinement the block products are split into BF16 terms
+
+    def mix(nbytes, parts):
+        work = dict(bytes=nbytes)
+        for k, v in parts:
+            work[k] = work.get(k, 0.0) + v
+        return work
+
     return {
         "doppler": dict(bytes=cube_b + snap_b, fp32=5.0 * T * C * R * P * np.log2(P)),
         "covariance": {"bytes": snap_b + cov_b, cov_key: herm},
-        "solve": dict(bytes=cov_lower_b + w_b, fp32=chol + solves * (1 + refine), fp64=solves * refine),
+        "solve": mix(cov_lower_b + w_b, [(solve_key, chol + solves * (1 + refine)), ("fp64", solves * refine)]),
         # fused: snapshots in, weights out; covariance products plus the solve
-        "covariance_solve": {"bytes": snap_b + w_b, cov_key: herm,
-                             "fp32": chol + solves * (1 + refine), "fp64": solves * refine},
+        "covariance_solve": mix(snap_b + w_b, [(cov_key, herm), (solve_key, chol + solves * (1 + refine)),
+                                               ("fp64", solves * refine)]),
         "inner": {"bytes": snap_b + w_b + pw_b, "bf16": 8.0 * S * D * N * sysn},  # BF16 matrix cores on every path
     }
 
 
 def cfar_work(wl, n_ref):
     """CA-CFAR on the power map: power in (4 B) and mask out (1 B) per cell,
-    2 n_ref FP64 additions per cell."""
+    (n_ref + 22) / 4 FP32 additions per cell (two windows, sums shared by
+    eight neighbouring cells)."""
     cells = wl.n_pulse * wl.n_steer * wl.n_range
-    return {"bytes": 5 * cells, "fp64_add": 2.0 * n_ref * cells}
+    return {"bytes": 5 * cells, "fp32_add": (n_ref + 22) / 4 * cells}
 
 
-# fp64_add: plain FP64 additions, one per lane per instruction, so half the
-# FMA-counted FP64 peak
-PEAKS = {"fp32": FP32_PEAK, "bf16": BF16_PEAK, "fp8": 5.0e15, "fp64": FP64_PEAK, "fp64_add": FP64_PEAK / 2}
+# fp32_add: plain FP32 additions, one per lane per instruction and not packed,
+# so a quarter of the packed, FMA-counted FP32 peak
+PEAKS = {"fp32": FP32_PEAK, "bf16": BF16_PEAK, "fp8": 5.0e15, "fp64": FP64_PEAK, "fp32_add": FP32_PEAK / 4}
 
 
 def roofline_of(name, work, sec):

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kThreads) void cfar_kernel(const float* __restrict_
   const int H = n_ref + n_guard;        // halo per side
   const float* prow = power + (long long)row * R;
   // stage cells t0 - H .. t0 + kTile + H - 1 (zero outside the row), plus
-  // kRun zeros of look-ahead
+  // kRun values of look-ahead (read, but in no sum)
   const int nl = kTile + H + kRun, off = H + n_guard + 1, span = kTile + 2 * H;
   const bool inside = t0 >= H && t0 + kTile + H <= R;
   // staged value i is cell t0 - H + i; first and last of them in the row

@@ -30,7 +30,8 @@
 // therefore has a narrow tile (256 threads) and, where the registers allow
 // it, a wide one that needs enough cells to fill the chip:
 //                                             before    narrow     wide
-//    64 pulses, 64 channels,  4096 cells                 0.102    0.097 ms
+//    32 pulses, 32 channels, 16384 cells      0.101     0.100             ms
+//    64 pulses, 64 channels,  4096 cells      0.096     0.102    0.095
 //   128 pulses, 16 channels,  4096 cells      0.056      0.055    0.050
 //   256 pulses, 32 channels, 16384 cells      0.94       0.94     0.86
 //   512 pulses, 64 channels,  4096 cells      1.45       1.01     0.90

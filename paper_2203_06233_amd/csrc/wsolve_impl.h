@@ -3,7 +3,7 @@
 // R_L and NS = 2 blocks of steering vectors: D <= 96, S <= 32), without
 // refinement.
 //
-// The steps and the block algebra are those of bsolve_system()
+// The steps and the block algebra are those of bsolve_blocks()
 // (bsolve_impl.h): right-looking factorisation with the in-wave diagonal
 // factor-and-invert, the forward solve of the steering rows M = V^H riding
 // along as extra rows, and the back solve in row form Z L = Y^H.  What
@@ -296,15 +296,16 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
       Acc a;
       float2 v[4];
       if (I == J) {
-        // the factorisation reads a diagonal block above its diagonal, which
-        // comes from the lower triangle: element (r, c) is conj(R[c][r])
+        // the factorisation reads a diagonal block above its diagonal alone,
+        // which comes from the lower triangle: element (r, c) is conj(R[c][r])
+        const float2* const p = R + min(r, D - 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int c = 16 * J + 4 * q + i;
-          const float2 x = R[min(max(c, r), D - 1) * D + min(min(c, r), D - 1)];
-          const bool ok = c < D && r < D;
+          const float2 x = p[(I == NB - 1 ? min(c, D - 1) : c) * D];
+          const bool ok = I < NB - 1 || (c < D && r < D);
           a.re[i] = ok ? x.x : r == c ? 1.f : 0.f;
-          a.im[i] = ok && c > r ? -x.y : 0.f;
+          a.im[i] = ok ? -x.y : 0.f;
           if (c == r) rdiag[r] = a.re[i];
         }
       } else {

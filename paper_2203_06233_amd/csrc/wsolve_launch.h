@@ -9,7 +9,7 @@ namespace stap {
 namespace wsv {
 
 // Waves per SIMD that the blocks of a system leave registers for: eight a
-// block and about 60 to work with.
+// block and about 60 to work with.  With 6 block columns 94 registers spill.
 constexpr int wsolve_waves(int NB, int NS) {
   const int blocks = NB * (NB + 1) / 2 + steer_group(NB, NS) * NB;
   return blocks <= 8 ? 4 : blocks <= 13 ? 3 : 2;
