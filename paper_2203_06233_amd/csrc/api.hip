@@ -378,13 +378,13 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
   struct Group {
     int lo, n, key;
     long long total;
-    int max_dof, max_steer, ty, cells;
+    int max_dof, max_steer, ty, cells, level;
   };
   std::vector<Group> groups;
   for (int i = 0; i < n_probs; ++i) {
     stap::ProbDesc& pd = desc[i];
     const int key = shape_class(pd.d);
-    if (groups.empty() || groups.back().key != key) groups.push_back(Group{i, 0, key, 0, 0, 0, 0, pd.d.N});
+    if (groups.empty() || groups.back().key != key) groups.push_back(Group{i, 0, key, 0, 0, 0, 0, pd.d.N, 0});
     Group& g = groups.back();
     pd.sys_begin = g.total;
     g.total += (long long)pd.d.P * pd.d.B;
@@ -397,6 +397,7 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
     cls.D = g.max_dof;
     cls.S = g.max_steer;
     g.ty = fused_variant(cls);
+    g.level = cls.refine == 0 ? 0 : cls.corr ? 2 : 1;
   }
   const int prec = probs[0].precision, refine = probs[0].refine_steps;
 
@@ -445,8 +446,8 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
     }
     for (size_t i = 0; i < groups.size(); ++i) {
       const Group& g = groups[i];
-      const hipError_t e = stap::launch_fused_batched(table + g.lo, g.n, g.total, g.max_dof, g.max_steer, prec, refine,
-                                                      g.ty, s, queue + i);
+      const hipError_t e = stap::launch_fused_batched(table + g.lo, g.n, g.total, g.max_dof, g.max_steer, prec,
+                                                      g.level, g.ty, s, queue + i);
       if (e != hipSuccess) return e;
     }
     for (const Group& g : groups) {
@@ -466,7 +467,7 @@ stap_status run_impl(const stap_problem* probs, int32_t n_probs, const stap_cf32
   if (hipGetDevice(&dev) != hipSuccess) return STAP_ERR_HIP;
   std::string key = std::to_string(dev) + "|" + std::to_string((uintptr_t)ws0) + "|" +
                     std::to_string(prec) + "|" + std::to_string(refine);
-  for (const Group& g : groups) key += "|v" + std::to_string(g.ty);
+  for (const Group& g : groups) key += "|v" + std::to_string(g.ty) + "," + std::to_string(g.level);
   for (const Dop& x : dop) key += x.wide ? (x.sub ? "|ws" : "|w") : (x.sub ? "|s" : "|n");
   for (auto& pd : desc) {
     key += "|" + std::to_string(pd.d.C) + "," + std::to_string(pd.d.P) + "," + std::to_string(pd.d.R) + "," +

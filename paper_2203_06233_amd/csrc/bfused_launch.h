@@ -16,30 +16,38 @@ namespace bfused {
 // register blocks per wave for NB block columns and NS steering blocks
 constexpr int nsl(int NB, int NW) { return (NB * (NB + 1) / 2 + NW - 1) / NW; }
 constexpr int nsm(int NB, int NS, int NW) { return (NS * NB + NW - 1) / NW; }
+// Whether the corrected form exists: not for 6 block columns on four waves,
+// which run where a tuned entry asked for them and never by default.
+constexpr bool has_corrected(int NB, int NW) { return NB != 6 || NW == 8; }
 
 template <int NB, int NS, int NW, int MODE>
 hipError_t go1(const Dims& d, const float2* snap, const float2* steer, float2* w, int* info, hipStream_t st) {
   constexpr int L = nsl(NB, NW), M = nsm(NB, NS, NW);
+  const dim3 grid(d.P * d.B), block(64 * NW);
   if (d.refine == 0)
-    hipLaunchKernelGGL((bfused_kernel<NB, NS, L, M, NW, MODE, false>), dim3(d.P * d.B), dim3(64 * NW), 0, st, snap, steer,
-                       w, info, d);
+    hipLaunchKernelGGL((bfused_kernel<NB, NS, L, M, NW, MODE, kPlain>), grid, block, 0, st, snap, steer, w, info, d);
+  else if (d.corr && has_corrected(NB, NW))
+    hipLaunchKernelGGL((bfused_kernel<NB, NS, L, M, NW, MODE, has_corrected(NB, NW) ? kCorrected : kRefined>), grid, block,
+                       0, st, snap, steer, w, info, d);
   else
-    hipLaunchKernelGGL((bfused_kernel<NB, NS, L, M, NW, MODE, true>), dim3(d.P * d.B), dim3(64 * NW), 0, st, snap, steer,
-                       w, info, d);
+    hipLaunchKernelGGL((bfused_kernel<NB, NS, L, M, NW, MODE, kRefined>), grid, block, 0, st, snap, steer, w, info, d);
   return hipGetLastError();
 }
 
 template <int NB, int NS, int NW, int MODE>
-hipError_t gob(const ProbDesc* desc, int n, long long total, int refine, hipStream_t st, unsigned long long* queue) {
+hipError_t gob(const ProbDesc* desc, int n, long long total, int level, hipStream_t st, unsigned long long* queue) {
   constexpr int L = nsl(NB, NW), M = nsm(NB, NS, NW);
   // enough workgroups to fill every CU a few times over, never more than systems
   const long long want = 256LL * (16 / NW);
   const dim3 grid((unsigned)(total < want ? total : want)), block(64 * NW);
-  if (refine == 0)
-    hipLaunchKernelGGL((bfused_batched_kernel<NB, NS, L, M, NW, MODE, false>), grid, block, 0, st, desc, n, total,
+  if (level == kPlain)
+    hipLaunchKernelGGL((bfused_batched_kernel<NB, NS, L, M, NW, MODE, kPlain>), grid, block, 0, st, desc, n, total,
                        queue);
+  else if (level == kCorrected && has_corrected(NB, NW))
+    hipLaunchKernelGGL((bfused_batched_kernel<NB, NS, L, M, NW, MODE, has_corrected(NB, NW) ? kCorrected : kRefined>),
+                       grid, block, 0, st, desc, n, total, queue);
   else
-    hipLaunchKernelGGL((bfused_batched_kernel<NB, NS, L, M, NW, MODE, true>), grid, block, 0, st, desc, n, total,
+    hipLaunchKernelGGL((bfused_batched_kernel<NB, NS, L, M, NW, MODE, kRefined>), grid, block, 0, st, desc, n, total,
                        queue);
   return hipGetLastError();
 }
@@ -95,10 +103,10 @@ hipError_t single(const Dims& d, const float2* snap, const float2* steer, float2
 }
 
 template <int MODE>
-hipError_t batched(const ProbDesc* desc, int n, long long total, int max_dof, int max_steer, int refine, int waves,
+hipError_t batched(const ProbDesc* desc, int n, long long total, int max_dof, int max_steer, int level, int waves,
                    hipStream_t st, unsigned long long* queue) {
   return pick<MODE>(max_dof, max_steer, waves, [&](auto nb, auto ns, auto nw) {
-    return gob<decltype(nb)::value, decltype(ns)::value, decltype(nw)::value, MODE>(desc, n, total, refine, st,
+    return gob<decltype(nb)::value, decltype(ns)::value, decltype(nw)::value, MODE>(desc, n, total, level, st,
                                                                                    queue);
   });
 }

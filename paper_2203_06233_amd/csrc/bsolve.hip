@@ -62,8 +62,8 @@ struct GlobalRB {
 // With refinement and 8 waves the register allocation is capped at 128 so
 // that two systems share a compute unit (no more than 4 registers spill with
 // up to 3 L and 2 M slots, 26 to 170 with more).
-template <int NSL, int NSM, int NW, bool REFINE>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(REFINE && NW == 8 ? 4 : 1)))
+template <int NSL, int NSM, int NW, int LEVEL>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(LEVEL != kPlain && NW == 8 ? 4 : 1)))
 void bsolve_kernel(const float2* __restrict__ cov,
                                                          const float2* __restrict__ steer,
                                                          float2* __restrict__ wout, int* __restrict__ info_out,
@@ -75,9 +75,12 @@ void bsolve_kernel(const float2* __restrict__ cov,
   const float2* const V = steer + steer_offset(d, sys);
   const GlobalRB R{A, d.D, rows16(A, d.D)};
   const Slots<C> sl(d.D, d.S, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
-  const SolveLds<C, REFINE> L(lds, sl.NB, sl.NS);
+  const SolveLds<C, LEVEL> L(lds, sl.NB, sl.NS);
   const int m = lane_tid() & 15, q = (lane_tid() & 63) >> 4;
   Acc al[NSL], am[NSM];
+  float top = 0.f;  // with refinement: the lane's largest of every 64th diagonal element
+  if (LEVEL != kPlain)
+    for (int r = threadIdx.x & 63; r < d.D; r += 64) top = fmaxf(top, A[r * (d.D + 1)].x);
 #pragma unroll
   for (int t = 0; t < NSL; ++t) {
     al[t] = acc_zero();
@@ -92,38 +95,35 @@ void bsolve_kernel(const float2* __restrict__ cov,
   }
   load_steer(sl, V, d.D, d.S, am);
   for (int r = threadIdx.x; r < 16 * sl.NB; r += C::NT) L.d64[r] = 0.0;
-  float top = 0.f;  // largest diagonal element, the same on every thread
-  if (REFINE) {
-    __syncthreads();
-    for (int r = threadIdx.x & 63; r < d.D; r += 64) top = fmaxf(top, L.rdiag[r]);
-    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-  }
+  for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
   const SysScale sc(top);
-  if (REFINE) {
+  if (LEVEL != kPlain) {
 #pragma unroll
     for (int t = 0; t < NSL; ++t) al[t] = acc_scale(al[t], sc.r);  // the identity beyond D scales with the rest
   }
-  bsolve_blocks<C, REFINE>(sl, al, am, L, R, V, wout + (long long)sys * d.S * d.D,
-                           info_out ? info_out + sys : nullptr, d, nullptr, sc);
+  bsolve_blocks<C, LEVEL>(sl, al, am, L, R, V, wout + (long long)sys * d.S * d.D, info_out ? info_out + sys : nullptr,
+                          d, nullptr, sc);
 }
 
-template <int NSL, int NSM, int NW, bool REFINE>
+template <int NSL, int NSM, int NW, int LEVEL>
 hipError_t go_r(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info, hipStream_t st) {
-  const size_t lds = BCfg<NSL, NSM, NW>::lds_bytes((d.D + 15) / 16, (d.S + 15) / 16, REFINE);
+  const size_t lds = BCfg<NSL, NSM, NW>::lds_bytes((d.D + 15) / 16, (d.S + 15) / 16, LEVEL);
   if (lds > 48 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsolve_kernel<NSL, NSM, NW, REFINE>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsolve_kernel<NSL, NSM, NW, LEVEL>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((bsolve_kernel<NSL, NSM, NW, REFINE>), dim3(d.P * d.B), dim3(64 * NW), lds, st, cov, steer, w,
+  hipLaunchKernelGGL((bsolve_kernel<NSL, NSM, NW, LEVEL>), dim3(d.P * d.B), dim3(64 * NW), lds, st, cov, steer, w,
                      info, d);
   return hipGetLastError();
 }
 
 template <int NSL, int NSM, int NW>
 hipError_t go(const Dims& d, const float2* cov, const float2* steer, float2* w, int* info, hipStream_t st) {
-  return d.refine == 0 ? go_r<NSL, NSM, NW, false>(d, cov, steer, w, info, st)
-                       : go_r<NSL, NSM, NW, true>(d, cov, steer, w, info, st);
+  if (d.refine == 0) return go_r<NSL, NSM, NW, kPlain>(d, cov, steer, w, info, st);
+  if constexpr (NW != 4)  // four waves run where they were asked for, the corrected form where nothing was
+    if (d.corr) return go_r<NSL, NSM, NW, kCorrected>(d, cov, steer, w, info, st);
+  return go_r<NSL, NSM, NW, kRefined>(d, cov, steer, w, info, st);
 }
 
 template <int NW>

@@ -242,18 +242,20 @@ __device__ __forceinline__ double bcast64(double v, int lane) {
 }
 
 // State of the in-wave factorisation and inversion of a 16 x 16 diagonal
-// block.  KEEP: the factor itself goes to LDS as well.
-template <bool KEEP>
+// block.  CORR: the multipliers come from the rows of A, and the factor itself
+// goes to LDS as well.
+template <bool CORR>
 struct Diag {
-  static constexpr bool kKeep = KEEP;
+  static constexpr bool kCorr = CORR;
   Acc A;           // row m: columns > j of A, columns <= j of Y
-  floatx4 cr, ci;  // conjugates of rows 4 (j / 4) .. + 3 of A at column m, on every lane
+  floatx4 cr, ci;  // columns 4 (j / 4) .. + 3 of A at row m, on every lane; with CORR the
+                   // conjugates of rows 4 (j / 4) .. + 3 at column m instead
   float rs;        // 1 / d_j of the column to come
   float rsm;       // 1 / d_m
   int fail;
   double p64;      // FP64 Schur diagonal of row m (on the lane holding (m, m))
-  float* rows;     // LDS scratch of kBlk floats, 16-byte aligned
-  float* keep;     // with KEEP: kBlk floats of LDS that take the factor below its diagonal, zero
+  float* rows;     // with CORR: LDS scratch of kBlk floats, 16-byte aligned
+  float* keep;     // with CORR: kBlk floats of LDS that take the factor below its diagonal, zero
                    // elsewhere: real part of column j, row m at 16 j + m, imaginary part 256 further
   int m, q;
 };
@@ -262,9 +264,10 @@ struct Diag {
 // and Y, l = lx + i ly: the row broadcast is a DPP operand of the FMA (the
 // compiler folds DPP moves into multiplications but not into FMAs, and
 // separate moves are a third of the column's instructions).  Per value the
-// order is fma(-lx, b, fma(+-ly, b', v)).  The copies c of rows j + 1 .. take
-// c -= conj(l of that row) a, a = ax + i ay the lane's own copy of row j, in
-// the same order, which gives them the bits of the rows that they copy.
+// order is fma(-lx, b, fma(+-ly, b', v)).  The copies (c, e) of columns take
+// part in the row update (STAP_COLS); copies of rows (STAP_ROWS) take c -=
+// conj(l of that row) a, a = ax + i ay the lane's own copy of row j, in the
+// same order, which gives them the bits of the rows that they copy.
 // l is zero on row j itself, so the broadcast reads the row's old value
 // whatever has been written, and every register's uses are at least 4
 // instructions apart (DPP reads need two wait states after a write); the
@@ -280,14 +283,17 @@ struct Diag {
 #define STAP_C2(N) "v_fmac_f32_dpp %[e" N "], %[ly], %[ax]" STAP_DPP("j" N)
 #define STAP_C3(N) "v_fmac_f32_dpp %[c" N "], -%[lx], %[ax]" STAP_DPP("j" N)
 #define STAP_C4(N) "v_fmac_f32_dpp %[e" N "], -%[lx], %[ay]" STAP_DPP("j" N)
-#define STAP_COLS(C1, C2, C3, C4)                                                                          \
+#define STAP_ASM(C1, C2, C3, C4, ...)                                                                      \
   asm("s_nop 1\n" C1 STAP_ROWUPD(STAP_P1) C2 STAP_ROWUPD(STAP_P2) C3 STAP_ROWUPD(STAP_P3) C4               \
           STAP_ROWUPD(STAP_P4) "s_nop 1"                                                                   \
       : [r0] "+v"(ar0), [r1] "+v"(ar1), [r2] "+v"(ar2), [r3] "+v"(ar3), [i0] "+v"(ai0), [i1] "+v"(ai1),     \
         [i2] "+v"(ai2), [i3] "+v"(ai3), [c1] "+v"(cr1), [c2] "+v"(cr2), [c3] "+v"(cr3), [e1] "+v"(ci1),     \
         [e2] "+v"(ci2), [e3] "+v"(ci3)                                                                     \
-      : [lx] "v"(lx), [ly] "v"(ly), [ax] "v"(ax), [ay] "v"(ay), [j] "n"(j), [j1] "n"(4 * jq + 1),           \
-        [j2] "n"(4 * jq + 2), [j3] "n"(4 * jq + 3))
+      : [lx] "v"(lx), [ly] "v"(ly), [j] "n"(j), ##__VA_ARGS__)
+#define STAP_COLS(C1, C2, C3, C4) STAP_ASM(C1, C2, C3, C4)
+#define STAP_ROWS(C1, C2, C3, C4)                                                                          \
+  STAP_ASM(C1, C2, C3, C4, [ax] "v"(ax), [ay] "v"(ay), [j1] "n"(4 * jq + 1), [j2] "n"(4 * jq + 2),          \
+           [j3] "n"(4 * jq + 3))
 
 // Column j of diag_factor_inv().  The inverse is formed in place: once the
 // multipliers l_mj of column j are taken, A's column j is dead and Y's column
@@ -297,16 +303,20 @@ struct Diag {
 // of row j records 1 / d_j for the final scaling.  What is left above the
 // diagonal at the end is dropped by diag_end().
 //
-// The multipliers l_mj come from row j, as conj(A[j][m]), and not from column
-// j: row and column of a Hermitian block drift apart in the rounding of the
-// earlier columns, and products of a multiplier from the one and a row from
-// the other magnify the difference by |l| / d (on clutter covariances the
-// factor's backward error was up to 45 times that of products which agree, and
-// the once-refined error 2 to 3 times: 96 DOF 8.1e-7, so 4.8e-7).  Every lane keeps a copy
-// of the current four rows at column m (cr, ci), updated with the same bits as
-// the rows and refreshed every fourth column through LDS, with its latency
-// once per four columns instead of once per column.  Below the diagonal A
-// itself is never read.
+// The multipliers of a column are read from a copy of the current four
+// columns that every lane of a row keeps (cr, ci), updated like A itself and
+// refreshed every fourth column: a cross-lane read through the LDS pipe, with
+// its latency, once per four columns instead of once per column.
+//
+// With CORR the multipliers l_mj come from row j instead, as conj(A[j][m]): row
+// and column of a Hermitian block drift apart in the rounding of the earlier
+// columns, and products of a multiplier from the one and a row from the other
+// magnify the difference by |l| / d (on clutter covariances the factor's
+// backward error was up to 45 times that of products which agree, and the
+// once-refined error 2 to 3 times: 96 DOF 8.1e-7, so 4.8e-7).  The copies are
+// then of the current four rows, with their very bits, and below the diagonal
+// A itself is never read.  Results that are not refined, and those of tuned
+// shapes, keep the columns' rounding, which the systems' conditioning shows.
 //
 // The pivot is taken in FP64: every lane keeps, for its row m, p64 =
 // (loaded diagonal R_mm) - (sum over earlier block columns of |L_mk|^2, FP64
@@ -326,7 +336,7 @@ __device__ __forceinline__ void diag_pivot(S& s) {
 template <int j, class S>
 __device__ __forceinline__ void diag_col(S& s) {
   constexpr int jq = j >> 2, ji = j & 3;
-  if constexpr (ji == 0) {
+  if constexpr (ji == 0 && S::kCorr) {
     // all rows go out, which spares a mask; a wave's LDS accesses keep their order
     *reinterpret_cast<floatx4*>(s.rows + 16 * s.m + 4 * s.q) = s.A.re;
     *reinterpret_cast<floatx4*>(s.rows + 256 + 16 * s.m + 4 * s.q) = s.A.im;
@@ -335,14 +345,20 @@ __device__ __forceinline__ void diag_col(S& s) {
       s.cr[i] = s.rows[16 * (4 * jq + i) + s.m];
       s.ci[i] = -s.rows[256 + 16 * (4 * jq + i) + s.m];
     }
+  } else if constexpr (ji == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s.cr[i] = __shfl(s.A.re[i], s.m + 16 * jq);
+      s.ci[i] = __shfl(s.A.im[i], s.m + 16 * jq);
+    }
   }
   const float rs = s.rs, r2 = rs * rs;
-  const float ax = s.m > j ? s.cr[ji] : 0.f, ay = s.m > j ? s.ci[ji] : 0.f;  // conj(A[j][m])
+  const float ax = s.m > j ? s.cr[ji] : 0.f, ay = s.m > j ? s.ci[ji] : 0.f;  // A[m][j] or conj(A[j][m])
   const float lx = ax * r2, ly = ay * r2;                                    // l_mj / d_j
   s.rsm = (s.m == j) ? rs : s.rsm;
-  // l_mj = conj(A[j][m]) / d_j in FP32, squared and summed in FP64 for row m
+  // l_mj in FP32, squared and summed in FP64 for row m
   const float lr = ax * rs, li = ay * rs;
-  if (S::kKeep) {  // the four lanes of row m write the same
+  if constexpr (S::kCorr) {  // the four lanes of row m write the same
     s.keep[16 * j + s.m] = lr;
     s.keep[256 + 16 * j + s.m] = li;
   }
@@ -354,16 +370,29 @@ __device__ __forceinline__ void diag_col(S& s) {
   float ai0 = s.A.im[0], ai1 = s.A.im[1], ai2 = s.A.im[2], ai3 = s.A.im[3];
   float cr1 = s.cr[1], cr2 = s.cr[2], cr3 = s.cr[3], ci1 = s.ci[1], ci2 = s.ci[2], ci3 = s.ci[3];
   // A[m][c] -= l_mj conj(l_cj) = (A[m][j] / d_j^2) A[j][c], and Y likewise
-  if constexpr (ji == 0)
-    STAP_COLS(STAP_C1("1") STAP_C1("2") STAP_C1("3"), STAP_C2("1") STAP_C2("2") STAP_C2("3"),
-              STAP_C3("1") STAP_C3("2") STAP_C3("3"), STAP_C4("1") STAP_C4("2") STAP_C4("3"));
-  else if constexpr (ji == 1)
-    STAP_COLS(STAP_C1("2") STAP_C1("3"), STAP_C2("2") STAP_C2("3"), STAP_C3("2") STAP_C3("3"),
-              STAP_C4("2") STAP_C4("3"));
-  else if constexpr (ji == 2)
-    STAP_COLS(STAP_C1("3"), STAP_C2("3"), STAP_C3("3"), STAP_C4("3"));
-  else
+  if constexpr (ji == 3)
     STAP_COLS("", "", "", "");
+  else if constexpr (S::kCorr && ji == 0)
+    STAP_ROWS(STAP_C1("1") STAP_C1("2") STAP_C1("3"), STAP_C2("1") STAP_C2("2") STAP_C2("3"),
+              STAP_C3("1") STAP_C3("2") STAP_C3("3"), STAP_C4("1") STAP_C4("2") STAP_C4("3"));
+  else if constexpr (S::kCorr && ji == 1)
+    STAP_ROWS(STAP_C1("2") STAP_C1("3"), STAP_C2("2") STAP_C2("3"), STAP_C3("2") STAP_C3("3"),
+              STAP_C4("2") STAP_C4("3"));
+  else if constexpr (S::kCorr)
+    STAP_ROWS(STAP_C1("3"), STAP_C2("3"), STAP_C3("3"), STAP_C4("3"));
+  else if constexpr (ji == 0)
+    STAP_COLS(STAP_P1("%[c1]", "%[e1]") STAP_P1("%[c2]", "%[e2]") STAP_P1("%[c3]", "%[e3]"),
+              STAP_P2("%[c1]", "%[e1]") STAP_P2("%[c2]", "%[e2]") STAP_P2("%[c3]", "%[e3]"),
+              STAP_P3("%[c1]", "%[e1]") STAP_P3("%[c2]", "%[e2]") STAP_P3("%[c3]", "%[e3]"),
+              STAP_P4("%[c1]", "%[e1]") STAP_P4("%[c2]", "%[e2]") STAP_P4("%[c3]", "%[e3]"));
+  else if constexpr (ji == 1)
+    STAP_COLS(STAP_P1("%[c2]", "%[e2]") STAP_P1("%[c3]", "%[e3]"),
+              STAP_P2("%[c2]", "%[e2]") STAP_P2("%[c3]", "%[e3]"),
+              STAP_P3("%[c2]", "%[e2]") STAP_P3("%[c3]", "%[e3]"),
+              STAP_P4("%[c2]", "%[e2]") STAP_P4("%[c3]", "%[e3]"));
+  else
+    STAP_COLS(STAP_P1("%[c3]", "%[e3]"), STAP_P2("%[c3]", "%[e3]"), STAP_P3("%[c3]", "%[e3]"),
+              STAP_P4("%[c3]", "%[e3]"));
   s.A.re = floatx4{ar0, ar1, ar2, ar3};
   s.A.im = floatx4{ai0, ai1, ai2, ai3};
   s.cr = floatx4{s.cr[0], cr1, cr2, cr3};
@@ -385,10 +414,12 @@ __device__ __forceinline__ void diag_cols(S& s) {
 #undef STAP_C2
 #undef STAP_C3
 #undef STAP_C4
+#undef STAP_ASM
 #undef STAP_COLS
+#undef STAP_ROWS
 
 template <class S>
-__device__ __forceinline__ void diag_begin(S& s, const Acc& A, double p64, float* rows, float* keep = nullptr) {
+__device__ __forceinline__ void diag_begin(S& s, const Acc& A, double p64, float* rows = nullptr, float* keep = nullptr) {
   const int l = lane_tid() & 63;
   s.A = A;
   s.rows = rows;
@@ -415,28 +446,28 @@ __device__ __forceinline__ Acc diag_end(const S& s) {
   return X;
 }
 
-// Factor the Hermitian 16 x 16 block A (of which the upper triangle is read)
-// as L L^H inside one wave and return X = SIGN L^-1 (lower triangular) and,
-// with KEEP, leave L in LDS at keep, but for its diagonal, which dm returns
-// (row m's element on the lanes of row m).  Column j: pivot d_j =
-// sqrt(A[j][j]) (taken in FP64 as above, p64 the lane's starting value for
-// its row: loaded diagonal minus the earlier block columns), l_mj =
-// conj(A[j][m]) / d_j for m > j, then A[m][c] -= l_mj conj(l_cj) for m, c >
-// j; the inverse is accumulated as X <- L_j^-1 X with L_j the identity
-// carrying column j of L (row j of X divided by d_j, then row m -= l_mj row
-// j), the row divisions deferred.  Row j of A and X lives in the same 16-lane
-// row of the wave (a DPP broadcast).  Returns 0 or the 1-based index of the
-// first non-positive pivot.  The wave runs at raised priority: the other
-// waves of its system wait for it.
-template <int SIGN, bool KEEP>
+// Factor the Hermitian 16 x 16 block A (full, both triangles; with CORR the
+// upper one is read) as L L^H inside one wave and return X = SIGN L^-1 (lower
+// triangular) and, with CORR, leave L in LDS at keep, but for its diagonal,
+// which dm returns (row m's element on the lanes of row m).  Column j: pivot
+// d_j = sqrt(A[j][j]) (taken in FP64 as above, p64 the lane's starting value
+// for its row: loaded diagonal minus the earlier block columns), l_mj =
+// A[m][j] / d_j for m > j, then A[m][c] -= l_mj conj(l_cj) for m, c > j; the
+// inverse is accumulated as X <- L_j^-1 X with L_j the identity carrying
+// column j of L (row j of X divided by d_j, then row m -= l_mj row j), the row
+// divisions deferred.  conj(l_cj) is read as A[j][c] from row j, which lives in
+// the same 16-lane row of the wave (a DPP broadcast).  Returns 0 or the 1-based
+// index of the first non-positive pivot.  The wave runs at raised priority:
+// the other waves of its system wait for it.
+template <int SIGN, bool CORR>
 __device__ __forceinline__ int diag_factor_inv(const Acc& A, Acc& X, float& dm, double p64, float* rows, float* keep) {
-  Diag<KEEP> s;
+  Diag<CORR> s;
   diag_begin(s, A, p64, rows, keep);
   __builtin_amdgcn_s_setprio(3);
   diag_cols<0>(s);
   __builtin_amdgcn_s_setprio(0);
   X = diag_end<SIGN>(s);
-  if (KEEP) dm = 1.f / s.rsm;
+  if (CORR) dm = 1.f / s.rsm;
   return s.fail;
 }
 
@@ -463,6 +494,11 @@ __device__ __forceinline__ double blk_row_norm2(const Acc& x) {
   return p;
 }
 
+// Level of refinement of a blocked solve: none, FP64 refinement, and FP64
+// refinement with the corrected factorisation (rows' multipliers in the
+// diagonal blocks, panels corrected for the error of the inverse).
+constexpr int kPlain = 0, kRefined = 1, kCorrected = 2;
+
 // Static layout of one system with NB block columns of R_L and NS block rows
 // of steering vectors (both run-time), NW waves, and per wave NSL register
 // slots for L blocks and NSM for M blocks (compile time).  L blocks are
@@ -488,21 +524,21 @@ struct BCfg {
   // owner; 96 DOF, 64 vectors, 128 x 32 systems 1078 and 1035 us; 96 DOF, 16
   // vectors 7.13 and 7.30 ms).
   static constexpr bool kOwnerSplits = NSM > 2;
-  // LDS: exchange blocks (NB + NS + 1 for the factorisation, one more with
-  // refinement; two times NB
+  // LDS: exchange blocks (NB + NS + 1 for the factorisation, one more where
+  // it is corrected; two times NB
   // blocks of L and NS for the solves; with refinement, all NS NB blocks
   // of Z in FP32 for the residual), the gamma
   // partials [NB][16 NS] (FP64), a flag, the FP64 row sums of |L|^2 over the
   // finished block columns [16 NB] and the loaded diagonal [16 NB] (for the
   // FP64 pivots)
-  __host__ __device__ static constexpr size_t xbytes(int NB, int NS, bool refine) {
-    const size_t kB = refine ? OpSplit::kB : OpF32::kB;
-    const size_t f = (NB + NS + (refine ? 2 : 1)) * kB * 4, s = (2 * NB * (kOwnerSplits ? kB : kBlk) + NS * kB) * 4;
-    const size_t z = refine ? (size_t)NS * NB * kBlk * 4 : 0;
+  __host__ __device__ static constexpr size_t xbytes(int NB, int NS, int level) {
+    const size_t kB = level ? OpSplit::kB : OpF32::kB;
+    const size_t f = (NB + NS + (level == kCorrected ? 2 : 1)) * kB * 4, s = (2 * NB * (kOwnerSplits ? kB : kBlk) + NS * kB) * 4;
+    const size_t z = level ? (size_t)NS * NB * kBlk * 4 : 0;
     return f > s ? (f > z ? f : z) : (s > z ? s : z);
   }
-  __host__ __device__ static constexpr size_t lds_bytes(int NB, int NS, bool refine) {
-    return xbytes(NB, NS, refine) + (size_t)NB * 16 * NS * 8 + 16 + (size_t)NB * 16 * (8 + 4);
+  __host__ __device__ static constexpr size_t lds_bytes(int NB, int NS, int level) {
+    return xbytes(NB, NS, level) + (size_t)NB * 16 * NS * 8 + 16 + (size_t)NB * 16 * (8 + 4);
   }
 };
 
@@ -543,13 +579,13 @@ struct Slots {
 // Number of L block (I, J) in that order.
 __device__ __forceinline__ int lblock(int NB, int I, int J) { return J * NB - J * (J - 1) / 2 + (I - J); }
 
-// The LDS regions of a system (lds_bytes(NB, NS, REFINE) at xlds).
-template <class C, bool REFINE>
+// The LDS regions of a system (lds_bytes(NB, NS, LEVEL) at xlds).
+template <class C, int LEVEL>
 struct SolveLds {
-  typedef std::conditional_t<REFINE, OpSplit, OpF32> Op;
+  typedef std::conditional_t<LEVEL != kPlain, OpSplit, OpF32> Op;
   float* xb;      // exchange blocks
   float* dinv;    // minus the inverse of the current diagonal block's factor
-  float* diag;    // that factor (with refinement)
+  float* diag;    // that factor (kCorrected)
   double* gpart;  // gamma partials
   int* sflag;     // pivot status
   double* d64;    // FP64 row sums of |L|^2
@@ -558,7 +594,7 @@ struct SolveLds {
     xb = reinterpret_cast<float*>(xlds);
     dinv = xb + (size_t)(NB + NS) * Op::kB;
     diag = dinv + Op::kB;
-    gpart = reinterpret_cast<double*>(xlds + C::xbytes(NB, NS, REFINE));
+    gpart = reinterpret_cast<double*>(xlds + C::xbytes(NB, NS, LEVEL));
     sflag = reinterpret_cast<int*>(gpart + NB * 16 * NS);
     d64 = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(sflag) + 16);
     rdiag = reinterpret_cast<float*>(d64 + NB * 16);
@@ -652,24 +688,25 @@ struct SysScale {
 // Solve one system (D <= 16 NB, S <= 16 NS, lslots(NB) <= NSL,
 // mslots(NB, NS) <= NSM).  al holds the wave's blocks of minus the loaded
 // covariance (identity beyond D, diagonal blocks with both triangles), with
-// REFINE times sc.r, am
+// refinement times sc.r, am
 // those of -M: blocks still to be finished are kept negated, so that every
 // update adds (x -= P Q^H is -x += P Q^H) and the panel product with
 // -Linv_JJ restores the sign, all exactly.  L.rdiag holds the loaded diagonal
 // of the diagonal blocks, unscaled
 // (written by the wave that owns them) and L.d64 zeros, visible after the
-// next barrier.  With REFINE src.get(J, I) yields, on lane (m, q), R_L[16J +
+// next barrier.  With refinement src.get(J, I) yields, on lane (m, q), R_L[16J +
 // 4q + s][16I + m], s = 0..3; it must stay readable for the whole call.  W is
 // this system's [S][D] output, info its status word (may be null).  park
 // (may be null) is LDS of at least NS NB blocks that is free once the last
 // residual has been formed (the source, when it lives in LDS): the last
 // refinement step keeps u there instead of in W.
-template <class C, bool REFINE, class RSrc>
+template <class C, int LEVEL, class RSrc>
 __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::NSL], Acc (&am)[C::NSM],
-                                              const SolveLds<C, REFINE>& L, const RSrc& src,
+                                              const SolveLds<C, LEVEL>& L, const RSrc& src,
                                               const float2* __restrict__ steer, float2* __restrict__ W,
                                               int* __restrict__ info, const Dims& d, float* park, SysScale sc) {
-  typedef typename SolveLds<C, REFINE>::Op Op;
+  constexpr bool REFINE = LEVEL != kPlain, CORR = LEVEL == kCorrected;
+  typedef typename SolveLds<C, LEVEL>::Op Op;
   typedef typename Op::Frag Frag;
   constexpr int NSL = C::NSL, NSM = C::NSM, kB = Op::kB;
   const int D = d.D, S = d.S, NB = sl.NB, NS = sl.NS;
@@ -693,7 +730,7 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
         if (sl.lv[t] && sl.lc[t] == J && sl.lr[t] != J) {
           Acc x = acc_zero();
           Op::pqh(x, Op::frag(al[t]), Q);
-          if (REFINE && d.corr) {
+          if (CORR) {
             // X = A Linv^H carries the inverse's error, |L| |Linv| times that
             // of a substitution, into everything that follows; one step of
             // X += (A - X L^H) Linv^H takes it out (96 DOF 4.8e-7, so 7e-8
@@ -742,9 +779,9 @@ __device__ __forceinline__ void bsolve_blocks(const Slots<C>& sl, Acc (&al)[C::N
       const double p64 = (double)(REFINE ? L.rdiag[r] * sc.r : L.rdiag[r]) - (J >= 0 ? L.d64[r] : 0.0);
       Acc X;
       float dm = 0.f;
-      const int f = diag_factor_inv<-1, REFINE>(acc_neg(A), X, dm, p64, L.dinv, L.diag);
+      const int f = diag_factor_inv<-1, CORR>(acc_neg(A), X, dm, p64, L.dinv, L.diag);
       Op::store(L.dinv, Op::frag(X), nat);
-      if (REFINE && d.corr) {
+      if (CORR) {
         Acc F;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

@@ -43,7 +43,7 @@ struct Dims {
   int tap_rel;       // 1: each tap's DFT referenced to its own first pulse
   int steer_bin;     // 1: steering vectors given per Doppler bin, [P][S][D]
   int sub;           // array elements summed into each channel C (>= 1)
-  int corr;          // 1: the blocked solve corrects its panels (with refinement)
+  int corr;          // 1: the blocked solve's factorisation is the corrected one (with refinement)
 };
 
 // The N range cells that train block b, as two runs: cells a0 .. a0+nl-1 and

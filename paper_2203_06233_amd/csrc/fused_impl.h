@@ -132,18 +132,19 @@ struct LdsR {
 // in the solve's register order (operands swapped), so the factorisation
 // starts on the accumulators: going through a packed copy in LDS instead took
 // 14 % of the kernel (39 of 274 thousand cycles per system at 96 DOF).  With
-// REFINE the blocks are also stored in LDS for the FP64 residual and the
+// refinement the blocks are also stored in LDS for the FP64 residual and the
 // solver's exchange blocks follow them; without, those reuse the staging
 // bytes.
-template <int NB, int NS, int NSL, int NSM, int NW, int MODE, bool REFINE>
+template <int NB, int NS, int NSL, int NSM, int NW, int MODE, int LEVEL>
 __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, const float2* __restrict__ steer,
                                               float2* __restrict__ wout, int* __restrict__ info_out,
                                               const Dims& d, int sys) {
+  constexpr bool REFINE = LEVEL != kPlain;
   using C = CovCfg<16 * NB, NW, MODE>;
   using B = BCfg<NSL, NSM, NW>;
   static_assert(C::TPW == NSL, "one covariance tile per L slot");
   constexpr int RBYTES = NB * (NB + 1) / 2 * kBlk * 4;
-  constexpr int EXCH = (int)B::lds_bytes(NB, NS, REFINE);
+  constexpr int EXCH = (int)B::lds_bytes(NB, NS, LEVEL);
   constexpr int B2 = REFINE ? RBYTES + EXCH : EXCH;
   constexpr int BYTES = C::LDS_BYTES > B2 ? C::LDS_BYTES : B2;
   __shared__ __align__(16) unsigned char lds[BYTES];
@@ -171,7 +172,7 @@ __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, c
   const SysScale sc(REFINE ? mean + dl : 1.f);
 
   float* const Rb = reinterpret_cast<float*>(lds);
-  const SolveLds<B, REFINE> L(lds + (REFINE ? RBYTES : 0), sl.NB, sl.NS);
+  const SolveLds<B, LEVEL> L(lds + (REFINE ? RBYTES : 0), sl.NB, sl.NS);
   const int lane = lane_tid() & 63, m = lane & 15, q = lane >> 4, nat = nat_ofs();
 #pragma unroll
   for (int t = 0; t < NSL; ++t) {
@@ -211,7 +212,7 @@ __device__ __forceinline__ void bfused_system(const float2* __restrict__ snap, c
   // the R_L blocks are dead after the last residual: u of that step is kept
   // there when it fits (their number at run time covers NS NB blocks)
   const bool park = REFINE && sl.NB + 1 >= 2 * sl.NS;
-  bsolve_blocks<B, REFINE>(sl, al, am, L, LdsR{Rb, sl.NB}, V, wout + (long long)sys * d.S * D,
+  bsolve_blocks<B, LEVEL>(sl, al, am, L, LdsR{Rb, sl.NB}, V, wout + (long long)sys * d.S * D,
                            info_out ? info_out + sys : nullptr, d, park ? Rb : nullptr, sc);
 }
 
@@ -229,16 +230,16 @@ constexpr int bfused_min_waves() {
   return NW <= 2 ? 3 : 1;
 }
 
-template <int NB, int NS, int NSL, int NSM, int NW, int MODE, bool REFINE>
+template <int NB, int NS, int NSL, int NSM, int NW, int MODE, int LEVEL>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(bfused_min_waves<NB, NS, NW>())))
 void bfused_kernel(const float2* __restrict__ snap,
                                                          const float2* __restrict__ steer,
                                                          float2* __restrict__ wout, int* __restrict__ info_out,
                                                          Dims d) {
-  bfused_system<NB, NS, NSL, NSM, NW, MODE, REFINE>(snap, steer, wout, info_out, d, blockIdx.x);
+  bfused_system<NB, NS, NSL, NSM, NW, MODE, LEVEL>(snap, steer, wout, info_out, d, blockIdx.x);
 }
 
-template <int NB, int NS, int NSL, int NSM, int NW, int MODE, bool REFINE>
+template <int NB, int NS, int NSL, int NSM, int NW, int MODE, int LEVEL>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(bfused_min_waves<NB, NS, NW>())))
 void bfused_batched_kernel(const ProbDesc* __restrict__ desc, int n,
                                                                  long long total, unsigned long long* queue) {
@@ -252,7 +253,7 @@ void bfused_batched_kernel(const ProbDesc* __restrict__ desc, int n,
     }
     const ProbDesc& pd = desc[lo];
     const Dims d = pd.d;
-    bfused_system<NB, NS, NSL, NSM, NW, MODE, REFINE>(pd.snap, pd.steer, pd.w, pd.info, d, (int)(g - pd.sys_begin));
+    bfused_system<NB, NS, NSL, NSM, NW, MODE, LEVEL>(pd.snap, pd.steer, pd.w, pd.info, d, (int)(g - pd.sys_begin));
     __syncthreads();
   }
 }

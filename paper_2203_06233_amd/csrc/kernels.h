@@ -41,6 +41,7 @@ hipError_t launch_doppler_batched(int P, const ProbDesc* desc, const BatchIndex&
 // table (all fused_supported, one precision; max_dof / max_steer the largest
 // D and S): workgroups take systems from the work queue `queue`, a counter
 // that must be zero at launch.
+// refine: 0, 1, or 2 where the blocked solve takes its corrected form.
 hipError_t launch_fused_batched(const ProbDesc* desc, int n, long long total_sys, int max_dof, int max_steer,
                                 int prec, int refine, int ty, hipStream_t st, unsigned long long* queue);
 

@@ -136,7 +136,7 @@ __device__ __forceinline__ void diag_cols_work(Diag<false>& s, Acc (&L)[NB * (NB
 // difference.
 template <int NB, int NS, int J>
 __device__ __forceinline__ void fact_step(Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[NS * NB], int& fail, double* d64,
-                                          const float* rdiag, float* rows) {
+                                          const float* rdiag) {
   const int lane = lane_tid() & 63;
 #pragma unroll
   for (int I = J + 1; I < NB; ++I) {
@@ -156,11 +156,11 @@ __device__ __forceinline__ void fact_step(Acc (&L)[NB * (NB + 1) / 2], Acc (&M)[
     mma_pqh<true>(L[tri(J + 1, J + 1)], L[tri(J + 1, J)], L[tri(J + 1, J)]);
     const int m = lane & 15;
     Diag<false> s;
-    diag_begin(s, L[tri(J + 1, J + 1)], (double)rdiag[16 * (J + 1) + m] - d64[16 * (J + 1) + m], rows);
+    diag_begin(s, L[tri(J + 1, J + 1)], (double)rdiag[16 * (J + 1) + m] - d64[16 * (J + 1) + m]);
     diag_cols_work<NB, NS, J, 0>(s, L, M);
     fail = (fail == 0 && s.fail != 0) ? 16 * (J + 1) + s.fail : fail;
     L[tri(J + 1, J + 1)] = diag_end<1>(s);
-    fact_step<NB, NS, J + 1>(L, M, fail, d64, rdiag, rows);
+    fact_step<NB, NS, J + 1>(L, M, fail, d64, rdiag);
   }
 }
 
@@ -296,16 +296,15 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
       Acc a;
       float2 v[4];
       if (I == J) {
-        // the factorisation reads a diagonal block above its diagonal alone,
-        // which comes from the lower triangle: element (r, c) is conj(R[c][r])
-        const float2* const p = R + min(r, D - 1);
+        // both triangles from the lower one, diagonal real
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int c = 16 * J + 4 * q + i;
-          const float2 x = p[(I == NB - 1 ? min(c, D - 1) : c) * D];
-          const bool ok = I < NB - 1 || (c < D && r < D);
+          const int hi = max(c, r), lo = min(c, r);
+          const float2 x = I < NB - 1 ? R[hi * D + lo] : R[min(hi, D - 1) * D + min(lo, D - 1)];
+          const bool ok = I < NB - 1 || hi < D;
           a.re[i] = ok ? x.x : r == c ? 1.f : 0.f;
-          a.im[i] = ok ? -x.y : 0.f;
+          a.im[i] = ok && c != r ? (c > r ? -x.y : x.y) : 0.f;
           if (c == r) rdiag[r] = a.re[i];
         }
       } else {
@@ -326,10 +325,10 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
   {
     Acc X;
     float unused;
-    fail = diag_factor_inv<1, false>(L[0], X, unused, (double)blk_diag(L[0]), tb, nullptr);
+    fail = diag_factor_inv<1, false>(L[0], X, unused, (double)blk_diag(L[0]), nullptr, nullptr);
     L[0] = X;
   }
-  fact_step<NB, G, 0>(L, M, fail, d64, rdiag, tb);  // tb is free until the back solve
+  fact_step<NB, G, 0>(L, M, fail, d64, rdiag);
   if (fail) {
     for (int e = lane; e < S * D; e += 64) W[e] = make_float2(0.f, 0.f);
     if (lane == 0 && info) *info = fail;

@@ -16,7 +16,7 @@ from tests.test_gpu_parity import solve_variant
 pytestmark = pytest.mark.gpu
 
 # (C, T, S) off the tuned classes, at the edges of their block columns
-SHAPES = [(5, 3, 24), (11, 3, 40), (16, 3, 33), (49, 1, 16), (17, 3, 40), (16, 4, 8), (28, 3, 48), (32, 3, 64),
+SHAPES = [(5, 3, 24), (8, 3, 40), (11, 3, 40), (16, 3, 33), (49, 1, 16), (17, 3, 40), (16, 4, 8), (28, 3, 48), (32, 3, 64),
           (33, 3, 16), (40, 3, 20), (32, 4, 64), (43, 3, 16), (64, 3, 31)]
 
 
@@ -47,3 +47,28 @@ def test_refined_weights_as_close_as_the_column_sweep(shape, kind, precision, ep
         sweep = error()
     print("refined", shape, kind, precision, eps, float(got.max()), float(sweep.max()), flush=True)
     assert np.all(got <= np.maximum(sweep.max(), 6 * U32))
+
+
+@pytest.mark.parametrize("steps", [2, 4])
+@pytest.mark.parametrize("shape", [(5, 3, 24), (10, 3, 50), (16, 3, 33), (17, 3, 40), (32, 3, 64), (40, 3, 20), (64, 3, 16)],
+                         ids=str)
+def test_more_steps_and_one_cube_as_in_a_batch(shape, steps):
+    """Several requested steps on the default route, by stage and fused, and
+    two cubes of the class in one call with the bits they have alone."""
+    stap = binding()
+    C, T, S = shape
+    D, P, B = C * T, 32, 2
+    wl = synth.Workload("steps", C, P, 2 * D * B, T, B, S, cnr_db=40.0, seed=6)
+    cube, V = dev(synth.make_cube(wl)), dev(synth.steering(wl))
+    prob = prob_of(wl, "fp32", steps)
+    X = stap.doppler(prob, cube)
+    cov = stap.covariance(prob, X)[0]
+    want, _, _ = orc.solve_weights(host(cov).astype(np.complex128), synth.steering(wl))
+    w, info = stap.solve_weights(prob, cov, V)
+    assert np.all(host(info) == 0) and metrics.per_system_rel_err(host(w), want).max() <= 6 * U32
+    if D <= 128:
+        w, info = stap.covariance_solve(prob, X, V)
+        assert np.all(host(info) == 0) and metrics.per_system_rel_err(host(w), want).max() <= 6 * U32
+    one = host(stap.run([prob], [cube], [V])[0])
+    for p in stap.run([prob] * 2, [cube] * 2, [V] * 2):
+        assert np.array_equal(host(p), one)
