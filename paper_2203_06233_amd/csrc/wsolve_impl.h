@@ -295,30 +295,36 @@ __device__ __forceinline__ void wsolve_system(const float2* __restrict__ R, cons
       const int r = 16 * I + m;
       Acc a;
       float2 v[4];
-      if (I == J) {
-        // both triangles from the lower one, diagonal real
+      if (J == NB - 1) load_row4<true>(R, r, 16 * J + 4 * q, D, D, v);
+      else load_row4<false>(R, r, 16 * J + 4 * q, D, D, v);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int c = 16 * J + 4 * q + i;
-          const int hi = max(c, r), lo = min(c, r);
-          const float2 x = I < NB - 1 ? R[hi * D + lo] : R[min(hi, D - 1) * D + min(lo, D - 1)];
-          const bool ok = I < NB - 1 || hi < D;
-          a.re[i] = ok ? x.x : r == c ? 1.f : 0.f;
-          a.im[i] = ok && c != r ? (c > r ? -x.y : x.y) : 0.f;
-          if (c == r) rdiag[r] = a.re[i];
-        }
-      } else {
-        load_row4<false>(R, r, 16 * J + 4 * q, D, D, v);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          a.re[i] = v[i].x;
-          a.im[i] = v[i].y;
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int c = 16 * J + 4 * q + i;
+        a.re[i] = I == J && r >= D && c == r ? 1.f : v[i].x;
+        a.im[i] = v[i].y;
+        if (I == J && c == r) rdiag[r] = a.re[i];
       }
       L[tri(I, J)] = a;
     }
   }
   load_m<NB, G>(steer, 0, D, S, M);
+  // both triangles of the diagonal blocks from the lower one, diagonal real; a
+  // wave's LDS accesses keep their order (reading the mirrored elements from
+  // memory instead costs 5 % of the solve)
+#pragma unroll
+  for (int I = 0; I < NB; ++I) {
+    float* const blk = tb + I * kBlk;
+    Acc a = L[tri(I, I)];
+    blk_store(blk, a, nat);
+    const Acc T = blk_load_t(blk);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = 4 * q + i;
+      a.re[i] = c > m ? T.re[i] : a.re[i];
+      a.im[i] = c > m ? -T.im[i] : c == m ? 0.f : a.im[i];
+    }
+    L[tri(I, I)] = a;
+  }
 
   // ---- factorisation with the forward solve of the first steering rows
   int fail = 0;
