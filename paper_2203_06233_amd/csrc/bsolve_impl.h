@@ -688,12 +688,11 @@ struct SysScale {
 // Solve one system (D <= 16 NB, S <= 16 NS, lslots(NB) <= NSL,
 // mslots(NB, NS) <= NSM).  al holds the wave's blocks of minus the loaded
 // covariance (identity beyond D, diagonal blocks with both triangles), with
-// refinement times sc.r, am
-// those of -M: blocks still to be finished are kept negated, so that every
-// update adds (x -= P Q^H is -x += P Q^H) and the panel product with
-// -Linv_JJ restores the sign, all exactly.  L.rdiag holds the loaded diagonal
-// of the diagonal blocks, unscaled
-// (written by the wave that owns them) and L.d64 zeros, visible after the
+// refinement times sc.r, am those of -M: blocks still to be finished are kept
+// negated, so that every update adds (x -= P Q^H is -x += P Q^H) and the panel
+// product with -Linv_JJ restores the sign, all exactly.  L.rdiag holds the
+// loaded diagonal of the diagonal blocks, unscaled (written by the wave that
+// owns them), and L.d64 zeros, visible after the
 // next barrier.  With refinement src.get(J, I) yields, on lane (m, q), R_L[16J +
 // 4q + s][16I + m], s = 0..3; it must stay readable for the whole call.  W is
 // this system's [S][D] output, info its status word (may be null).  park
