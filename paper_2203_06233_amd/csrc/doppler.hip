@@ -54,7 +54,11 @@ struct FftShape {
   static constexpr int RT = !WIDE ? 256 / P2 : P == 64 ? 128 : P == 128 ? 64 : P >= 256 ? 32 : 256 / P2;
   static constexpr int NT = P2 * RT;
   static constexpr int WPE = P == 512 ? 1 : P == 256 && !WIDE ? 3 : 4;
-  static constexpr int ELEMS = 1;  // elements loaded at a time (subarrays)
+  // Elements loaded at a time (subarrays): four where a thread has eight
+  // samples of each, so that enough loads are in flight (32 pulses, 6 channels
+  // of 25 elements x 2000 cells: 19.2 us with one, 13.8 with four; 64 pulses,
+  // 6 of 10 x 6154: 52.6 and 50.0).  From 128 pulses on one fills the registers.
+  static constexpr int ELEMS = !WIDE && P <= 64 ? 4 : 1;
   // Whether the compiler is kept from gathering all window, twiddle and
   // address values of an unrolled loop before their use: only where the
   // registers need it (256 pulses, narrow, 8 channels x 1024 cells: 12.4 us

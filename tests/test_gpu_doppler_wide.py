@@ -54,3 +54,11 @@ def test_cubes_that_are_wide_together(P, cubes):
         w, info = stap.covariance_solve(one, X, vs[i])
         assert np.all(host(info) == 0)
         assert np.array_equal(both[i], host(stap.inner_products(one, w, X))), i
+
+
+@pytest.mark.parametrize("outer", [False, True], ids=["", "pulse-outer"])
+@pytest.mark.parametrize("n_sub", [2, 3, 4, 5, 8, 11])
+@pytest.mark.parametrize("shape", [(3, 32, 130, 2), (2, 64, 95, 3), (5, 32, 33, 1), (2, 128, 40, 1)], ids=str)
+def test_subarrays_on_narrow_tiles(shape, n_sub, outer):
+    """Elements read four at a time (32 and 64 pulses), with and without a remainder."""
+    test_doppler_wide_tiles((*shape, n_sub), "absolute", outer)
